@@ -89,12 +89,12 @@ def kernel_models(sc, res, N):
     name (all VALU-bound: see the design doc), from the library's counters of that
     query:
 
-    expand_sim (particle stage, per-phase mode): per simulated pair
-      OPS_SIM_PAIR, per tested waypoint OPS_SIM_WP_UNIFORM + OPS_SIM_WP_PER_BOX
+    expand_sim (the expansion, per-phase mode): the pair terms below, and per
+      simulated pair OPS_SIM_PAIR, per tested waypoint OPS_SIM_WP_UNIFORM + OPS_SIM_WP_PER_BOX
       x n_obs + N x OPS_PARTICLE_WP, per waypoint-box test N x OPS_PARTICLE_BOX
       (the scope table's terms, with the measured waypoints and box tests);
-    expand (pair stage, per-phase mode): every pair OPS_PAIR, every pair past
-      the pre-prune OPS_GEOM + OPS_GEOM_PER_BOX x n_obs;
+    expand (its pair terms): every pair OPS_PAIR, every pair past the
+      pre-prune OPS_GEOM + OPS_GEOM_PER_BOX x n_obs;
     explore_single (every phase in one launch): the sum of the two.
     """
     sim = (OPS_SIM_PAIR * res["simulated"]
@@ -105,7 +105,8 @@ def kernel_models(sc, res, N):
     # pre-prunes are counted with them, so this is a slight undercount)
     geom = max(res["simulated"], res["partial_plans"] - res["preprune"] - res["dropped_steps"])
     pairs = OPS_PAIR * res["partial_plans"] + (OPS_GEOM + OPS_GEOM_PER_BOX * sc.n_obs) * geom
-    return {"expand_sim": sim, "expand": pairs, "explore_single": sim + pairs}
+    # (with the box model, the bench's, expand_sim is the whole expansion)
+    return {"expand_sim": sim + pairs, "expand": pairs, "explore_single": sim + pairs}
 
 
 def cpu_baseline(seconds, procs):

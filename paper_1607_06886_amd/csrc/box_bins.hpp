@@ -93,4 +93,84 @@ __device__ __forceinline__ void box_bins_query(const BoxBins* s, const float* lo
     }
 }
 
+// The same table built once per query in device memory, in the layout the
+// Explore kernels copy to LDS: 8 header words (org xyz, scale xyz, boxes,
+// words per set), then the sets lo_le[3][kBins][nw] and hi_ge[3][kBins][nw].
+constexpr int kBinHeader = 8;
+__host__ __device__ constexpr int bin_words(int n_obs) {
+    return kBinHeader + 2 * 3 * kBins * ((n_obs + 63) / 64) * 2;
+}
+
+// One workgroup; boxes b[o * 6 + (lo xyz, hi xyz)], out: bin_words(n) words.
+__device__ __forceinline__ void box_bins_write(const float* __restrict__ b, int n,
+                                               uint32_t* __restrict__ out) {
+    __shared__ float s_org[3], s_scale[3];
+    const int nw = (n + 63) / 64;
+    if (threadIdx.x < 3) {
+        const int a = threadIdx.x;
+        float lo = INFINITY, hi = -INFINITY;
+        for (int o = 0; o < n; ++o) {
+            lo = fminf(lo, b[o * 6 + a]);
+            hi = fmaxf(hi, b[o * 6 + 3 + a]);
+        }
+        const bool ok = n > 0 && hi > lo;
+        s_org[a] = ok ? lo : 0.0f;   // otherwise every box in bin 0
+        s_scale[a] = ok ? (float)kBins / (hi - lo) : 0.0f;
+        out[a] = __float_as_uint(s_org[a]);
+        out[3 + a] = __float_as_uint(s_scale[a]);
+    }
+    if (threadIdx.x == 0) {
+        out[6] = (uint32_t)n;
+        out[7] = (uint32_t)nw;
+    }
+    __syncthreads();
+    const int per = 3 * kBins * nw;
+    for (int t = threadIdx.x; t < 2 * per; t += blockDim.x) {
+        const bool ge = t >= per;
+        const int u = ge ? t - per : t;
+        const int w = u % nw, bn = (u / nw) % kBins, a = u / (nw * kBins);
+        unsigned long long bits = 0ull;
+        for (int k = 0; k < 64 && w * 64 + k < n; ++k) {
+            const float x = b[(w * 64 + k) * 6 + (ge ? 3 : 0) + a];
+            const int bx = (int)fminf(fmaxf((x - s_org[a]) * s_scale[a], 0.0f), (float)(kBins - 1));
+            if (ge ? bx >= bn : bx <= bn) bits |= 1ull << k;
+        }
+        out[kBinHeader + 2 * t] = (uint32_t)bits;
+        out[kBinHeader + 2 * t + 1] = (uint32_t)(bits >> 32);
+    }
+}
+
+// A copy of it in LDS.
+struct BinView {
+    float org[3], scale[3];
+    const unsigned long long* set;   // lo_le, then hi_ge
+    int nw;
+};
+
+// Candidate boxes (word w) of the bins idx = (bin(hi) on lo_le, bin(lo) on
+// hi_ge) per axis.  A range that is not finite needs no case of its own: NaN
+// ends fall in bin 0 and meet no box, infinite ones in the end bins.
+struct BinRange {
+    int le[3], ge[3];
+};
+
+__device__ __forceinline__ void bin_range(const BinView& v, const float* lo3, const float* hi3,
+                                          BinRange& r) {
+    const int per = 3 * kBins * v.nw;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float top = (float)(kBins - 1);
+        const int bh = (int)fminf(fmaxf((hi3[a] - v.org[a]) * v.scale[a], 0.0f), top);
+        const int bl = (int)fminf(fmaxf((lo3[a] - v.org[a]) * v.scale[a], 0.0f), top);
+        r.le[a] = (a * kBins + bh) * v.nw;
+        r.ge[a] = per + (a * kBins + bl) * v.nw;
+    }
+}
+
+__device__ __forceinline__ unsigned long long bin_candidates(const BinView& v, const BinRange& r,
+                                                             int w) {
+    return v.set[r.le[0] + w] & v.set[r.ge[0] + w] & v.set[r.le[1] + w] & v.set[r.ge[1] + w] &
+           v.set[r.le[2] + w] & v.set[r.ge[2] + w];
+}
+
 }  // namespace pump

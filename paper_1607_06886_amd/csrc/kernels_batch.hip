@@ -73,6 +73,15 @@ __global__ void k_b_cloud(BatchQuery* qs) {
     cloud_dev(Q.ra[0].D, const_cast<float*>(Q.ra[0].cloud), Q.N);
 }
 
+__global__ __launch_bounds__(256) void k_b_rank_tables(BatchQuery* qs, int S1) {
+    __shared__ float s_v[256], s_o[256];
+    __shared__ int s_r[256];
+    BatchQuery& Q = qs[blockIdx.y];
+    if ((int)blockIdx.x * (256 / Q.N) >= 3 * S1) return;
+    rank_tables_dev(Q.ra[0].D, Q.ra[0].cloud, const_cast<float*>(Q.ra[0].rank),
+                    const_cast<uint32_t*>(Q.ra[0].prefix), &Q.rank_nan, Q.N, S1, blockIdx.x, s_v, s_o, s_r);
+}
+
 __global__ void k_b_gcloud(BatchQuery* qs, int S1) {
     const BatchQuery& Q = qs[blockIdx.y];
     gcloud_dev(Q.ra[0].cloud, const_cast<float*>(Q.ra[0].gcloud), S1);
@@ -80,6 +89,10 @@ __global__ void k_b_gcloud(BatchQuery* qs, int S1) {
 
 __global__ void k_b_valid(BatchQuery* qs) {
     BatchQuery& Q = qs[blockIdx.y];
+    if (blockIdx.x == gridDim.x - 1) {   // the last workgroup: the box bins
+        box_bins_write(Q.obs, Q.ra[0].n_obs, const_cast<uint32_t*>(Q.ra[0].bins));
+        return;
+    }
     const float* g = Q.goal_box;
     mark_valid_dev(Q.X, Q.n_nodes, Q.obs, Q.ra[0].n_obs, g[0], g[1], g[2], g[3], g[4], g[5], Q.valid,
                    Q.goal, &Q.bad);
@@ -249,12 +262,11 @@ __global__ __launch_bounds__(256) void k_b_edge_cost(BatchQuery* qs) {
 // One kernel per particle count N (a schedule holds only queries of that N),
 // so each gets the registers its own N needs: two workgroups of 256 per CU
 // fit for N <= 128, one for N = 256.
-template <int N>
+template <int N, int CP>
 __global__ __launch_bounds__(256, 2) void k_b_explore(BatchQuery* qs, BatchSched sch,
                                                                     int* counter, BatchOut* outs) {
-    __shared__ float s_raw[kMaxObs * 6];
-    __shared__ float s_in[kMaxObs * 6];
-    __shared__ float s_out[kMaxObs * 6];
+    extern __shared__ __align__(16) char s_box[];
+    __shared__ __align__(16) char s_pair[CP == 0 ? pair_lds_bytes(256) : 16];
     __shared__ int s_w[16];
     __shared__ unsigned long long s_m[16];
     __shared__ long long s_ll[16];
@@ -290,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void k_b_explore(BatchQuery* qs, BatchSched
         t.open_cur = Q.open_a;
         t.open_next = Q.open_b;
         t.cap_pairs = Q.cap_pairs;
-        explore_team<N>(Q.ra, t, true, Q.n_nodes, s_raw, s_in, s_out, s_w, s_m, s_ll, &s_fail);
+        explore_team<N, CP>(Q.ra, t, true, Q.n_nodes, s_box, pair_lds(s_pair, 256), s_w, s_m, s_ll, &s_fail);
         if (t.rank == 0 && threadIdx.x == 0) {
             const Ctl* c = Q.ra[0].ctl;
             BatchOut& o = outs[qi];
@@ -455,9 +467,24 @@ __global__ void k_b_reset(BatchQuery* qs, int* counter) {
     for (int t = threadIdx.x; t < 2 * kMaxTeam; t += blockDim.x) Q.team_tot[t] = 0ull;
 }
 
+namespace {
+template <int CP>
+const void* explore_fn(int N) {
+    switch (N) {
+        case 32: return (const void*)k_b_explore<32, CP>;
+        case 64: return (const void*)k_b_explore<64, CP>;
+        case 128: return (const void*)k_b_explore<128, CP>;
+        default: return (const void*)k_b_explore<256, CP>;
+    }
+}
+const void* explore_fn(int N, int cp_model) {
+    return cp_model == 0 ? explore_fn<0>(N) : explore_fn<1>(N);
+}
+}  // namespace
+
 void launch_batch(hipStream_t s, BatchQuery* qs, int q, int N_max, int max_nodes, int S_max, int M,
                   int words, int explore_threads, int* counter, BatchOut* out,
-                  const BatchGroup* groups, int n_groups, bool smooth) {
+                  const BatchGroup* groups, int n_groups, bool smooth, int cp_model, int max_obs) {
     const int max_elems = std::max(max_nodes * 6, kMaxObs * 6);
     k_b_load<<<dim3((max_elems + 255) / 256, q), 256, 0, s>>>(qs);
     {
@@ -468,9 +495,11 @@ void launch_batch(hipStream_t s, BatchQuery* qs, int q, int N_max, int max_nodes
         k_b_dev_final<<<dim3((threads + 255) / 256, q), 256, 0, s>>>(qs, S_max);
     }
     k_b_cloud<<<dim3(S_max + 1, q), 256, 0, s>>>(qs);
+    if (cp_model == 0)
+        k_b_rank_tables<<<dim3(3 * (S_max + 1), q), 256, 0, s>>>(qs, S_max + 1);
     k_b_gcloud<<<dim3(1, q), 256, 0, s>>>(qs, S_max + 1);
     const int vmax = std::max(max_nodes, kMaxObs);
-    k_b_valid<<<dim3((vmax + 255) / 256, q), 256, 0, s>>>(qs);
+    k_b_valid<<<dim3((vmax + 255) / 256 + 1, q), 256, 0, s>>>(qs);
     k_b_zero_ebits<<<dim3(256, q), 256, 0, s>>>(qs);
     k_b_rm_check<<<dim3((max_nodes * 6 + 255) / 256, q), 256, 0, s>>>(qs);
     k_b_gw_near_rows<<<dim3(max_nodes, q), kNearThreads, 0, s>>>(qs);
@@ -488,12 +517,11 @@ void launch_batch(hipStream_t s, BatchQuery* qs, int q, int N_max, int max_nodes
     for (int g = 0; g < n_groups; ++g) {
         const BatchGroup& G = groups[g];
         int* ctr = counter + g;
-        switch (G.N) {
-            case 32: k_b_explore<32><<<G.blocks, explore_threads, 0, s>>>(qs, G.sch, ctr, out); break;
-            case 64: k_b_explore<64><<<G.blocks, explore_threads, 0, s>>>(qs, G.sch, ctr, out); break;
-            case 128: k_b_explore<128><<<G.blocks, explore_threads, 0, s>>>(qs, G.sch, ctr, out); break;
-            default: k_b_explore<256><<<G.blocks, explore_threads, 0, s>>>(qs, G.sch, ctr, out); break;
-        }
+        const void* fn = explore_fn(G.N, cp_model);
+        BatchSched sch = G.sch;
+        void* args[4] = {(void*)&qs, (void*)&sch, (void*)&ctr, (void*)&out};
+        (void)hipLaunchKernel(fn, dim3(G.blocks), dim3(explore_threads), args,
+                              team_lds_bytes(cp_model, max_obs), s);
     }
     k_b_goal_collect<<<q, 1024, 0, s>>>(qs);
     k_b_front<<<q, 256, 0, s>>>(qs);
@@ -512,16 +540,11 @@ void launch_batch(hipStream_t s, BatchQuery* qs, int q, int N_max, int max_nodes
     }
 }
 
-int batch_explore_per_cu(int N, int threads) {
-    const void* fn;
-    switch (N) {
-        case 32: fn = (const void*)k_b_explore<32>; break;
-        case 64: fn = (const void*)k_b_explore<64>; break;
-        case 128: fn = (const void*)k_b_explore<128>; break;
-        default: fn = (const void*)k_b_explore<256>; break;
-    }
+int batch_explore_per_cu(int N, int threads, int cp_model, int max_obs) {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, 0) != hipSuccess) return 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, explore_fn(N, cp_model), threads,
+                                                     team_lds_bytes(cp_model, max_obs)) != hipSuccess)
+        return 0;
     return n;
 }
 

@@ -1,6 +1,8 @@
 // Explore (Alg. 4): one round = expand the group B to every neighbour,
 // RemoveDominated, retire B, select the next group.
-#include "explore_ops.hpp"
+#include <algorithm>
+
+#include "explore_lane.hpp"
 
 namespace pump {
 
@@ -188,6 +190,10 @@ void launch_counters_clear(hipStream_t s, const RoundArgs& a) {
     k_counters_reduce<<<kReduceBlocks, 256, 0, s>>>(a, 0);
 }
 
+// workgroups of k_expand_box: three per CU, what fits at once, so that each
+// takes many passes and drains its last records only once
+constexpr int kBoxGrid = 768;
+
 static int part_grid(long long n, int per_block) {
     long long b = (n + per_block - 1) / per_block;
     if (b < 1) b = 1;
@@ -197,18 +203,47 @@ static int part_grid(long long n, int per_block) {
 
 // ---------------------------------------------------------------------------
 // Expansion (Alg. 4: every pair (p in B, x in N(p.head)) forms q with
-// Cost and CP_hat, then the CP cutoff): k_expand_pairs runs the first part
-// with one pair per lane and queues the pairs whose particles must be
-// simulated; k_expand_sim simulates them with one pair per wave.
-//
-// The queue records of a workgroup gather in LDS (one LDS atomic per wave)
-// and go out in one coalesced copy, behind one global atomic, after each
-// 256-pair pass that queued any.  The box-model pair stage runs six waves
-// per SIMD (80 VGPRs, a few values spilled; 20 KB of LDS per workgroup): on
-// the 20,000-sample indoor query it took 1.48 ms per query against 1.59 ms
-// at four waves (105 VGPRs, a 768-record stage) and 1.61 ms at eight.  The
-// half-space model's, with more live values, stays at four.
+// Cost and CP_hat, then the CP cutoff).  The box model runs in one kernel
+// (k_expand_box, explore_lane.hpp).  The half-space model keeps two:
+// k_expand_pairs with one pair per lane queues the pairs whose particles must
+// be simulated; k_expand_sim simulates them with one pair per wave.
 // ---------------------------------------------------------------------------
+template <int N>
+__global__ __launch_bounds__(256, 3) void k_expand_box(RoundArgs a) {
+    extern __shared__ __align__(16) char s_box[];
+    __shared__ __align__(16) char s_pair[pair_lds_bytes(256)];
+    __shared__ long long s_ll[4];
+    const BoxLds box = stage_box_lds(a, s_box);
+    const PairLds pl = pair_lds(s_pair, 256);
+    if (threadIdx.x < 3) pl.cnt[threadIdx.x] = 0;
+    __syncthreads();
+    // pairs [a.q0, q_end) of the round: all of them, or one chunk
+    const int q_end = a.chunked ? a.q0 + a.ctl->chunk_n : a.ctl->n_pairs;
+    float gl[3], gh[3];
+    for (int k = 0; k < 3; ++k) { gl[k] = a.gcloud[k]; gh[k] = a.gcloud[3 + k]; }
+    PairCounts n;
+    expand_box_block<N>(a, a.q0, q_end, blockIdx.x, gridDim.x, a.ctl->n_B, box, gl, gh, pl, n);
+    // (wave-uniform counts: one lane of each wave brings them)
+    const bool first = (threadIdx.x & 63) == 0;
+    const long long t_sim = block_sum(first ? n.sim : 0, s_ll);
+    const long long t_pre = block_sum(first ? n.pre : 0, s_ll);
+    const long long t_drop = block_sum(first ? n.drop : 0, s_ll);
+    const long long t_flag = block_sum(first ? n.flag : 0, s_ll);
+    const long long t_wp = block_sum(first ? n.wp : 0, s_ll);
+    const long long t_bt = block_sum(first ? n.bt : 0, s_ll);
+    if (threadIdx.x == 0 && !a.quiet) {
+        part_add(a, kPartSimulated, t_sim);
+        part_add(a, kPartPreprune, t_pre);
+        part_add(a, kPartDropped, t_drop);
+        part_add(a, kPartFlagged, t_flag);
+        part_add(a, kPartWaypoints, t_wp);
+        part_add(a, kPartBoxTests, t_bt);
+    }
+}
+
+// The half-space model's queue records gather in LDS per workgroup (one LDS
+// atomic per wave) and go out in one coalesced copy, behind one global
+// atomic, after each 256-pair pass that queued any.
 constexpr int kTaskStage = 256;   // records staged per workgroup (8 KB): one pass
 
 __device__ __forceinline__ void flush_tasks(const RoundArgs& a, SimTask* s_tq, int* s_tn, int* s_tb) {
@@ -223,22 +258,19 @@ __device__ __forceinline__ void flush_tasks(const RoundArgs& a, SimTask* s_tq, i
     __syncthreads();
 }
 
-template <int N, int CP>
-__global__ __launch_bounds__(256, CP == 0 ? 6 : 4) void k_expand_pairs(RoundArgs a) {
+template <int N>
+__global__ __launch_bounds__(256, 4) void k_expand_pairs(RoundArgs a) {
     __shared__ float s_raw[kMaxObs * 6];
-    __shared__ float s_out[kMaxObs * 6];
     __shared__ SimTask s_tq[kTaskStage];
     __shared__ int s_tn, s_tb;
     __shared__ long long s_ll[4];
-    stage_obstacles_block(a.obs, a.n_obs, s_raw, nullptr, s_out);
+    stage_obstacles_block(a.obs, a.n_obs, s_raw);
     if (threadIdx.x == 0) s_tn = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63;
     // pairs [a.q0, q_end) of the round: all of them, or one chunk
     const int q_end = a.chunked ? a.q0 + a.ctl->chunk_n : a.ctl->n_pairs;
     const int n_B = a.ctl->n_B;
-    float gl[3], gh[3];
-    for (int k = 0; k < 3; ++k) { gl[k] = a.gcloud[k]; gh[k] = a.gcloud[3 + k]; }
     long long n_sim = 0, n_pre = 0, n_drop = 0;
     // workgroup passes of 256 pairs (the same count in every thread)
     for (int base = a.q0 + blockIdx.x * 256; base < q_end; base += gridDim.x * 256) {
@@ -248,8 +280,7 @@ __global__ __launch_bounds__(256, CP == 0 ? 6 : 4) void k_expand_pairs(RoundArgs
         int st = 0;
         if (tile < q_end) {   // the wave's pairs
             const int grp = wave_group_of(a.b_off, n_B, tile, q);
-            st = q < q_end ? expand_pair<N, CP>(a, q, grp, s_raw, s_out, gl, gh, n_sim, n_pre, n_drop,
-                                                tk) : 0;
+            st = q < q_end ? expand_pair_hsmc<N>(a, q, grp, s_raw, n_sim, n_pre, n_drop, tk) : 0;
         }
         const unsigned long long need = __ballot(st == 2);
         int wb = 0;
@@ -270,25 +301,17 @@ __global__ __launch_bounds__(256, CP == 0 ? 6 : 4) void k_expand_pairs(RoundArgs
     }
 }
 
-// CP = 0: the box predicate, 1: the half-space model (one instantiation each,
-// so the box kernel keeps only its own registers: 4 waves per SIMD).
-template <int N, int CP>
+template <int N>
 __global__ __launch_bounds__(256) void k_expand_sim(RoundArgs a) {
     __shared__ float s_raw[kMaxObs * 6];
-    __shared__ float s_in[kMaxObs * 6];
-    __shared__ float s_out[kMaxObs * 6];
     __shared__ long long s_ll[4];
-    stage_obstacles_block(a.obs, a.n_obs, s_raw, s_in, s_out);
+    stage_obstacles_block(a.obs, a.n_obs, s_raw);
     __syncthreads();
     const int lane = threadIdx.x & 63;
     const int n_tasks = a.ctl->n_tasks;
     long long n_pre = 0, n_flag = 0, n_wp = 0, n_bt = 0;
-    for (int task = blockIdx.x * 4 + (threadIdx.x >> 6); task < n_tasks; task += gridDim.x * 4) {
-        if (CP == 1)
-            simulate_pair_hsmc<N>(a, task, s_raw, n_pre, n_flag, n_wp, n_bt);
-        else
-            simulate_pair_box<N>(a, task, s_raw, s_in, s_out, n_pre, n_flag, n_wp, n_bt);
-    }
+    for (int task = blockIdx.x * 4 + (threadIdx.x >> 6); task < n_tasks; task += gridDim.x * 4)
+        simulate_pair_hsmc<N>(a, task, s_raw, n_pre, n_flag, n_wp, n_bt);
     // the counts are wave-uniform: lane 0 brings them
     const long long t_pre = block_sum(lane == 0 ? n_pre : 0, s_ll);
     const long long t_flag = block_sum(lane == 0 ? n_flag : 0, s_ll);
@@ -303,37 +326,28 @@ __global__ __launch_bounds__(256) void k_expand_sim(RoundArgs a) {
 }
 
 template <int N>
-static void launch_expand_n(hipStream_t s, const RoundArgs& a, unsigned blocks, unsigned sim_blocks,
-                            int part) {
-    if (part & 1) {
-        if (a.cp_model == 1)
-            k_expand_pairs<N, 1><<<blocks, 256, 0, s>>>(a);
-        else
-            k_expand_pairs<N, 0><<<blocks, 256, 0, s>>>(a);
+static void launch_expand_n(hipStream_t s, const RoundArgs& a, int32_t n_pairs, int part) {
+    if (a.cp_model == 0) {
+        if (part & 2)
+            k_expand_box<N><<<(unsigned)std::min(part_grid(n_pairs, 16), kBoxGrid), 256,
+                              box_lds_bytes(a.n_obs), s>>>(a);
+        return;
     }
-    if (part & 2) {
-        if (a.cp_model == 1)
-            k_expand_sim<N, 1><<<sim_blocks, 256, 0, s>>>(a);
-        else
-            k_expand_sim<N, 0><<<sim_blocks, 256, 0, s>>>(a);
-    }
+    // pair stage: a workgroup per 256 pairs, at most kPartSlots of them (each
+    // owns a counter slot); the particle kernel's grid covers the worst case
+    // (every pair queued), capped; its waves stride over the queue length
+    // read on the device
+    if (part & 1) k_expand_pairs<N><<<part_grid(n_pairs, 256), 256, 0, s>>>(a);
+    if (part & 2) k_expand_sim<N><<<part_grid(n_pairs, 4), 256, 0, s>>>(a);
 }
 
 void launch_expand(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, int part) {
     if (n_pairs <= 0) return;
-    // pair stage: a workgroup per 256 pairs, at most kPartSlots of them (each
-    // owns a counter slot); one pass per workgroup measured faster than four
-    // (indoor query: 1.92 -> 1.59 ms), more workgroups hiding the loads'
-    // latency better than fewer that flush their queue records less often
-    const int blocks = part_grid(n_pairs, 256);
-    // the particle kernel's grid covers the worst case (every pair queued),
-    // capped; its waves stride over the queue length read on the device
-    const int sim_blocks = part_grid(n_pairs, 4);
     switch (N) {
-        case 32: launch_expand_n<32>(s, a, (unsigned)blocks, (unsigned)sim_blocks, part); break;
-        case 64: launch_expand_n<64>(s, a, (unsigned)blocks, (unsigned)sim_blocks, part); break;
-        case 128: launch_expand_n<128>(s, a, (unsigned)blocks, (unsigned)sim_blocks, part); break;
-        default: launch_expand_n<256>(s, a, (unsigned)blocks, (unsigned)sim_blocks, part); break;
+        case 32: launch_expand_n<32>(s, a, n_pairs, part); break;
+        case 64: launch_expand_n<64>(s, a, n_pairs, part); break;
+        case 128: launch_expand_n<128>(s, a, n_pairs, part); break;
+        default: launch_expand_n<256>(s, a, n_pairs, part); break;
     }
 }
 

@@ -1,5 +1,6 @@
 // Per-query setup kernels: the particle deviation table and BuildGraph (Alg. 3).
 // The bodies live in setup_ops.hpp.
+#include "rank_tables.hpp"
 #include "setup_ops.hpp"
 
 namespace pump {
@@ -43,6 +44,22 @@ __global__ void k_gcloud(const float* __restrict__ cloud, float* __restrict__ g,
     gcloud_dev(cloud, g, S1);
 }
 
+__global__ __launch_bounds__(256) void k_rank_tables(const float* __restrict__ D,
+                                                     const float* __restrict__ cloud,
+                                                     float* __restrict__ rank,
+                                                     uint32_t* __restrict__ prefix,
+                                                     int32_t* __restrict__ has_nan, int N, int S1) {
+    __shared__ float s_v[256], s_o[256];
+    __shared__ int s_r[256];
+    rank_tables_dev(D, cloud, rank, prefix, has_nan, N, S1, blockIdx.x, s_v, s_o, s_r);
+}
+
+void launch_rank_tables(hipStream_t s, const float* D, const float* cloud, float* rank,
+                        uint32_t* prefix, int32_t* has_nan, int N, int S1) {
+    const int per = 256 / N;
+    k_rank_tables<<<(S1 * 3 + per - 1) / per, 256, 0, s>>>(D, cloud, rank, prefix, has_nan, N, S1);
+}
+
 void launch_deviation_table(hipStream_t s, const float* noise, float* D, float* cloud,
                             float* gcloud, int N, int S_max, const double* Acl, const double* L,
                             double* scratch) {
@@ -75,15 +92,21 @@ void launch_deviation_table_lqg(hipStream_t s, const float* noise, const float* 
 __global__ void k_mark_valid(const float* __restrict__ X, int n, const float* __restrict__ obs,
                              int n_obs, float g0, float g1, float g2, float g3, float g4, float g5,
                              uint8_t* __restrict__ valid, uint8_t* __restrict__ goal,
-                             int32_t* __restrict__ bad) {
+                             int32_t* __restrict__ bad, uint32_t* __restrict__ bins) {
+    // the last workgroup, when asked for, builds the box bins
+    if (bins && blockIdx.x == gridDim.x - 1) {
+        box_bins_write(obs, n_obs, bins);
+        return;
+    }
     mark_valid_dev(X, n, obs, n_obs, g0, g1, g2, g3, g4, g5, valid, goal, bad);
 }
 
 void launch_mark_valid(hipStream_t s, const float* X, int n_nodes, const float* obs, int n_obs,
-                       const float* gb, uint8_t* valid, uint8_t* goal, int32_t* bad) {
+                       const float* gb, uint8_t* valid, uint8_t* goal, int32_t* bad,
+                       uint32_t* bins) {
     int n = n_nodes > n_obs ? n_nodes : n_obs;
-    k_mark_valid<<<(n + 255) / 256, 256, 0, s>>>(X, n_nodes, obs, n_obs, gb[0], gb[1], gb[2],
-                                                 gb[3], gb[4], gb[5], valid, goal, bad);
+    k_mark_valid<<<(n + 255) / 256 + (bins ? 1 : 0), 256, 0, s>>>(
+        X, n_nodes, obs, n_obs, gb[0], gb[1], gb[2], gb[3], gb[4], gb[5], valid, goal, bad, bins);
 }
 
 // ---- BuildGraph pass 1 stages (setup_ops.hpp) ----

@@ -9,8 +9,10 @@
 #include <string>
 #include <vector>
 
+#include "box_bins.hpp"
 #include "host_consts.hpp"
 #include "pump_internal.hpp"
+#include "rank_tables.hpp"
 
 using namespace pump;
 
@@ -41,7 +43,12 @@ struct pump_ctx {
     double* dev_scratch = nullptr;  // deviation-table chunk states
     float* cloud = nullptr;
     float* gcloud = nullptr;
-    int32_t* dev_ints = nullptr;  // [0] n_nodes, [1] bad-input flag
+    float* rank = nullptr;          // rank rows and prefix sets of D (box model)
+    uint32_t* prefix = nullptr;
+    uint32_t* bins = nullptr;       // box bins
+    // [0] n_nodes, [1] bad-input flag, [2] near and [3] exact-queue counts,
+    // [4] edges, [7] the deviation table holds a NaN
+    int32_t* dev_ints = nullptr;
     // graph
     uint32_t* ebits = nullptr;
     int32_t* wstart = nullptr;  // pass 2: CSR slot of each bit-matrix word's first edge
@@ -151,6 +158,10 @@ RoundArgs round_args(pump_ctx* c) {
     a.D = c->D;
     a.cloud = c->cloud;
     a.gcloud = c->gcloud;
+    a.rank = c->rank;
+    a.prefix = c->prefix;
+    a.rank_nan = c->dev_ints + 7;
+    a.bins = c->bins;
     a.S_max = c->S_max;
     a.dt = c->dt;
     a.c_cut = c->c_cut;
@@ -329,7 +340,7 @@ int pump_destroy(pump_ctx* ctx) {
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     void* ptrs[] = {ctx->X, ctx->valid, ctx->goal, ctx->obs, ctx->noise_buf, ctx->noise_mc_buf,
                     ctx->noise_meas_buf, ctx->noise_mc_meas_buf,
-                    ctx->D, ctx->cloud, ctx->gcloud, ctx->dev_ints, ctx->ebits, ctx->wstart, ctx->deg,
+                    ctx->D, ctx->cloud, ctx->gcloud, ctx->rank, ctx->prefix, ctx->bins, ctx->dev_ints, ctx->ebits, ctx->wstart, ctx->deg,
                     ctx->row_ptr, ctx->col, ctx->esrc, ctx->etau, ctx->ecost, ctx->p_head, ctx->p_parent,
                     ctx->p_edge, ctx->p_step, ctx->p_pop, ctx->p_round, ctx->p_cost, ctx->p_mask,
                     ctx->p_state, ctx->stair, ctx->open_a, ctx->open_b, ctx->o_keep, ctx->o_inB,
@@ -410,6 +421,11 @@ int pump_create(const pump_config* cfg_in, void* hip_stream, pump_ctx** out) {
     A(dalloc(&ctx->dev_scratch, (size_t)kDevScratchPer * ((S + 15) / 16) * 3 * N));
     A(dalloc(&ctx->cloud, (S + 1) * 6));
     A(dalloc(&ctx->gcloud, 8));
+    if (cfg.cp_model == 0) {
+        A(dalloc(&ctx->rank, rank_floats((int)S + 1, N)));
+        A(dalloc(&ctx->prefix, prefix_words((int)S + 1, N)));
+    }
+    A(dalloc(&ctx->bins, (size_t)bin_words(kMaxObs)));
     A(dalloc(&ctx->dev_ints, 8));
     A(dalloc(&ctx->ebits, nn * ctx->words_per_row));
     A(dalloc(&ctx->wstart, nn * ctx->words_per_row));
@@ -451,7 +467,7 @@ int pump_create(const pump_config* cfg_in, void* hip_stream, pump_ctx** out) {
     A(hipMemset(ctx->part, 0, sizeof(long long) * kPartSlots * kPartK));
     {
         int dev = 0;
-        if (hipGetDevice(&dev) == hipSuccess) ctx->coop_blocks = coop_max_blocks(N);
+        if (hipGetDevice(&dev) == hipSuccess) ctx->coop_blocks = coop_max_blocks(N, cfg.cp_model, cfg.max_obstacles);
         // one workgroup per CU (PUMP_SINGLE_LAUNCH_WG_PER_CU may raise it):
         // each barrier costs a cache write-back and invalidation per
         // workgroup, which outweighs the extra waves of a second workgroup
@@ -589,6 +605,7 @@ int pump_setup(pump_ctx* ctx, const pump_problem* pr) {
     }
     float gb[6] = {pr->goal.lo[0], pr->goal.lo[1], pr->goal.lo[2],
                    pr->goal.hi[0], pr->goal.hi[1], pr->goal.hi[2]};
+    HIPCHK(hipMemsetAsync(ctx->dev_ints, 0, 8 * sizeof(int32_t), ctx->stream));
     tbeg(ctx, 0);
     if (cfg.estimator == 1)
         launch_deviation_table_lqg(ctx->stream, ctx->noise, ctx->noise_meas, ctx->D, ctx->cloud,
@@ -596,10 +613,12 @@ int pump_setup(pump_ctx* ctx, const pump_problem* pr) {
     else
         launch_deviation_table(ctx->stream, ctx->noise, ctx->D, ctx->cloud, ctx->gcloud, N,
                                ctx->S_max, ctx->Acl, ctx->L, ctx->dev_scratch);
+    if (cfg.cp_model == 0)
+        launch_rank_tables(ctx->stream, ctx->D, ctx->cloud, ctx->rank, ctx->prefix,
+                           ctx->dev_ints + 7, N, ctx->S_max + 1);
     tend(ctx);
-    HIPCHK(hipMemsetAsync(ctx->dev_ints, 0, 8 * sizeof(int32_t), ctx->stream));
     launch_mark_valid(ctx->stream, ctx->X, ctx->n_nodes, ctx->obs, ctx->n_obs, gb, ctx->valid, ctx->goal,
-                      ctx->dev_ints + 1);
+                      ctx->dev_ints + 1, ctx->bins);
     HIPCHK(hipMemsetAsync(ctx->deg, 0, (size_t)(ctx->n_nodes + 1) * sizeof(int32_t), ctx->stream));
     // pass-1 work lists: the near list in the edge arrays (free until pass 2),
     // the exact queue in two Explore candidate arrays (free until Explore)
@@ -705,9 +724,11 @@ int pump_explore_round(pump_ctx* ctx, int32_t* done) {
     RoundArgs a = round_args(ctx);
     const long long slots = ctx->cfg.cap_pairs;
     if ((long long)n_pairs <= slots) {
-        tbeg(ctx, 3);
-        launch_expand(ctx->stream, a, ctx->N, n_pairs, 1);
-        tend(ctx);
+        if (ctx->cfg.cp_model == 1) {
+            tbeg(ctx, 3);
+            launch_expand(ctx->stream, a, ctx->N, n_pairs, 1);
+            tend(ctx);
+        }
         tbeg(ctx, 18);
         launch_expand(ctx->stream, a, ctx->N, n_pairs, 2);
         tend(ctx);
@@ -734,9 +755,11 @@ int pump_explore_round(pump_ctx* ctx, int32_t* done) {
                 const int32_t n = (int32_t)std::min<long long>(slots, (long long)n_pairs - q0);
                 a.q0 = (int32_t)q0;
                 launch_chunk_begin(ctx->stream, a, n);
-                tbeg(ctx, 3);
-                launch_expand(ctx->stream, a, ctx->N, n, 1);
-                tend(ctx);
+                if (ctx->cfg.cp_model == 1) {
+                    tbeg(ctx, 3);
+                    launch_expand(ctx->stream, a, ctx->N, n, 1);
+                    tend(ctx);
+                }
                 tbeg(ctx, 18);
                 launch_expand(ctx->stream, a, ctx->N, n, 2);
                 tend(ctx);
@@ -810,7 +833,8 @@ static int explore_single_enqueue(pump_ctx* ctx) {
     ctx->ra_h[1].open_out = ctx->open_cur;
     HIPCHK(hipMemcpyAsync(ctx->ra_dev, ctx->ra_h, 2 * sizeof(RoundArgs), hipMemcpyHostToDevice,
                           ctx->stream));
-    HIPCHK(launch_explore_coop(ctx->stream, ctx->ra_dev, ca, ctx->N, ctx->coop_blocks));
+    HIPCHK(launch_explore_coop(ctx->stream, ctx->ra_dev, ca, ctx->N, ctx->cfg.cp_model, ctx->n_obs,
+                               ctx->coop_blocks));
     tend(ctx);
     return PUMP_OK;
 }

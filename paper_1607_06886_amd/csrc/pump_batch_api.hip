@@ -7,13 +7,16 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <string>
 #include <type_traits>
 #include <vector>
 
+#include "box_bins.hpp"
 #include "host_consts.hpp"
 #include "pump_internal.hpp"
+#include "rank_tables.hpp"
 
 using namespace pump;
 
@@ -23,7 +26,8 @@ constexpr int kBatchFrontHost = kMaxFront;
 
 struct Slot {
     // per-query buffers (sized for the batch's maxima)
-    float *X, *obs, *D, *cloud, *gcloud;
+    float *X, *obs, *D, *cloud, *gcloud, *rank;
+    uint32_t *prefix, *bins;
     uint8_t *valid, *goal, *p_state, *o_inB, *c_flag;
     uint32_t *ebits, *p_mask, *c_mask;
     int32_t *wstart, *deg, *row_ptr, *col, *esrc, *p_head, *p_parent, *p_edge, *p_step, *p_pop, *p_round;
@@ -138,6 +142,10 @@ int pump_batch_create(const pump_config* cfg_in, int32_t max_queries, void* hip_
     Slot lay{};
     take(&lay.X, nn * 6); take(&lay.obs, (size_t)kMaxObs * 6); take(&lay.D, (S + 1) * 3 * N);
     take(&lay.cloud, (S + 1) * 6);
+    // (a query's N may be any up to the configuration's)
+    take(&lay.rank, cfg.cp_model == 0 ? (size_t)(S + 1) * 3 * rank_row(N) : 1);
+    take(&lay.prefix, cfg.cp_model == 0 ? prefix_words((int)S + 1, N) : 1);
+    take(&lay.bins, (size_t)bin_words(kMaxObs));
     take(&lay.dev_scratch, (size_t)kDevScratchPer * ((S + 15) / 16) * 3 * N); take(&lay.gcloud, 8); take(&lay.valid, nn); take(&lay.goal, nn);
     take(&lay.ebits, nn * b->words); take(&lay.wstart, nn * b->words); take(&lay.deg, nn + 1); take(&lay.row_ptr, nn + 2);
     take(&lay.col, E); take(&lay.esrc, E); take(&lay.etau, E); take(&lay.ecost, E);
@@ -206,7 +214,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         t.blocks_per_cu < 1 || t.blocks_per_cu > 8 || t.team_scale < 0 || t.team_scale > 256)
         return bfail(b, PUMP_E_ARG, "bad tuning");
     b->qs.assign(q, BatchQuery());
-    int N_max = 0, max_nodes = 0;
+    int N_max = 0, max_nodes = 0, max_obs = 0;
     std::vector<double> work(q);
     for (int i = 0; i < q; ++i) {
         const pump_problem& pr = probs[i];
@@ -268,7 +276,10 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         Q.ecost = s.ecost; Q.b_deg = s.b_deg; Q.open_a = s.open_a; Q.open_b = s.open_b;
         RoundArgs& a = Q.ra[0];
         a.X = s.X; a.goal = s.goal; a.obs = s.obs; a.n_obs = pr.n_obs; a.D = s.D; a.cloud = s.cloud;
-        a.gcloud = s.gcloud; a.S_max = cfg.max_steps; a.dt = (double)cfg.dt;
+        a.gcloud = s.gcloud; a.rank = s.rank; a.prefix = s.prefix; a.bins = s.bins;
+        a.rank_nan = reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(b->qs_dev + i) +
+                                                      offsetof(BatchQuery, rank_nan));
+        a.S_max = cfg.max_steps; a.dt = (double)cfg.dt;
         cp_thresholds(alpha, eta, N, &a.c_cut, &a.c_min);
         a.h = (double)cfg.lambda * (double)cfg.r_conn;
         a.preprune = cfg.preprune;
@@ -298,6 +309,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         sa.ctl = s.ctl;
         N_max = std::max(N_max, N);
         max_nodes = std::max(max_nodes, Q.n_nodes);
+        max_obs = std::max(max_obs, pr.n_obs);
         work[i] = (double)Q.n_nodes * Q.n_nodes * sqrt((double)N);
     }
     // Schedules of the persistent Explore kernels, one per particle count:
@@ -318,7 +330,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
             if (b->qs[i].N == Ns[gi]) mem.push_back(i);
         if (mem.empty()) continue;
         int per_cu = t.blocks_per_cu;
-        const int fit = batch_explore_per_cu(Ns[gi], t.explore_threads);
+        const int fit = batch_explore_per_cu(Ns[gi], t.explore_threads, cfg.cp_model, max_obs);
         if (fit > 0 && per_cu > fit) per_cu = fit;
         const int grid = std::max(1, b->n_cu * per_cu);
         if (t.order == 1)
@@ -360,7 +372,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         BCHK(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
         launch_batch(b->stream, b->qs_dev, q, N_max, max_nodes, cfg.max_steps, cfg.mc_particles,
                      b->words, t.explore_threads, b->counter, b->out_dev, groups, n_groups,
-                     cfg.smooth != 0);
+                     cfg.smooth != 0, cfg.cp_model, max_obs);
         BCHK(hipStreamEndCapture(b->stream, &graph));
         BCHK(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
         BCHK(hipGraphLaunch(exec, b->stream));
@@ -370,7 +382,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
     } else {
         launch_batch(b->stream, b->qs_dev, q, N_max, max_nodes, cfg.max_steps, cfg.mc_particles,
                      b->words, t.explore_threads, b->counter, b->out_dev, groups, n_groups,
-                     cfg.smooth != 0);
+                     cfg.smooth != 0, cfg.cp_model, max_obs);
     }
     BCHK(hipGetLastError());
     BCHK(hipMemcpyAsync(b->outs.data(), b->out_dev, sizeof(BatchOut) * q, hipMemcpyDeviceToHost, b->stream));

@@ -129,6 +129,10 @@ struct RoundArgs {
     const float* D;            // [S_max+1][3][N]
     const float* cloud;        // [S_max+1][6] (lo xyz, hi xyz) of D over particles
     const float* gcloud;       // [6] union of cloud over all steps
+    const float* rank;         // rank rows of D's columns (rank_tables.hpp; box model only)
+    const uint32_t* prefix;    // their prefix sets
+    const int32_t* rank_nan;   // 1: D holds a NaN
+    const uint32_t* bins;      // box bins (box_bins.hpp)
     int32_t S_max;
     double dt;
     int32_t c_cut, c_min;
@@ -206,6 +210,10 @@ void launch_deviation_table(hipStream_t s, const float* noise, float* D, float* 
 void launch_deviation_table_lqg(hipStream_t s, const float* noise, const float* noise_meas,
                                 float* D, float* cloud, float* gcloud, int N, int S_max,
                                 const LqgCoef& q, double* scratch);
+// Rank rows and prefix sets of the finished table (rank_tables.hpp);
+// *has_nan zero before.
+void launch_rank_tables(hipStream_t s, const float* D, const float* cloud, float* rank,
+                        uint32_t* prefix, int32_t* has_nan, int N, int S1);
 // The obstacle-independent part of BuildGraph over a fixed sample set
 // (roadmap_ops.hpp): every Near connection between samples with its tau*,
 // c* and nominal position range.  Node numbering as in a query (samples are
@@ -247,9 +255,10 @@ void launch_graph_cols(hipStream_t s, int n_nodes, const uint32_t* ebits, const 
 // into out [n][6] (kernels_sample.hip).
 hipError_t launch_halton(hipStream_t s, int64_t start, int32_t n, const float* lo, const float* hi,
                          float* out);
+// Node validity and goal membership, and the box bins (bins may be null).
 void launch_mark_valid(hipStream_t s, const float* X, int n_nodes, const float* obs,
                        int n_obs, const float* goal_box, uint8_t* valid, uint8_t* goal,
-                       int32_t* bad);
+                       int32_t* bad, uint32_t* bins);
 // BuildGraph pass 1 from scratch: the edge bit matrix (cleared here) and the
 // row degrees.  gw.counts must be zero.
 void launch_graph_mark(hipStream_t s, const float* X, const uint8_t* valid, int n_nodes,
@@ -274,8 +283,9 @@ void scan_exclusive(hipStream_t s, const int32_t* in, int32_t* out, const int32_
 // launch's barrier words).
 void launch_explore_init(hipStream_t s, const RoundArgs& a, int n_nodes, int N, unsigned* zero,
                          int n_zero);
-// part: 1 the pair stage, 2 the particle stage, 3 both
-void launch_expand(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, int part = 3);
+// Half-space model: part 1 the pair stage, 2 the particle stage.  Box model:
+// one kernel, in part 2.
+void launch_expand(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, int part);
 void launch_prune(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, int32_t n_open);
 void launch_compact(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs,
                     int32_t n_open, int32_t* blk_scratch);
@@ -383,8 +393,8 @@ struct CoopArgs {
 // ra_dev: two round-argument blocks in device memory, open lists
 // (open_cur -> open_next) and (open_next -> open_cur).
 hipError_t launch_explore_coop(hipStream_t s, const RoundArgs* ra_dev, const CoopArgs& ca, int N,
-                               int blocks);
-int coop_max_blocks(int N);
+                               int cp_model, int n_obs, int blocks);
+int coop_max_blocks(int N, int cp_model, int max_obs);
 
 // One query of the batched engine: its round and selection state plus the
 // graph-build buffers and inputs, all in device memory.
@@ -406,6 +416,7 @@ struct BatchQuery {
     int32_t cap_pairs, cap_edges;
     int32_t bad;               // input / capacity errors (bit flags)
     int32_t gcount[4];         // graph-build work-list counters (zero on upload)
+    int32_t rank_nan;          // the deviation table holds a NaN (zero on upload)
     int32_t use_rm;            // 1: the graph comes from `rm` (cached roadmap)
     RoadmapDev rm;
     float* X;
@@ -461,9 +472,9 @@ struct BatchGroup {
 };
 void launch_batch(hipStream_t s, BatchQuery* qs_dev, int q, int N_max, int max_nodes, int S_max,
                   int M, int words, int explore_threads, int* counters, BatchOut* out,
-                  const BatchGroup* groups, int n_groups, bool smooth);
+                  const BatchGroup* groups, int n_groups, bool smooth, int cp_model, int max_obs);
 // Workgroups of the batched Explore kernel for N that fit on one CU at once.
-int batch_explore_per_cu(int N, int threads);
+int batch_explore_per_cu(int N, int threads, int cp_model, int max_obs);
 
 // P_goal and its front; scratch: an int per plan (free after Explore), blk:
 // the scan's block scratch.

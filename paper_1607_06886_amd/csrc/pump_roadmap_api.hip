@@ -94,7 +94,7 @@ int pump_roadmap_create(const pump_config* cfg, const float* samples, int32_t n,
     A(hipMemcpyAsync(t.ints, ints_h, sizeof(ints_h), hipMemcpyHostToDevice, s));
     // every sample valid (no obstacles; bit 1 of ints[1] flags a bad sample),
     // the placeholder node 0 excluded
-    launch_mark_valid(s, rm->X, nn, nullptr, 0, zeros, t.valid, t.goal, t.ints + 1);
+    launch_mark_valid(s, rm->X, nn, nullptr, 0, zeros, t.valid, t.goal, t.ints + 1, nullptr);
     A(hipMemsetAsync(t.valid, 0, 1, s));
     A(hipMemsetAsync(t.deg, 0, ((size_t)nn + 1) * sizeof(int32_t), s));
     const GraphWork gw{t.w_ns, t.w_nd, t.w_nt, t.w_xe, t.w_xb, t.ints + 4, (int32_t)ncap, 1};
