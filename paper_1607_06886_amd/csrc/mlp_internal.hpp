@@ -17,32 +17,41 @@ constexpr int kOutPad = 224;
 constexpr int kLayers = 5;              // 4 hidden + output
 constexpr float kLogStdMin = -4.0f, kLogStdMax = 2.0f;
 
-enum { kEpiHidden = 0, kEpiOutput = 1, kEpiWgrad = 2, kEpiDgrad = 3 };
+constexpr int kBiasTotal = 4 * kHidden + kOut;   // bias entries of all layers
 
-struct EpiArgs {
-    const float* bias;      // [n_real]
-    int n_real;             // columns with a bias / kept
-    int m_real;             // rows kept (wgrad)
-    uint16_t* out_bf;       // hidden: BF16 activations [M][ld_out]
-    uint16_t* out_bfT;      // hidden: transpose [N][ld_outT]
-    int ld_out, ld_outT;
-    float* out_f32;         // output / wgrad / dgrad destination
-    const uint16_t* mask_bf;  // dgrad: layer input activations (ReLU mask)
-    int ld_mask;
+// Shapes of layer l: real and padded (multiples of 32).
+__host__ __device__ constexpr int mlp_in(int l) { return l == 0 ? kIn : kHidden; }
+__host__ __device__ constexpr int mlp_in_p(int l) { return l == 0 ? kInPad : kHidden; }
+__host__ __device__ constexpr int mlp_out(int l) { return l == kLayers - 1 ? kOut : kHidden; }
+__host__ __device__ constexpr int mlp_out_p(int l) { return l == kLayers - 1 ? kOutPad : kHidden; }
+
+// Network state and buffers the kernels read and write.
+struct MlpDev {
+    int off_W[kLayers], off_b[kLayers];    // into params and grads
+    float *params, *m1, *m2, *grads;       // [n_params]
+    uint16_t *Wb[kLayers], *WbT[kLayers];  // BF16 weights [out_p][in_p] and [in_p][out_p], in fragment order
+    // a training step, batch rows contiguous (Bp of them)
+    uint16_t* HT[kLayers];                 // layer inputs [in_p][Bp], in fragment order
+    uint16_t* GT[kLayers];                 // output gradients [out_p][Bp], likewise
+    float* bpart;                          // bias gradients [Bp / 16][kBiasTotal]
+    float* lpart;                          // losses [Bp / 16]
+    int n_params;
 };
 
-void launch_gemm_nt(hipStream_t s, int epi, const uint16_t* A, int lda, const uint16_t* B,
-                    int ldb, int M, int N, int K, const EpiArgs& ep);
-void launch_input_bf16(hipStream_t s, const float* X, int B, int Bp, int d_in, int d_pad,
-                       uint16_t* H, uint16_t* HT);
-void launch_mixture_nll(hipStream_t s, const float* Y, int ldy, const float* Z, int B, int Bp,
-                        float* G, int ldg, float* partial, float* loss);
-void launch_grad_prep(hipStream_t s, const float* G, int ldg, int Bp, int width, int n_real,
-                      uint16_t* GB, uint16_t* GBT, float* bias_grad);
-void launch_adam(hipStream_t s, float* p, float* m1, float* m2, const float* g, int n, float lr,
-                 int t);
-void launch_refresh_bf16(hipStream_t s, const float* W, int out, int in, int out_p, int in_p,
-                         uint16_t* Wb, uint16_t* WbT);
+// out[m * ld + n] (n < n_out, m < rows) = the network's outputs for the
+// condition rows X [B][kIn].
+void launch_mlp_forward(hipStream_t s, const MlpDev& d, const float* X, int B, float* out, int ld,
+                        int n_out, int rows);
+// Loss and gradients of a batch, in two launches: the rows through the network
+// and back (layer inputs, output gradients, bias and loss partials), then the
+// gradients (into grads) and the mean loss (*loss, memory the device can
+// write).
+void launch_mlp_grad(hipStream_t s, const MlpDev& d, const float* X, const float* Z, int B, int Bp,
+                     float* loss);
+// One Adam step (t counts from 1) on grads, and the BF16 weights it changes.
+void launch_adam(hipStream_t s, const MlpDev& d, float lr, int t);
+// BF16 weights from the parameters, padding zeroed.
+void launch_refresh_bf16(hipStream_t s, const MlpDev& d);
 void launch_condition(hipStream_t s, const float* x_init, const float* goal, const float* boxes,
                       const int32_t* n_obs, int q, int max_boxes_in, float* cond);
 void launch_sample(hipStream_t s, const float* Y, int ldy, int q, int n, const float* u,

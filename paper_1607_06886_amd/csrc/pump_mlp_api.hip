@@ -11,13 +11,6 @@
 
 using namespace pump;
 
-namespace {
-const int kInReal[kLayers] = {kIn, kHidden, kHidden, kHidden, kHidden};
-const int kInP[kLayers] = {kInPad, kHidden, kHidden, kHidden, kHidden};
-const int kOutReal[kLayers] = {kHidden, kHidden, kHidden, kHidden, kOut};
-const int kOutP[kLayers] = {kHidden, kHidden, kHidden, kHidden, kOutPad};
-}  // namespace
-
 // Staging for pump_mlp_sample_noalloc (draws in host memory): the uniforms,
 // the normals and the drawn states pass through this array instead of
 // buffers allocated per call.  One copy per GPU, held until the process
@@ -33,15 +26,10 @@ struct pump_mlp {
     float* staging = nullptr;       // that device's address of `scratch`
     bool own_stream = false;
     int max_batch = 0, maxBp = 0;
-    int n_params = 0;
-    int off_W[kLayers] = {0}, off_b[kLayers] = {0};
-    float *params = nullptr, *m1 = nullptr, *m2 = nullptr, *grads = nullptr;
-    uint16_t *Wb[kLayers] = {nullptr}, *WbT[kLayers] = {nullptr};
-    uint16_t *H[kLayers] = {nullptr}, *HT[kLayers] = {nullptr};
-    float *Y = nullptr, *G = nullptr, *G2 = nullptr;
-    uint16_t *GB = nullptr, *GBT = nullptr;
-    float *partial = nullptr, *loss = nullptr;
-    float *xbuf = nullptr, *zbuf = nullptr, *ubuf = nullptr, *ebuf = nullptr, *obuf = nullptr;
+    MlpDev d{};
+    float* Y = nullptr;             // outputs [maxBp][kOutPad]
+    float* loss_h = nullptr;        // pinned; the kernels write the mean loss here
+    float *xbuf = nullptr, *zbuf = nullptr;
     int t = 0;
     std::string err;
 };
@@ -62,64 +50,9 @@ int mfail(pump_mlp* m, int code, const std::string& msg) {
 
 int round32(int b) { return (b + 31) / 32 * 32; }
 
-void refresh_all(pump_mlp* m) {
-    for (int l = 0; l < kLayers; ++l)
-        launch_refresh_bf16(m->stream, m->params + m->off_W[l], kOutReal[l], kInReal[l], kOutP[l],
-                            kInP[l], m->Wb[l], m->WbT[l]);
-}
-
-// Y = MLP(cond rows in m->xbuf or `X`), rows padded to Bp.
-void forward(pump_mlp* m, const float* X, int B, int Bp) {
-    launch_input_bf16(m->stream, X, B, Bp, kIn, kInPad, m->H[0], m->HT[0]);
-    for (int l = 0; l < kLayers; ++l) {
-        EpiArgs ep;
-        memset(&ep, 0, sizeof(ep));
-        ep.bias = m->params + m->off_b[l];
-        ep.n_real = kOutReal[l];
-        if (l < kLayers - 1) {
-            ep.out_bf = m->H[l + 1];
-            ep.ld_out = kOutP[l];
-            ep.out_bfT = m->HT[l + 1];
-            ep.ld_outT = Bp;
-            launch_gemm_nt(m->stream, kEpiHidden, m->H[l], kInP[l], m->Wb[l], kInP[l], Bp, kOutP[l],
-                           kInP[l], ep);
-        } else {
-            ep.out_f32 = m->Y;
-            ep.ld_out = kOutPad;
-            launch_gemm_nt(m->stream, kEpiOutput, m->H[l], kInP[l], m->Wb[l], kInP[l], Bp, kOutP[l],
-                           kInP[l], ep);
-        }
-    }
-}
-
-// Gradients of the mean NLL into m->grads (and the loss into m->loss).
-void backward(pump_mlp* m, const float* Z, int B, int Bp) {
-    launch_mixture_nll(m->stream, m->Y, kOutPad, Z, B, Bp, m->G, kOutPad, m->partial, m->loss);
-    float* G = m->G;
-    float* G2 = m->G2;
-    for (int l = kLayers - 1; l >= 0; --l) {
-        const int width = kOutP[l];
-        launch_grad_prep(m->stream, G, width, Bp, width, kOutReal[l], m->GB, m->GBT,
-                         m->grads + m->off_b[l]);
-        EpiArgs ep;
-        memset(&ep, 0, sizeof(ep));
-        ep.m_real = kOutReal[l];
-        ep.n_real = kInReal[l];
-        ep.out_f32 = m->grads + m->off_W[l];
-        ep.ld_out = kInReal[l];
-        launch_gemm_nt(m->stream, kEpiWgrad, m->GBT, Bp, m->HT[l], Bp, kOutP[l], kInP[l], Bp, ep);
-        if (l > 0) {
-            EpiArgs ed;
-            memset(&ed, 0, sizeof(ed));
-            ed.out_f32 = G2;
-            ed.ld_out = kInP[l];
-            ed.mask_bf = m->H[l];
-            ed.ld_mask = kInP[l];
-            launch_gemm_nt(m->stream, kEpiDgrad, m->GB, width, m->WbT[l], kOutP[l], Bp, kInP[l],
-                           kOutP[l], ed);
-            std::swap(G, G2);
-        }
-    }
+// Y = MLP(cond rows X).
+void forward(pump_mlp* m, const float* X, int B) {
+    launch_mlp_forward(m->stream, m->d, X, B, m->Y, kOutPad, kOutPad, B);
 }
 
 // Device address of `scratch` on the current device, looked up on the first
@@ -174,40 +107,35 @@ int pump_mlp_create(int32_t max_batch, void* hip_stream, pump_mlp** out) {
         delete m;
         return PUMP_E_HIP;
     }
+    MlpDev& d = m->d;
     int off = 0;
     for (int l = 0; l < kLayers; ++l) {
-        m->off_W[l] = off;
-        off += kOutReal[l] * kInReal[l];
-        m->off_b[l] = off;
-        off += kOutReal[l];
+        d.off_W[l] = off;
+        off += mlp_out(l) * mlp_in(l);
+        d.off_b[l] = off;
+        off += mlp_out(l);
     }
-    m->n_params = off;
+    d.n_params = off;
     const size_t Bp = (size_t)m->maxBp;
     bool ok = true;
     auto A = [&](hipError_t e) { ok = ok && e == hipSuccess; };
-    auto alloc = [&](void** p, size_t bytes) { A(hipMalloc(p, bytes ? bytes : 16)); };
-    alloc((void**)&m->params, (size_t)off * 4);
-    alloc((void**)&m->m1, (size_t)off * 4);
-    alloc((void**)&m->m2, (size_t)off * 4);
-    alloc((void**)&m->grads, (size_t)off * 4);
+    auto alloc = [&](auto** p, size_t n) { A(hipMalloc((void**)p, n * sizeof(**p))); };
+    alloc(&d.params, (size_t)off);
+    alloc(&d.m1, (size_t)off);
+    alloc(&d.m2, (size_t)off);
+    alloc(&d.grads, (size_t)off);
     for (int l = 0; l < kLayers; ++l) {
-        alloc((void**)&m->Wb[l], (size_t)kOutP[l] * kInP[l] * 2);
-        alloc((void**)&m->WbT[l], (size_t)kOutP[l] * kInP[l] * 2);
-        alloc((void**)&m->H[l], Bp * kInP[l] * 2);
-        alloc((void**)&m->HT[l], Bp * kInP[l] * 2);
+        alloc(&d.Wb[l], (size_t)mlp_out_p(l) * mlp_in_p(l));
+        alloc(&d.WbT[l], (size_t)mlp_out_p(l) * mlp_in_p(l));
+        alloc(&d.HT[l], Bp * mlp_in_p(l));
+        alloc(&d.GT[l], Bp * mlp_out_p(l));
     }
-    alloc((void**)&m->Y, Bp * kOutPad * 4);
-    alloc((void**)&m->G, Bp * kInPad * 4);
-    alloc((void**)&m->G2, Bp * kInPad * 4);
-    alloc((void**)&m->GB, Bp * kHidden * 2);
-    alloc((void**)&m->GBT, Bp * kHidden * 2);
-    alloc((void**)&m->partial, (Bp / 256 + 2) * 4);
-    alloc((void**)&m->loss, 16);
-    alloc((void**)&m->xbuf, Bp * kIn * 4);
-    alloc((void**)&m->zbuf, Bp * kDState * 4);
-    alloc((void**)&m->ubuf, Bp * 4);
-    alloc((void**)&m->ebuf, Bp * kDState * 4);
-    alloc((void**)&m->obuf, Bp * kDState * 4);
+    alloc(&d.bpart, (Bp / 16) * kBiasTotal);
+    alloc(&d.lpart, Bp / 16);
+    alloc(&m->Y, Bp * kOutPad);
+    alloc(&m->xbuf, Bp * kIn);
+    alloc(&m->zbuf, Bp * kDState);
+    A(hipHostMalloc((void**)&m->loss_h, 16, hipHostMallocDefault));
     if (!ok) {
         pump_mlp_destroy(m);
         return PUMP_E_HIP;
@@ -219,15 +147,16 @@ int pump_mlp_create(int32_t max_batch, void* hip_stream, pump_mlp** out) {
 int pump_mlp_destroy(pump_mlp* m) {
     if (!m) return PUMP_OK;
     if (m->stream) (void)hipStreamSynchronize(m->stream);
-    void* ptrs[] = {m->params, m->m1, m->m2, m->grads, m->Y, m->G, m->G2, m->GB, m->GBT,
-                    m->partial, m->loss, m->xbuf, m->zbuf, m->ubuf, m->ebuf, m->obuf};
+    const MlpDev& d = m->d;
+    void* ptrs[] = {d.params, d.m1, d.m2, d.grads, d.bpart, d.lpart, m->Y, m->xbuf, m->zbuf};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     for (int l = 0; l < kLayers; ++l) {
-        void* q[] = {m->Wb[l], m->WbT[l], m->H[l], m->HT[l]};
+        void* q[] = {d.Wb[l], d.WbT[l], d.HT[l], d.GT[l]};
         for (void* p : q)
             if (p) (void)hipFree(p);
     }
+    if (m->loss_h) (void)hipHostFree(m->loss_h);
     if (m->own_stream && m->stream) (void)hipStreamDestroy(m->stream);
     delete m;
     return PUMP_OK;
@@ -235,17 +164,17 @@ int pump_mlp_destroy(pump_mlp* m) {
 
 int pump_mlp_num_params(void) {
     int n = 0;
-    for (int l = 0; l < kLayers; ++l) n += kOutReal[l] * kInReal[l] + kOutReal[l];
+    for (int l = 0; l < kLayers; ++l) n += mlp_out(l) * mlp_in(l) + mlp_out(l);
     return n;
 }
 
 int pump_mlp_set_params(pump_mlp* m, const float* params, int64_t n) {
     if (!m || !params) return PUMP_E_ARG;
-    if (n != m->n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
-    MCHK(hipMemcpyAsync(m->params, params, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
-    MCHK(hipMemsetAsync(m->m1, 0, (size_t)n * 4, m->stream));
-    MCHK(hipMemsetAsync(m->m2, 0, (size_t)n * 4, m->stream));
-    refresh_all(m);
+    if (n != m->d.n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
+    MCHK(hipMemcpyAsync(m->d.params, params, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
+    MCHK(hipMemsetAsync(m->d.m1, 0, (size_t)n * 4, m->stream));
+    MCHK(hipMemsetAsync(m->d.m2, 0, (size_t)n * 4, m->stream));
+    launch_refresh_bf16(m->stream, m->d);
     m->t = 0;
     MCHK(hipStreamSynchronize(m->stream));
     return PUMP_OK;
@@ -253,18 +182,18 @@ int pump_mlp_set_params(pump_mlp* m, const float* params, int64_t n) {
 
 int pump_mlp_get_params(pump_mlp* m, float* params, int64_t n) {
     if (!m || !params) return PUMP_E_ARG;
-    if (n != m->n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
-    MCHK(hipMemcpyAsync(params, m->params, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
+    if (n != m->d.n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
+    MCHK(hipMemcpyAsync(params, m->d.params, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
     MCHK(hipStreamSynchronize(m->stream));
     return PUMP_OK;
 }
 
 int pump_mlp_get_state(pump_mlp* m, float* params, float* m1, float* m2, int64_t n, int32_t* t) {
     if (!m || !params || !m1 || !m2 || !t) return PUMP_E_ARG;
-    if (n != m->n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
-    MCHK(hipMemcpyAsync(params, m->params, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
-    MCHK(hipMemcpyAsync(m1, m->m1, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
-    MCHK(hipMemcpyAsync(m2, m->m2, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
+    if (n != m->d.n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
+    MCHK(hipMemcpyAsync(params, m->d.params, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
+    MCHK(hipMemcpyAsync(m1, m->d.m1, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
+    MCHK(hipMemcpyAsync(m2, m->d.m2, (size_t)n * 4, hipMemcpyDeviceToHost, m->stream));
     MCHK(hipStreamSynchronize(m->stream));
     *t = m->t;
     return PUMP_OK;
@@ -273,12 +202,12 @@ int pump_mlp_get_state(pump_mlp* m, float* params, float* m1, float* m2, int64_t
 int pump_mlp_set_state(pump_mlp* m, const float* params, const float* m1, const float* m2,
                        int64_t n, int32_t t) {
     if (!m || !params || !m1 || !m2) return PUMP_E_ARG;
-    if (n != m->n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
+    if (n != m->d.n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
     if (t < 0) return mfail(m, PUMP_E_ARG, "negative step count");
-    MCHK(hipMemcpyAsync(m->params, params, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
-    MCHK(hipMemcpyAsync(m->m1, m1, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
-    MCHK(hipMemcpyAsync(m->m2, m2, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
-    refresh_all(m);
+    MCHK(hipMemcpyAsync(m->d.params, params, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
+    MCHK(hipMemcpyAsync(m->d.m1, m1, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
+    MCHK(hipMemcpyAsync(m->d.m2, m2, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
+    launch_refresh_bf16(m->stream, m->d);
     m->t = t;
     MCHK(hipStreamSynchronize(m->stream));
     return PUMP_OK;
@@ -286,16 +215,15 @@ int pump_mlp_set_state(pump_mlp* m, const float* params, const float* m1, const 
 
 int pump_mlp_adam_step(pump_mlp* m, const float* grads, int64_t n, float lr, int32_t mem) {
     if (!m || !grads) return PUMP_E_ARG;
-    if (n != m->n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
+    if (n != m->d.n_params) return mfail(m, PUMP_E_ARG, "parameter count mismatch");
     if (!(lr > 0.0f)) return mfail(m, PUMP_E_ARG, "learning rate must be positive");
     if (mem == PUMP_MEM_DEVICE) {
-        MCHK(hipMemcpyAsync(m->grads, grads, (size_t)n * 4, hipMemcpyDeviceToDevice, m->stream));
+        MCHK(hipMemcpyAsync(m->d.grads, grads, (size_t)n * 4, hipMemcpyDeviceToDevice, m->stream));
     } else {
-        MCHK(hipMemcpyAsync(m->grads, grads, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
+        MCHK(hipMemcpyAsync(m->d.grads, grads, (size_t)n * 4, hipMemcpyHostToDevice, m->stream));
     }
     m->t += 1;
-    launch_adam(m->stream, m->params, m->m1, m->m2, m->grads, m->n_params, lr, m->t);
-    refresh_all(m);
+    launch_adam(m->stream, m->d, lr, m->t);
     MCHK(hipStreamSynchronize(m->stream));
     MCHK(hipGetLastError());
     return PUMP_OK;
@@ -307,10 +235,12 @@ int pump_mlp_forward(pump_mlp* m, const float* cond, int32_t B, float* out, int3
     hipError_t e;
     const float* X = stage(m, cond, m->xbuf, (size_t)B * kIn, mem, &e);
     MCHK(e);
-    forward(m, X, B, round32(B));
-    MCHK(hipMemcpy2DAsync(out, kOut * 4, m->Y, kOutPad * 4, kOut * 4, B,
-                          mem == PUMP_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
-                          m->stream));
+    // (device rows are written where the caller wants them; host rows go
+    // through a packed copy)
+    float* dst = mem == PUMP_MEM_DEVICE ? out : m->Y;
+    launch_mlp_forward(m->stream, m->d, X, B, dst, kOut, kOut, B);
+    if (mem != PUMP_MEM_DEVICE)
+        MCHK(hipMemcpyAsync(out, m->Y, (size_t)B * kOut * 4, hipMemcpyDeviceToHost, m->stream));
     MCHK(hipStreamSynchronize(m->stream));
     MCHK(hipGetLastError());
     return PUMP_OK;
@@ -326,15 +256,14 @@ int pump_mlp_loss_grad(pump_mlp* m, const float* cond, const float* target, int3
     const float* Z = stage(m, target, m->zbuf, (size_t)B * kDState, mem, &e);
     MCHK(e);
     const int Bp = round32(B);
-    forward(m, X, B, Bp);
-    backward(m, Z, B, Bp);
-    if (loss) MCHK(hipMemcpyAsync(loss, m->loss, 4, hipMemcpyDeviceToHost, m->stream));
+    launch_mlp_grad(m->stream, m->d, X, Z, B, Bp, m->loss_h);
     if (grads)
-        MCHK(hipMemcpyAsync(grads, m->grads, (size_t)m->n_params * 4,
+        MCHK(hipMemcpyAsync(grads, m->d.grads, (size_t)m->d.n_params * 4,
                             mem == PUMP_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
                             m->stream));
     MCHK(hipStreamSynchronize(m->stream));
     MCHK(hipGetLastError());
+    if (loss) *loss = *m->loss_h;
     return PUMP_OK;
 }
 
@@ -349,14 +278,12 @@ int pump_mlp_train_step(pump_mlp* m, const float* cond, const float* target, int
     const float* Z = stage(m, target, m->zbuf, (size_t)B * kDState, mem, &e);
     MCHK(e);
     const int Bp = round32(B);
-    forward(m, X, B, Bp);
-    backward(m, Z, B, Bp);
+    launch_mlp_grad(m->stream, m->d, X, Z, B, Bp, m->loss_h);
     m->t += 1;
-    launch_adam(m->stream, m->params, m->m1, m->m2, m->grads, m->n_params, lr, m->t);
-    refresh_all(m);
+    launch_adam(m->stream, m->d, lr, m->t);
     if (loss) {
-        MCHK(hipMemcpyAsync(loss, m->loss, 4, hipMemcpyDeviceToHost, m->stream));
         MCHK(hipStreamSynchronize(m->stream));
+        *loss = *m->loss_h;
     }
     MCHK(hipGetLastError());
     return PUMP_OK;
@@ -379,11 +306,10 @@ int pump_mlp_sample(pump_mlp* m, const float* cond, int32_t q, const float* u, c
     hipError_t e;
     const float* X = stage(m, cond, m->xbuf, (size_t)q * kIn, mem, &e);
     MCHK(e);
-    forward(m, X, q, round32(q));
+    forward(m, X, q);
     const float* U = u;
     const float* EPS = eps;
     float* O = out;
-    std::vector<float> dummy;
     float *du = nullptr, *de = nullptr, *dout = nullptr;
     if (mem != PUMP_MEM_DEVICE) {
         const size_t total = (size_t)q * n;
@@ -422,7 +348,7 @@ int pump_mlp_sample_noalloc(pump_mlp* m, const float* cond, int32_t q, const flo
     hipError_t e;
     const float* X = stage(m, cond, m->xbuf, (size_t)q * kIn, mem, &e);
     MCHK(e);
-    forward(m, X, q, round32(q));
+    forward(m, X, q);
     const float* U = u;
     const float* EPS = eps;
     float* O = out;
