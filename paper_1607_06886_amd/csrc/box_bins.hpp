@@ -13,8 +13,8 @@
 // the bit set.  The exact range test then runs over that superset only, so
 // the boxes found are exactly those of a test over every box.
 //
-// One workgroup builds the table in LDS from the boxes it already holds
-// there; a range that is not finite gets every box.
+// The table is built once per query in device memory, and the kernels that ask
+// it copy it to LDS.
 #pragma once
 
 #include "device_math.hpp"
@@ -24,100 +24,39 @@ namespace pump {
 
 constexpr int kBins = 64;
 
-struct BoxBins {
-    float org[3], scale[3];
-    int n;                                               // boxes
-    int nw;                                              // bit-set words in use
-    unsigned long long lo_le[3][kBins][kMaxObsWords];
-    unsigned long long hi_ge[3][kBins][kMaxObsWords];
-};
-
-__device__ __forceinline__ int box_bin(const BoxBins* s, int a, float x) {
-    const float f = (x - s->org[a]) * s->scale[a];
-    // fmaxf(NaN, 0) = 0; the clamp keeps the conversion in range
-    return (int)fminf(fmaxf(f, 0.0f), (float)(kBins - 1));
-}
-
-// All threads of the workgroup call it; boxes b[o * 6 + (lo xyz, hi xyz)].
-__device__ __forceinline__ void box_bins_build(const float* b, int n, BoxBins* s) {
-    if (threadIdx.x < 3) {
-        const int a = threadIdx.x;
-        float lo = INFINITY, hi = -INFINITY;
-        for (int o = 0; o < n; ++o) {
-            lo = fminf(lo, b[o * 6 + a]);
-            hi = fmaxf(hi, b[o * 6 + 3 + a]);
-        }
-        if (n > 0 && hi > lo) {
-            s->org[a] = lo;
-            s->scale[a] = (float)kBins / (hi - lo);
-        } else {
-            s->org[a] = 0.0f;   // every box in bin 0
-            s->scale[a] = 0.0f;
-        }
-    }
-    if (threadIdx.x == 0) {
-        s->n = n;
-        s->nw = (n + 63) / 64;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < 3 * kBins * kMaxObsWords; t += blockDim.x) {
-        const int a = t / (kBins * kMaxObsWords);
-        const int bn = (t / kMaxObsWords) % kBins;
-        const int w = t % kMaxObsWords;
-        unsigned long long le = 0ull, ge = 0ull;
-        for (int k = 0; k < 64 && w * 64 + k < n; ++k) {
-            const int o = w * 64 + k;
-            if (box_bin(s, a, b[o * 6 + a]) <= bn) le |= 1ull << k;
-            if (box_bin(s, a, b[o * 6 + 3 + a]) >= bn) ge |= 1ull << k;
-        }
-        s->lo_le[a][bn][w] = le;
-        s->hi_ge[a][bn][w] = ge;
-    }
-    __syncthreads();
-}
-
-// Candidate boxes of the range [lo3, hi3]: bits o < s->n of cand[0 .. kMaxObsWords).
-__device__ __forceinline__ void box_bins_query(const BoxBins* s, const float* lo3, const float* hi3,
-                                               unsigned long long* cand) {
-    const int n = s->n, nw = s->nw;
-    bool finite = true;
-    for (int a = 0; a < 3; ++a) finite &= isfinite(lo3[a]) && isfinite(hi3[a]);
-    for (int w = 0; w < kMaxObsWords; ++w) {
-        const int left = n - w * 64;   // boxes from this word on
-        cand[w] = left >= 64 ? ~0ull : (left > 0 ? (1ull << left) - 1ull : 0ull);
-    }
-    if (!finite) return;
-    for (int a = 0; a < 3; ++a) {
-        const int b0 = box_bin(s, a, lo3[a]), b1 = box_bin(s, a, hi3[a]);
-        for (int w = 0; w < nw; ++w) cand[w] &= s->lo_le[a][b1][w] & s->hi_ge[a][b0][w];
-    }
-}
-
-// The same table built once per query in device memory, in the layout the
-// Explore kernels copy to LDS: 8 header words (org xyz, scale xyz, boxes,
-// words per set), then the sets lo_le[3][kBins][nw] and hi_ge[3][kBins][nw].
+// Layout: 8 header words (org xyz, scale xyz, boxes, words per set), then the
+// sets lo_le[3][kBins][nw] and hi_ge[3][kBins][nw].
 constexpr int kBinHeader = 8;
 __host__ __device__ constexpr int bin_words(int n_obs) {
     return kBinHeader + 2 * 3 * kBins * ((n_obs + 63) / 64) * 2;
 }
 
-// One workgroup; boxes b[o * 6 + (lo xyz, hi xyz)], out: bin_words(n) words.
+// One workgroup (n at most kMaxObs); boxes b[o * 6 + (lo xyz, hi xyz)], out: bin_words(n) words.
 __device__ __forceinline__ void box_bins_write(const float* __restrict__ b, int n,
                                                uint32_t* __restrict__ out) {
-    __shared__ float s_org[3], s_scale[3];
+    __shared__ float s_org[3], s_scale[3], s_b[kMaxObs * 6];
     const int nw = (n + 63) / 64;
-    if (threadIdx.x < 3) {
-        const int a = threadIdx.x;
-        float lo = INFINITY, hi = -INFINITY;
-        for (int o = 0; o < n; ++o) {
-            lo = fminf(lo, b[o * 6 + a]);
-            hi = fmaxf(hi, b[o * 6 + 3 + a]);
+    for (int t = threadIdx.x; t < n * 6; t += blockDim.x) s_b[t] = b[t];
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        for (int a = 0; a < 3; ++a) {
+            float lo = INFINITY, hi = -INFINITY;
+            for (int o = threadIdx.x; o < n; o += 64) {
+                lo = fminf(lo, s_b[o * 6 + a]);
+                hi = fmaxf(hi, s_b[o * 6 + 3 + a]);
+            }
+            for (int k = 32; k > 0; k >>= 1) {
+                lo = fminf(lo, __shfl_xor(lo, k, 64));
+                hi = fmaxf(hi, __shfl_xor(hi, k, 64));
+            }
+            if (threadIdx.x == 0) {
+                const bool ok = n > 0 && hi > lo;
+                s_org[a] = ok ? lo : 0.0f;   // otherwise every box in bin 0
+                s_scale[a] = ok ? (float)kBins / (hi - lo) : 0.0f;
+                out[a] = __float_as_uint(s_org[a]);
+                out[3 + a] = __float_as_uint(s_scale[a]);
+            }
         }
-        const bool ok = n > 0 && hi > lo;
-        s_org[a] = ok ? lo : 0.0f;   // otherwise every box in bin 0
-        s_scale[a] = ok ? (float)kBins / (hi - lo) : 0.0f;
-        out[a] = __float_as_uint(s_org[a]);
-        out[3 + a] = __float_as_uint(s_scale[a]);
     }
     if (threadIdx.x == 0) {
         out[6] = (uint32_t)n;
@@ -131,7 +70,7 @@ __device__ __forceinline__ void box_bins_write(const float* __restrict__ b, int 
         const int w = u % nw, bn = (u / nw) % kBins, a = u / (nw * kBins);
         unsigned long long bits = 0ull;
         for (int k = 0; k < 64 && w * 64 + k < n; ++k) {
-            const float x = b[(w * 64 + k) * 6 + (ge ? 3 : 0) + a];
+            const float x = s_b[(w * 64 + k) * 6 + (ge ? 3 : 0) + a];
             const int bx = (int)fminf(fmaxf((x - s_org[a]) * s_scale[a], 0.0f), (float)(kBins - 1));
             if (ge ? bx >= bn : bx <= bn) bits |= 1ull << k;
         }

@@ -229,6 +229,7 @@ __device__ __forceinline__ bool surely_not_near32(const float* x0, const float* 
 struct Cubic {
     double c0, c1, c2, c3;
     __device__ double at(double t) const { return c0 + t * (c1 + t * (c2 + t * c3)); }
+    __device__ double slope(double t) const { return c1 + t * (2.0 * c2 + t * 3.0 * c3); }
 };
 
 // 1 / b from the hardware reciprocal and two Newton steps: within an ulp or
@@ -375,18 +376,15 @@ __device__ __forceinline__ void cubic_range(const Cubic& c, double tau, double& 
 // so it meets the box iff the three per-axis in-slab sets intersect
 // (trajectory_hits_box_exact).
 //
-// Two cheap tests settle most cases first (trajectory_box_quick).  The
-// trajectory is swept over 8 equal pieces: a sample point (interior piece
-// ends) inside the box proves a hit; and on each piece a cubic lies in the
-// hull of its Bernstein coefficients p(ta), p(ta) + h p'(ta)/3,
-// p(tb) - h p'(tb)/3, p(tb), so a piece whose hull (widened by kHullMargin,
-// far above the rounding of these values) misses the box on some axis
-// cannot meet it.  A piece whose hull does meet the box is split once more
-// into 4 (more sample points, tighter hulls).  When every piece is cleared
-// the trajectory misses the box.  Both tests only settle cases the exact
-// test decides the same way.
+// Cheaper tests settle most cases first, over equal pieces of the trajectory
+// and their quarters: a sample point (interior piece ends) inside the box
+// proves a hit; and on each piece a cubic lies in the hull of its Bernstein
+// coefficients p(ta), p(ta) + h p'(ta)/3, p(tb) - h p'(tb)/3, p(tb), so a piece
+// whose hull (widened by kHullMargin, far above the rounding of these values)
+// misses the box on some axis cannot meet it.  When every piece is cleared the
+// trajectory misses the box.  They only settle cases the exact test decides
+// the same way.
 constexpr double kHullMargin = 1e-9;
-enum BoxTest : int { kBoxMiss = 0, kBoxHit = 1, kBoxUnsure = 2 };
 
 // Does the hull of the piece with end values (pa, da), (pb, db) and length
 // 3 * h3 miss the box on some axis?
@@ -411,56 +409,8 @@ __device__ __forceinline__ bool point_in_box(const double* p, const float* box) 
 __device__ __forceinline__ void eval_pd(const Cubic* cs, double t, double* p, double* d) {
     for (int a = 0; a < 3; ++a) {
         p[a] = cs[a].at(t);
-        d[a] = cs[a].c1 + t * (2.0 * cs[a].c2 + t * 3.0 * cs[a].c3);
+        d[a] = cs[a].slope(t);
     }
-}
-
-// The piecewise test with `pieces` equal pieces (each split into 4 when its
-// hull meets the box).  The quick test uses 8 pieces; the exact stage first
-// tries 64 before solving for the slab crossings.
-__device__ __forceinline__ int trajectory_box_pieces(const Cubic* cs, double tau, const float* box,
-                                                     int pieces) {
-    const double inv = 1.0 / (double)pieces;
-    const double h = inv * tau;
-    const double h3 = h * (1.0 / 3.0);          // piece length / 3 (within the margin)
-    const double q3 = 0.25 * h3;                // the same for a quarter piece
-    double pa[3], da[3];
-    for (int a = 0; a < 3; ++a) {
-        pa[a] = cs[a].c0;
-        da[a] = cs[a].c1;
-    }
-    bool ambiguous = false;
-    for (int k = 1; k <= pieces; ++k) {
-        const double ta = tau * (inv * (double)(k - 1));
-        const double t = k == pieces ? tau : tau * (inv * (double)k);
-        double pb[3], db[3];
-        eval_pd(cs, t, pb, db);
-        if (k < pieces && point_in_box(pb, box)) return kBoxHit;
-        if (!piece_clear(pa, da, pb, db, h3, box)) {
-            // split the piece into 4
-            double qa[3] = {pa[0], pa[1], pa[2]}, qd[3] = {da[0], da[1], da[2]};
-            for (int j = 1; j <= 4; ++j) {
-                double qb[3], qe[3];
-                if (j == 4) {
-                    for (int a = 0; a < 3; ++a) { qb[a] = pb[a]; qe[a] = db[a]; }
-                } else {
-                    eval_pd(cs, ta + 0.25 * (double)j * h, qb, qe);
-                    if (point_in_box(qb, box)) return kBoxHit;
-                }
-                ambiguous |= !piece_clear(qa, qd, qb, qe, q3, box);
-                for (int a = 0; a < 3; ++a) { qa[a] = qb[a]; qd[a] = qe[a]; }
-            }
-        }
-        for (int a = 0; a < 3; ++a) {
-            pa[a] = pb[a];
-            da[a] = db[a];
-        }
-    }
-    return ambiguous ? kBoxUnsure : kBoxMiss;
-}
-
-__device__ __forceinline__ int trajectory_box_quick(const Cubic* cs, double tau, const float* box) {
-    return trajectory_box_pieces(cs, tau, box, 8);
 }
 
 __device__ __forceinline__ bool trajectory_hits_box_exact(const Cubic* cs, double tau,
@@ -484,12 +434,6 @@ __device__ __forceinline__ bool trajectory_hits_box_exact(const Cubic* cs, doubl
                 hit |= ok[0][i] && ok[1][j] && ok[2][k] && st <= en;
             }
     return hit;
-}
-
-__device__ __forceinline__ bool trajectory_hits_box(const Cubic* cs, double tau, const float* box) {
-    const int q = trajectory_box_quick(cs, tau, box);
-    if (q != kBoxUnsure) return q == kBoxHit;
-    return trajectory_hits_box_exact(cs, tau, box);
 }
 
 // ---------------------------------------------------------------------------

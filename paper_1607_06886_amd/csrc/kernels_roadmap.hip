@@ -43,11 +43,11 @@ void launch_rm_bbox(hipStream_t s, const float* X, const int32_t* esrc, const in
 }
 
 void launch_rm_query(hipStream_t s, const float* X, const uint8_t* valid, int n_nodes,
-                     const float* obs, int n_obs, double r_steer, double r_conn,
+                     const float* obs, int n_obs, const uint32_t* bins, double r_steer, double r_conn,
                      const RoadmapDev& rm, uint32_t* ebits, int words, int32_t* deg, int32_t* bad,
                      const GraphWork& gw) {
     k_rm_check<<<(n_nodes * 6 + 255) / 256, 256, 0, s>>>(X, rm.X, n_nodes, bad);
-    launch_graph_pass1_roadmap(s, X, valid, n_nodes, obs, n_obs, r_steer, r_conn, rm.esrc, rm.col,
+    launch_graph_pass1_roadmap(s, X, valid, n_nodes, obs, n_obs, bins, r_steer, r_conn, rm.esrc, rm.col,
                                rm.tau, rm.bbox, rm.n_edges, ebits, deg, words, gw);
 }
 

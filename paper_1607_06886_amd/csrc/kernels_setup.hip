@@ -127,32 +127,16 @@ __global__ __launch_bounds__(256) void k_gw_near_col0(const float* __restrict__ 
 }
 
 // boxes over the near list (count on the device) or a cached list (count given)
-// (three waves per SIMD: the compiler spills about 40 VGPRs there, which
-// measured faster than two waves without spills -- indoor query, pass 1
-// 7.36 -> 6.96 ms -- and than four waves with more spills)
-__global__ __launch_bounds__(kBoxThreads, 3) void k_gw_boxes(const float* __restrict__ X,
-                                                          const uint8_t* __restrict__ valid,
-                                                          const int32_t* __restrict__ src,
-                                                          const int32_t* __restrict__ dst,
-                                                          const double* __restrict__ tau,
-                                                          const double* __restrict__ bbox,
-                                                          int count, int near_list,
-                                                          const float* __restrict__ obs,
-                                                          int n_obs, GraphWork gw,
-                                                          uint32_t* __restrict__ ebits,
-                                                          int words) {
-    __shared__ float s_obs[kMaxObs * 6];
-    __shared__ uint32_t s_q[kBoxThreads / 64 * kBoxQueue];
-    __shared__ int s_src[kBoxThreads], s_dst[kBoxThreads], s_blk[kBoxThreads];
-    __shared__ double s_tau[kBoxThreads];
-    __shared__ BoxBins s_bins;
-    for (int t = threadIdx.x; t < n_obs * 6; t += blockDim.x) s_obs[t] = obs[t];
-    __syncthreads();
-    box_bins_build(s_obs, n_obs, &s_bins);
+__global__ __launch_bounds__(kBoxThreads, 4) void k_gw_boxes(
+    const float* __restrict__ X, const uint8_t* __restrict__ valid, const int32_t* __restrict__ src,
+    const int32_t* __restrict__ dst, const double* __restrict__ tau, const double* __restrict__ bbox, int count,
+    int near_list, const float* __restrict__ obs, int n_obs, const uint32_t* __restrict__ bins, GraphWork gw,
+    uint32_t* __restrict__ ebits, int words) {
+    extern __shared__ __align__(16) char s_raw[];
     const int N = near_list ? min(gw.counts[0], gw.near_cap) : count;
-    gw_boxes(X, valid, src, dst, tau, bbox, N, near_list != 0, near_list == 0, s_obs, n_obs, &s_bins, gw,
-             ebits, words, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, s_q,
-             s_src, s_dst, s_tau, s_blk);
+    if ((int)(blockIdx.x * blockDim.x) >= N) return;
+    gw_boxes(X, valid, src, dst, tau, bbox, N, near_list != 0, near_list == 0, obs, n_obs, bins, gw, ebits, words,
+             blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, s_raw);
 }
 
 __global__ __launch_bounds__(256) void k_gw_exact(const float* __restrict__ X,
@@ -212,18 +196,18 @@ constexpr int kStageBlocks = 2048;   // grid of the grid-stride stages
 }
 
 void launch_graph_mark(hipStream_t s, const float* X, const uint8_t* valid, int n_nodes,
-                       const float* obs, int n_obs, double r_steer, double r_conn,
+                       const float* obs, int n_obs, const uint32_t* bins, double r_steer, double r_conn,
                        uint32_t* ebits, int32_t* deg, int words, const GraphWork& gw) {
     (void)hipMemsetAsync(ebits, 0, (size_t)n_nodes * words * sizeof(uint32_t), s);
     k_gw_near_rows<<<n_nodes, kNearThreads, 0, s>>>(X, valid, n_nodes, 0, r_steer, r_conn, gw);
-    k_gw_boxes<<<kStageBlocks, kBoxThreads, 0, s>>>(X, valid, gw.near_src, gw.near_dst, gw.near_tau,
-                                            nullptr, 0, 1, obs, n_obs, gw, ebits, words);
+    k_gw_boxes<<<kStageBlocks, kBoxThreads, gw_boxes_lds(n_obs), s>>>(X, valid, gw.near_src, gw.near_dst, gw.near_tau,
+                                            nullptr, 0, 1, obs, n_obs, bins, gw, ebits, words);
     k_gw_exact<<<kStageBlocks, 256, 0, s>>>(X, obs, gw, nullptr, nullptr, nullptr, ebits, words);
     k_row_deg<<<(n_nodes + 3) / 4, 256, 0, s>>>(ebits, n_nodes, words, deg);
 }
 
 void launch_graph_pass1_roadmap(hipStream_t s, const float* X, const uint8_t* valid, int n_nodes,
-                                const float* obs, int n_obs, double r_steer, double r_conn,
+                                const float* obs, int n_obs, const uint32_t* bins, double r_steer, double r_conn,
                                 const int32_t* rm_src, const int32_t* rm_dst,
                                 const double* rm_tau, const double* rm_bbox, int rm_edges,
                                 uint32_t* ebits, int32_t* deg, int words, const GraphWork& gw) {
@@ -233,13 +217,13 @@ void launch_graph_pass1_roadmap(hipStream_t s, const float* X, const uint8_t* va
     const int col = n_nodes - 1;
     k_gw_near_col0<<<(col + 255) / 256 > 0 ? (col + 255) / 256 : 1, 256, 0, s>>>(
         X, valid, n_nodes, r_steer, r_conn, gw);
-    k_gw_boxes<<<64, kBoxThreads, 0, s>>>(X, valid, gw.near_src, gw.near_dst, gw.near_tau, nullptr, 0, 1, obs,
-                                  n_obs, gw, ebits, words);
+    k_gw_boxes<<<64, kBoxThreads, gw_boxes_lds(n_obs), s>>>(X, valid, gw.near_src, gw.near_dst, gw.near_tau, nullptr, 0, 1, obs,
+                                  n_obs, bins, gw, ebits, words);
     int blocks = (rm_edges + 255) / 256;
     if (blocks < 1) blocks = 1;
     if (blocks > kStageBlocks) blocks = kStageBlocks;
-    k_gw_boxes<<<blocks, kBoxThreads, 0, s>>>(X, valid, rm_src, rm_dst, rm_tau, rm_bbox, rm_edges, 0, obs,
-                                      n_obs, gw, ebits, words);
+    k_gw_boxes<<<blocks, kBoxThreads, gw_boxes_lds(n_obs), s>>>(X, valid, rm_src, rm_dst, rm_tau, rm_bbox, rm_edges, 0, obs,
+                                      n_obs, bins, gw, ebits, words);
     k_gw_exact<<<kStageBlocks, 256, 0, s>>>(X, obs, gw, rm_src, rm_dst, rm_tau, ebits, words);
     k_row_deg<<<(n_nodes + 3) / 4, 256, 0, s>>>(ebits, n_nodes, words, deg);
 }

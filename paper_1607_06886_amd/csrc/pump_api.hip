@@ -628,11 +628,11 @@ int pump_setup(pump_ctx* ctx, const pump_problem* pr) {
     tbeg(ctx, 1);
     if (ctx->rm)
         launch_rm_query(ctx->stream, ctx->X, ctx->valid, ctx->n_nodes, ctx->obs, ctx->n_obs,
-                        (double)cfg.r_steer, (double)cfg.r_conn, ctx->rm->d, ctx->ebits,
+                        ctx->bins, (double)cfg.r_steer, (double)cfg.r_conn, ctx->rm->d, ctx->ebits,
                         ctx->words_per_row, ctx->deg, ctx->dev_ints + 1, gw);
     else
         launch_graph_mark(ctx->stream, ctx->X, ctx->valid, ctx->n_nodes, ctx->obs, ctx->n_obs,
-                          (double)cfg.r_steer, (double)cfg.r_conn, ctx->ebits, ctx->deg,
+                          ctx->bins, (double)cfg.r_steer, (double)cfg.r_conn, ctx->ebits, ctx->deg,
                           ctx->words_per_row, gw);
     tend(ctx);
     const int32_t nn = ctx->n_nodes;

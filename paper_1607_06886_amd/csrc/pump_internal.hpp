@@ -234,13 +234,13 @@ void launch_rm_bbox(hipStream_t s, const float* X, const int32_t* esrc, const in
 // Pass 1 from a roadmap (ebits cleared here), then the row degrees; bit 4 of
 // *bad when the query's samples differ from it.  gw.counts must be zero.
 void launch_rm_query(hipStream_t s, const float* X, const uint8_t* valid, int n_nodes,
-                     const float* obs, int n_obs, double r_steer, double r_conn,
+                     const float* obs, int n_obs, const uint32_t* bins, double r_steer, double r_conn,
                      const RoadmapDev& rm, uint32_t* ebits, int words, int32_t* deg, int32_t* bad,
                      const GraphWork& gw);
 // Pass 1 over cached connections (src, dst, tau, nominal range) plus the
 // pairs at node 0 (kernels_setup.hip).
 void launch_graph_pass1_roadmap(hipStream_t s, const float* X, const uint8_t* valid, int n_nodes,
-                                const float* obs, int n_obs, double r_steer, double r_conn,
+                                const float* obs, int n_obs, const uint32_t* bins, double r_steer, double r_conn,
                                 const int32_t* rm_src, const int32_t* rm_dst,
                                 const double* rm_tau, const double* rm_bbox, int rm_edges,
                                 uint32_t* ebits, int32_t* deg, int words, const GraphWork& gw);
@@ -262,7 +262,7 @@ void launch_mark_valid(hipStream_t s, const float* X, int n_nodes, const float* 
 // BuildGraph pass 1 from scratch: the edge bit matrix (cleared here) and the
 // row degrees.  gw.counts must be zero.
 void launch_graph_mark(hipStream_t s, const float* X, const uint8_t* valid, int n_nodes,
-                       const float* obs, int n_obs, double r_steer, double r_conn,
+                       const float* obs, int n_obs, const uint32_t* bins, double r_steer, double r_conn,
                        uint32_t* ebits, int32_t* deg, int words, const GraphWork& gw);
 void launch_graph_fill(hipStream_t s, const float* X, int n_nodes, double r_steer,
                        const uint32_t* ebits, const int32_t* row_ptr, int32_t* col,

@@ -98,7 +98,7 @@ int pump_roadmap_create(const pump_config* cfg, const float* samples, int32_t n,
     A(hipMemsetAsync(t.valid, 0, 1, s));
     A(hipMemsetAsync(t.deg, 0, ((size_t)nn + 1) * sizeof(int32_t), s));
     const GraphWork gw{t.w_ns, t.w_nd, t.w_nt, t.w_xe, t.w_xb, t.ints + 4, (int32_t)ncap, 1};
-    launch_graph_mark(s, rm->X, t.valid, nn, nullptr, 0, (double)cfg->r_steer, (double)cfg->r_conn,
+    launch_graph_mark(s, rm->X, t.valid, nn, nullptr, 0, nullptr, (double)cfg->r_steer, (double)cfg->r_conn,
                       t.ebits, t.deg, words, gw);
     scan_exclusive(s, t.deg, rm->row_ptr, t.ints, nn, t.ints + 2, t.blk);
     A(hipMemcpyAsync(ints_h, t.ints, sizeof(ints_h), hipMemcpyDeviceToHost, s));

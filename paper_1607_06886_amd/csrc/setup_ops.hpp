@@ -441,229 +441,375 @@ __device__ __forceinline__ void gw_near_col0(const float* __restrict__ X,
     gw_push_near(gw, ok, src, 0, tau);
 }
 
-// The quick test's 8 pieces of one connection against the boxes its range
-// meets (bit set ov, n_ov boxes), each piece's hull computed once for all of
-// them.  A hull that misses a box clears that piece for that box (as in
-// trajectory_box_pieces).  A piece whose hull lies inside a box's slabs on
-// two axes, by kHullMargin, while its end values on the third axis enclose a
-// value inside that slab by the same margin, proves a hit: the third
-// coordinate passes through its slab while the other two stay in theirs (a
-// thin wall crossed inside its extent is settled this way).  Returns true on
-// a proved hit; otherwise ov / n_ov keep the boxes that some piece's hull
-// meets without a proof (left to the quick test) and the others are missed.
-__device__ __forceinline__ bool pieces_vs_boxes(const Cubic* cs, double tau, const float* s_obs,
-                                                unsigned long long* ov, int& n_ov) {
-    constexpr int kP = 8;
-    const double inv = 1.0 / (double)kP;
-    const double h3 = (inv * tau) * (1.0 / 3.0);
-    double pa[3], da[3];
-    for (int a = 0; a < 3; ++a) {
-        pa[a] = cs[a].c0;
-        da[a] = cs[a].c1;
-    }
-    unsigned long long unres[kMaxObsWords] = {0ull, 0ull, 0ull, 0ull};
-    for (int k = 1; k <= kP; ++k) {
-        const double t = k == kP ? tau : tau * (inv * (double)k);
-        double pb[3], db[3];
-        eval_pd(cs, t, pb, db);
-        double lo[3], hi[3], emin[3], emax[3];
-        for (int a = 0; a < 3; ++a) {
-            const double b1 = pa[a] + h3 * da[a], b2 = pb[a] - h3 * db[a];
-            emin[a] = fmin(pa[a], pb[a]);
-            emax[a] = fmax(pa[a], pb[a]);
-            lo[a] = fmin(emin[a], fmin(b1, b2)) - kHullMargin;
-            hi[a] = fmax(emax[a], fmax(b1, b2)) + kHullMargin;
-        }
-        for (int w = 0; w < kMaxObsWords; ++w) {
-            unsigned long long m = ov[w];
-            while (m) {
-                const int o = w * 64 + __ffsll((long long)m) - 1;
-                const unsigned long long bit = m & (~m + 1ull);
-                m &= m - 1ull;
-                const float* bx = s_obs + o * 6;
-                bool sep = false, in[3], cr[3];
-                for (int a = 0; a < 3; ++a) {
-                    const double blo = (double)bx[a], bhi = (double)bx[3 + a];
-                    sep |= (hi[a] < blo) | (lo[a] > bhi);
-                    in[a] = (lo[a] >= blo) & (hi[a] <= bhi);
-                    const double ilo = blo + kHullMargin, ihi = bhi - kHullMargin;
-                    cr[a] = (ilo <= ihi) & (emin[a] <= ihi) & (emax[a] >= ilo);
-                }
-                if (sep) continue;
-                if ((in[0] & in[1] & cr[2]) | (in[0] & cr[1] & in[2]) | (cr[0] & in[1] & in[2]))
-                    return true;
-                unres[w] |= bit;
-            }
-        }
-        for (int a = 0; a < 3; ++a) {
-            pa[a] = pb[a];
-            da[a] = db[a];
-        }
-    }
-    n_ov = 0;
-    for (int w = 0; w < kMaxObsWords; ++w) {
-        ov[w] = unres[w];
-        n_ov += __popcll(unres[w]);
-    }
-    return false;
-}
-
 // boxes over one list of connections (src, dst, tau, optional cached range).
 // Exact-queue entries name the connection by `tag` (>= 0: index into the
 // roadmap list, < 0: -1 - index into the near list).  check_valid: skip
 // connections with an invalid end (the cached roadmap list).
 //
-// Lane i of a wave takes connection i of the wave's 64 and finds the boxes
-// its range meets (candidates from the workspace partition `bins`, then the
-// range test), then runs pieces_vs_boxes over them.  The (connection, box)
-// pairs that leaves open are spread over all 64 lanes through an LDS queue
-// per wave, so a connection with many of them does not hold its wave: each
-// pair gets the quick test, a hit blocks the connection, an unsure pair goes
-// to the exact queue; connections not blocked set their bit.  Whole
-// workgroup of kBoxThreads; s_q/s_src/s_dst/s_tau/s_blk are per-wave LDS
-// arrays (kBoxQueue, 64, 64, 64, 64 entries per wave).
+// What bounds it is lanes without work: which boxes a connection comes near,
+// and how far each must be looked into, differs from lane to lane.  So a wave
+// takes 64 connections, lane by lane, only as far as every lane does the same
+// -- the cubic, then its 8 pieces one after the other, each with the boxes that
+// its extents' bins hold (FP32, in units of bins, widened by a bound of the
+// rounding) -- and what differs goes through two
+// queues in the wave's LDS, each worked on 64 entries at a time:
+//   1. (connection, piece, box), the box met by the piece's extents in FP32:
+//      the hull of the piece against the box in FP64.  It may miss the box (as
+//      piece_clear), or prove a hit: it lies inside the box's slabs on two
+//      axes, by kHullMargin, while its end values on the third enclose a value
+//      inside that slab by the same margin (the third coordinate passes through
+//      its slab while the other two stay in theirs; a thin wall crossed inside
+//      its extent is settled this way);
+//   2. those left: the piece's end and quarters; a sample point (not the
+//      trajectory's own ends) inside the box proves a hit, and a box that some
+//      quarter's hull still meets is left to the exact stage.
+// A connection that a hit blocks drops out.  The indoor query of 20,000 samples
+// (20.3 million connections, 6 in 10 blocked, 1.4 entries of queue 1 and 0.3 of
+// queue 2 each) took 3.53 ms in this kernel with a lane per connection for all
+// of it (29 % of the lanes with work) and a step of the exact list's counter for
+// each connection's boxes; now it takes 1.29.
 constexpr int kBoxThreads = 256;
-constexpr int kBoxQueue = 256;
+constexpr int kBoxWaves = kBoxThreads / 64;
+constexpr int kPieces = 8;
+constexpr int kBoxQueue = 128;   // 63 left + 64 new
+
+// One wave's LDS.
+struct BoxWaveLds {
+    double c23[6][64], tau[64];              // cubics: c2, c3 per axis
+    float c01[6][64];                        // and c0, c1 (the start's FP32 state)
+    uint32_t q1[kBoxQueue], q2[kBoxQueue];   // connection | piece << 6 | box << 9
+    int x_edge[kBoxQueue], x_box[kBoxQueue]; // for the exact stage
+    int blocked[64];
+};
+
+// Workgroup's dynamic LDS: per wave its BoxWaveLds, then per connection the
+// boxes left to the exact stage, then the boxes and their bins.
+__host__ __device__ inline size_t gw_boxes_lds(int n_obs) {
+    return sizeof(BoxWaveLds) * kBoxWaves + (size_t)kBoxThreads * ((n_obs + 63) / 64) * 8 +
+           (size_t)(bin_words(n_obs) - kBinHeader) * 4 + (size_t)n_obs * 48;
+}
 
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
 }
 
+struct BoxStage {
+    BoxWaveLds* w;               // this wave's
+    uint32_t* left;              // [64][2 nw] bits of the boxes left to the exact stage
+    const float* obs;
+    const float* obs_bins;       // the boxes in units of bins
+    BinView bins;
+    int n1, n2, nx;              // queue lengths (wave-uniform)
+};
+
+__device__ __forceinline__ Cubic axis_cubic(const BoxWaveLds& l, int c, int a) {
+    return Cubic{(double)l.c01[2 * a][c], (double)l.c01[2 * a + 1][c], l.c23[2 * a][c], l.c23[2 * a + 1][c]};
+}
+
+// Time of piece end k.
+__device__ __forceinline__ double piece_end(double tau, int k) {
+    constexpr double inv = 1.0 / (double)kPieces;
+    return k == kPieces ? tau : tau * (inv * (double)k);
+}
+
+// The last (at most 16) entries of queue 2, a lane per quarter.
+__device__ __forceinline__ void box_quarters(BoxStage& g) {
+    const int lane = threadIdx.x & 63, j = lane & 3;
+    wave_lds_sync();
+    const int n = min(g.n2, 16);
+    g.n2 -= n;
+    if ((lane >> 2) < n) {
+        const uint32_t e = g.w->q2[g.n2 + (lane >> 2)];
+        const int c = e & 63, k = (e >> 6) & 7, o = e >> 9;
+        if (!g.w->blocked[c]) {
+            const double tau = g.w->tau[c];
+            const float* box = g.obs + o * 6;
+            constexpr double inv = 1.0 / (double)kPieces;
+            const double h = inv * tau, q3 = 0.25 * (h * (1.0 / 3.0)), t0 = tau * (inv * (double)k);
+            const double ta = j == 0 ? piece_end(tau, k) : t0 + 0.25 * (double)j * h;
+            const double tb = j == 3 ? piece_end(tau, k + 1) : t0 + 0.25 * (double)(j + 1) * h;
+            bool sep = false, inside = true;
+#pragma unroll 1
+            for (int a = 0; a < 3; ++a) {
+                const Cubic q = axis_cubic(*g.w, c, a);
+                const double pa = q.at(ta), pb = q.at(tb);
+                const double b1 = pa + q3 * q.slope(ta), b2 = pb - q3 * q.slope(tb);
+                const double lo = fmin(fmin(pa, pb), fmin(b1, b2)) - kHullMargin;
+                const double hi = fmax(fmax(pa, pb), fmax(b1, b2)) + kHullMargin;
+                const double blo = (double)box[a], bhi = (double)box[3 + a];
+                sep |= (hi < blo) | (lo > bhi);
+                inside &= (pb >= blo) & (pb <= bhi);
+            }
+            if (inside && (j < 3 || k + 1 < kPieces))
+                g.w->blocked[c] = 1;
+            else if (!sep)
+                atomicOr(&g.left[c * 2 * g.bins.nw + (o >> 5)], 1u << (o & 31));
+        }
+    }
+    wave_lds_sync();
+}
+
+// Lanes before this one for which ok holds (all lanes call it).
+__device__ __forceinline__ int wave_rank(bool ok) {
+    const unsigned long long m = __ballot(ok);
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Appends to a wave's queue (all lanes call it); at most 64 entries.
+__device__ __forceinline__ void box_push(uint32_t* q, int& n, bool ok, uint32_t e) {
+    const int at = n + wave_rank(ok);
+    if (ok) q[at] = e;
+    n += (int)__popcll(__ballot(ok));
+}
+
+// The last (at most 64) entries of queue 1.
+__device__ __forceinline__ void box_hulls(BoxStage& g) {
+    const int lane = threadIdx.x & 63;
+    wave_lds_sync();
+    const int n = min(g.n1, 64);
+    g.n1 -= n;
+    bool open = false;
+    uint32_t e = 0;
+    if (lane < n) {
+        e = g.w->q1[g.n1 + lane];
+        const int c = e & 63, k = (e >> 6) & 7, o = e >> 9;
+        if (!g.w->blocked[c]) {
+            const double tau = g.w->tau[c];
+            const double h3 = (1.0 / (double)kPieces * tau) * (1.0 / 3.0);
+            const double ta = piece_end(tau, k), tb = piece_end(tau, k + 1);
+            const float* bx = g.obs + o * 6;
+            bool sep = false;
+            uint32_t in = 0, cr = 0;
+#pragma unroll 1
+            for (int a = 0; a < 3; ++a) {   // (an axis at a time: registers)
+                const Cubic q = axis_cubic(*g.w, c, a);
+                const double pa = q.at(ta), pb = q.at(tb);
+                const double b1 = pa + h3 * q.slope(ta), b2 = pb - h3 * q.slope(tb);
+                const double emin = fmin(pa, pb), emax = fmax(pa, pb);
+                const double lo = fmin(emin, fmin(b1, b2)) - kHullMargin;
+                const double hi = fmax(emax, fmax(b1, b2)) + kHullMargin;
+                const double blo = (double)bx[a], bhi = (double)bx[3 + a];
+                sep |= (hi < blo) | (lo > bhi);
+                const double ilo = blo + kHullMargin, ihi = bhi - kHullMargin;
+                in |= (uint32_t)((lo >= blo) & (hi <= bhi)) << a;
+                cr |= (uint32_t)((ilo <= ihi) & (emin <= ihi) & (emax >= ilo)) << a;
+            }
+            const uint32_t out = 7u & ~in;   // axes on which it is not inside
+            const bool hit = out == 0u ? cr != 0u : ((out & (out - 1u)) == 0u && (cr & out));
+            if (!sep && hit) g.w->blocked[c] = 1;
+            open = !sep && !hit;
+        }
+    }
+    box_push(g.w->q2, g.n2, open, e);
+    while (g.n2 >= 64) box_quarters(g);
+    wave_lds_sync();
+}
+
+// The last (at most 64) entries for the exact stage to its list: one step of
+// the list's counter, which all waves share, for all of them (with a step for
+// every connection's boxes, 180,000 of them, the indoor query's stage took 2.28
+// ms instead of 1.48).
+__device__ __forceinline__ void box_exact_flush(BoxStage& g, const GraphWork& gw) {
+    const int lane = threadIdx.x & 63;
+    wave_lds_sync();
+    const int n = min(g.nx, 64);
+    g.nx -= n;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(gw.counts + 1, n);
+    at = __shfl(at, 0, 64) + lane;
+    if (lane < n && at < gw.xq_cap) {
+        gw.xq_edge[at] = g.w->x_edge[g.nx + lane];
+        gw.xq_box[at] = g.w->x_box[g.nx + lane];
+    }
+    wave_lds_sync();
+}
+
+__device__ __forceinline__ bool boxes_apart(const float* lo, const float* hi, const float* bx) {
+    return (hi[0] < bx[0]) | (lo[0] > bx[3]) | (hi[1] < bx[1]) | (lo[1] > bx[4]) | (hi[2] < bx[2]) |
+           (lo[2] > bx[5]);
+}
+
+// Whole workgroup of kBoxThreads; lds: gw_boxes_lds(n_obs) bytes; bins: the
+// query's table in memory (not read without boxes).
 __device__ __forceinline__ void gw_boxes(const float* __restrict__ X,
                                          const uint8_t* __restrict__ valid,
                                          const int32_t* __restrict__ src_a,
                                          const int32_t* __restrict__ dst_a,
                                          const double* __restrict__ tau_a,
                                          const double* __restrict__ bbox, int count, bool near_list,
-                                         bool check_valid, const float* s_obs, int n_obs,
-                                         const BoxBins* bins,
-                                         const GraphWork& gw, uint32_t* __restrict__ ebits,
-                                         int words, int gid, int stride, uint32_t* s_q,
-                                         int* s_src, int* s_dst, double* s_tau, int* s_blk) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint32_t* q = s_q + w * kBoxQueue;
-    int* qs = s_src + w * 64;
-    int* qd = s_dst + w * 64;
-    double* qt = s_tau + w * 64;
-    int* blk = s_blk + w * 64;
+                                         bool check_valid, const float* __restrict__ obs, int n_obs,
+                                         const uint32_t* __restrict__ bins, const GraphWork& gw,
+                                         uint32_t* __restrict__ ebits, int words, int gid, int stride,
+                                         char* lds) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    BoxStage g;
+    g.w = reinterpret_cast<BoxWaveLds*>(lds) + wave;
+    g.n1 = g.n2 = g.nx = 0;
+    {
+        const int nw = (n_obs + 63) / 64, n_set = bin_words(n_obs) - kBinHeader;
+        uint32_t* left = reinterpret_cast<uint32_t*>(lds + sizeof(BoxWaveLds) * kBoxWaves);
+        uint32_t* set = left + kBoxThreads * nw * 2;
+        float* s_obs = reinterpret_cast<float*>(set + n_set);
+        for (int t = threadIdx.x; t < n_set; t += kBoxThreads) set[t] = bins[kBinHeader + t];
+        float* s_obs_bins = s_obs + n_obs * 6;
+        for (int t = threadIdx.x; t < n_obs * 6; t += kBoxThreads) {
+            const int a = t % 3;
+            s_obs[t] = obs[t];
+            s_obs_bins[t] = (obs[t] - __uint_as_float(bins[a])) * __uint_as_float(bins[3 + a]);
+        }
+        g.obs_bins = s_obs_bins;
+        for (int a = 0; a < 3; ++a) {
+            g.bins.org[a] = n_obs ? __uint_as_float(bins[a]) : 0.0f;
+            g.bins.scale[a] = n_obs ? __uint_as_float(bins[3 + a]) : 0.0f;
+        }
+        g.bins.nw = nw;
+        g.bins.set = reinterpret_cast<const unsigned long long*>(set);
+        g.left = left + wave * 64 * nw * 2;
+        g.obs = s_obs;
+        for (int k = 0; k < 2 * nw; ++k) g.left[lane * 2 * nw + k] = 0u;
+        __syncthreads();
+    }
+    const int nw = g.bins.nw;
     // all lanes of a wave iterate together (stride is a multiple of 64)
     for (int base = gid - lane; base < count; base += stride) {
         const int i = base + lane;
         bool keep = i < count;
-        int src = 0, dst = 0;
-        double tau = 0.0;
-        if (keep) {
-            src = src_a[i];
-            dst = dst_a[i];
-            tau = tau_a[i];
-            keep = !check_valid || (valid[src] && valid[dst]);
+        if (keep) keep = !check_valid || (valid[src_a[i]] && valid[dst_a[i]]);
+        bool look = keep;
+        if (bbox && look) {
+            // a cached range that meets no box settles the connection
+            float lo[3], hi[3];
+            for (int a = 0; a < 3; ++a) {
+                lo[a] = __double2float_rd(bbox[(size_t)i * 6 + a]);
+                hi[a] = __double2float_ru(bbox[(size_t)i * 6 + 3 + a]);
+            }
+            BinRange r;
+            bin_range(g.bins, lo, hi, r);
+            look = false;
+            for (int w = 0; w < nw && !look; ++w) look = bin_candidates(g.bins, r, w) != 0ull;
         }
-        unsigned long long ov[kMaxObsWords] = {0ull, 0ull, 0ull, 0ull};
-        int n_ov = 0;
-        bool proved = false;
-        if (keep) {
-            if (n_obs > 0) {
-                double mn[3], mx[3];
+        g.w->blocked[lane] = 0;
+        if (__ballot(look) != 0ull) {
+            // q(u) = (p - org) * scale, u = piece units: k0 + u (k1 + u (k2 + u k3))
+            float k0[3], k1[3], k2[3], k3[3], pad[3];
+            for (int a = 0; a < 3; ++a) k0[a] = k1[a] = k2[a] = k3[a] = pad[a] = 0.0f;
+            if (look) {
                 Cubic cs[3];
-                if (bbox) {
-                    for (int a = 0; a < 3; ++a) {
-                        mn[a] = bbox[(size_t)i * 6 + a];
-                        mx[a] = bbox[(size_t)i * 6 + 3 + a];
-                    }
-                } else {
-                    hermite(X + (size_t)src * 6, X + (size_t)dst * 6, tau, cs);
-                    for (int a = 0; a < 3; ++a) cubic_range(cs[a], tau, mn[a], mx[a]);
-                }
-                // the range rounded outwards to FP32: a box it misses in FP32
-                // the FP64 range misses too; the few it then meets that the
-                // FP64 range would not go to the piece and exact tests, which
-                // decide them the same way
-                float mnf[3], mxf[3];
+                const double tau = tau_a[i], h = tau * (1.0 / (double)kPieces);
+                hermite(X + (size_t)src_a[i] * 6, X + (size_t)dst_a[i] * 6, tau, cs);
+                g.w->tau[lane] = tau;
+#pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    mnf[a] = __double2float_rd(mn[a]);
-                    mxf[a] = __double2float_ru(mx[a]);
+                    g.w->c01[2 * a][lane] = (float)cs[a].c0;
+                    g.w->c01[2 * a + 1][lane] = (float)cs[a].c1;
+                    g.w->c23[2 * a][lane] = cs[a].c2;
+                    g.w->c23[2 * a + 1][lane] = cs[a].c3;
+                    const double sc = (double)g.bins.scale[a], org = (double)g.bins.org[a];
+                    k0[a] = (float)((cs[a].c0 - org) * sc);
+                    k1[a] = (float)(cs[a].c1 * (sc * h));
+                    k2[a] = (float)(cs[a].c2 * (sc * h * h));
+                    k3[a] = (float)(cs[a].c3 * (sc * h * h * h));
+                    // The coefficients, the Horner steps of the piece ends and the
+                    // control points round at most some 12 times by 2^-24 of
+                    // sums no larger than this; a box's ends three times by
+                    // 2^-24 of themselves and of 16 * scale (|org| at most 16).
+                    const float mag = fabsf(k0[a]) + 8.0f * fabsf(k1[a]) + 64.0f * fabsf(k2[a]) + 512.0f * fabsf(k3[a]);
+                    pad[a] = 0x1p-18f * (mag + (float)kBins + 16.0f * g.bins.scale[a]) +
+                             2.0f * (float)kHullMargin * g.bins.scale[a];
+                    if (!(mag <= 1e30f)) {   // (no bound: every box)
+                        k0[a] = k1[a] = k2[a] = k3[a] = 0.0f;
+                        pad[a] = INFINITY;
+                    }
                 }
-                unsigned long long cand[kMaxObsWords];
-                box_bins_query(bins, mnf, mxf, cand);
-                for (int w = 0; w < kMaxObsWords; ++w) {
-                    unsigned long long m = cand[w];
-                    while (m) {
-                        const int o = w * 64 + __ffsll((long long)m) - 1;
-                        m &= m - 1ull;
-                        const float* bx = s_obs + o * 6;
-                        const bool disjoint = (mxf[0] < bx[0]) | (mnf[0] > bx[3]) |
-                                              (mxf[1] < bx[1]) | (mnf[1] > bx[4]) |
-                                              (mxf[2] < bx[2]) | (mnf[2] > bx[5]);
-                        if (!disjoint) {
-                            ov[w] |= 1ull << (o & 63);
-                            ++n_ov;
+            }
+            float qa[3], ea[3];   // a piece's start, and a third of its length along the tangent
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                qa[a] = k0[a];
+                ea[a] = k1[a] * (1.0f / 3.0f);
+            }
+#pragma unroll 1
+            for (int k = 0; k < kPieces; ++k) {
+                const float u = (float)(k + 1);
+                float lo[3], hi[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const float qb = k0[a] + u * (k1[a] + u * (k2[a] + u * k3[a]));
+                    const float eb = (k1[a] + u * (2.0f * k2[a] + u * (3.0f * k3[a]))) * (1.0f / 3.0f);
+                    const float c1 = qa[a] + ea[a], c2 = qb - eb;
+                    lo[a] = fminf(fminf(qa[a], qb), fminf(c1, c2)) - pad[a];
+                    hi[a] = fmaxf(fmaxf(qa[a], qb), fmaxf(c1, c2)) + pad[a];
+                    qa[a] = qb;
+                    ea[a] = eb;
+                }
+                look = look && !g.w->blocked[lane];
+                if (__ballot(look) == 0ull) break;
+                for (int w = 0; w < nw; ++w) {
+                    unsigned long long m = 0ull;
+                    if (look) {
+                        BinRange r;
+#pragma unroll
+                        for (int a = 0; a < 3; ++a) {
+                            const int bh = (int)fminf(fmaxf(hi[a], 0.0f), (float)(kBins - 1));
+                            const int bl = (int)fminf(fmaxf(lo[a], 0.0f), (float)(kBins - 1));
+                            r.le[a] = (a * kBins + bh) * nw;
+                            r.ge[a] = (3 * kBins + a * kBins + bl) * nw;
                         }
+                        m = bin_candidates(g.bins, r, w);
                     }
-                }
-                if (n_ov > 0) {
-                    if (bbox) hermite(X + (size_t)src * 6, X + (size_t)dst * 6, tau, cs);
-                    proved = pieces_vs_boxes(cs, tau, s_obs, ov, n_ov);
-                    if (proved) n_ov = 0;
-                }
-            }
-        }
-        qs[lane] = src;
-        qd[lane] = dst;
-        qt[lane] = tau;
-        blk[lane] = proved ? 1 : 0;
-        // this lane's first pair within the wave's list
-        int x = n_ov;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-        }
-        const int total = __shfl(x, 63, 64);
-        const int first = x - n_ov;
-        const int tag_base = near_list ? -1 - base : base;   // tag of lane 0's connection
-        for (int seg = 0; seg < total; seg += kBoxQueue) {
-            // this lane's pairs that fall in [seg, seg + kBoxQueue)
-            if (n_ov > 0 && first < seg + kBoxQueue && first + n_ov > seg) {
-                int k = first;
-                for (int wd = 0; wd < kMaxObs / 64; ++wd) {
-                    unsigned long long m = ov[wd];
-                    while (m) {
-                        const int o = wd * 64 + __ffsll((long long)m) - 1;
+                    while (__ballot(m != 0ull) != 0ull) {
+                        const int o = w * 64 + (m ? __ffsll((long long)m) - 1 : 0);
+                        const bool met = m && !boxes_apart(lo, hi, g.obs_bins + o * 6);
                         m &= m - 1ull;
-                        if (k >= seg && k < seg + kBoxQueue) q[k - seg] = ((uint32_t)lane << 8) | (uint32_t)o;
-                        ++k;
+                        box_push(g.w->q1, g.n1, met, (uint32_t)lane | (uint32_t)k << 6 | (uint32_t)o << 9);
+                        if (g.n1 >= 64) box_hulls(g);
                     }
                 }
             }
+            while (g.n1) box_hulls(g);
+            while (g.n2) box_quarters(g);
+            // what the quarters left open, if the connection's range meets the box
             wave_lds_sync();
-            const int m_seg = min(total - seg, kBoxQueue);
-            for (int j0 = 0; j0 < m_seg; j0 += 64) {
-                const int j = j0 + lane;
-                bool unsure = false;
-                int who = 0, o = 0;
-                if (j < m_seg) {
-                    who = (int)(q[j] >> 8);
-                    o = (int)(q[j] & 255u);
-                    const int cs_src = qs[who], cs_dst = qd[who];
-                    const double ct = qt[who];
-                    Cubic cs[3];
-                    hermite(X + (size_t)cs_src * 6, X + (size_t)cs_dst * 6, ct, cs);
-                    const int r = trajectory_box_quick(cs, ct, s_obs + o * 6);
-                    if (r == kBoxHit) blk[who] = 1;
-                    unsure = r == kBoxUnsure;
+            for (int w = 0; w < 2 * nw; ++w) {
+                uint32_t m = g.left[lane * 2 * nw + w];
+                if (m) g.left[lane * 2 * nw + w] = 0u;
+                if (g.w->blocked[lane]) m = 0u;
+                float lo[3] = {0.f, 0.f, 0.f}, hi[3] = {0.f, 0.f, 0.f};
+                if (m) {
+                    for (int a = 0; a < 3; ++a) {
+                        double mn, mx;
+                        if (bbox) {
+                            mn = bbox[(size_t)i * 6 + a];
+                            mx = bbox[(size_t)i * 6 + 3 + a];
+                        } else {
+                            cubic_range(axis_cubic(*g.w, lane, a), g.w->tau[lane], mn, mx);
+                        }
+                        lo[a] = __double2float_rd(mn);
+                        hi[a] = __double2float_ru(mx);
+                    }
                 }
-                const int slot = wave_append(unsure, gw.counts + 1);
-                if (unsure && slot < gw.xq_cap) {
-                    gw.xq_edge[slot] = near_list ? tag_base - who : tag_base + who;
-                    gw.xq_box[slot] = o;
+                while (__ballot(m != 0u) != 0ull) {
+                    const int o = w * 32 + (m ? __ffs((int)m) - 1 : 0);
+                    const bool ask = m && !boxes_apart(lo, hi, g.obs + o * 6);
+                    m &= m - 1u;
+                    const int at = g.nx + wave_rank(ask);
+                    if (ask) {
+                        g.w->x_edge[at] = near_list ? -1 - i : i;
+                        g.w->x_box[at] = o;
+                    }
+                    g.nx += (int)__popcll(__ballot(ask));
+                    if (g.nx >= 64) box_exact_flush(g, gw);
                 }
             }
-            wave_lds_sync();
         }
-        wave_lds_sync();
-        if (keep && !blk[lane]) atomicOr(&ebits[(size_t)src * words + (dst >> 5)], 1u << (dst & 31));
+        if (keep && !g.w->blocked[lane]) {
+            const int dst = dst_a[i];
+            atomicOr(&ebits[(size_t)src_a[i] * words + (dst >> 5)], 1u << (dst & 31));
+        }
         wave_lds_sync();
     }
+    if (g.nx) box_exact_flush(g, gw);
 }
 
 // exact: queued (connection, box) pairs; a hit clears the connection's bit
@@ -673,9 +819,8 @@ __device__ __forceinline__ void gw_exact(const float* __restrict__ X, const floa
                                          const double* __restrict__ rm_tau,
                                          uint32_t* __restrict__ ebits, int words, int gid,
                                          int stride) {
-    // One wave per queued (connection, box); lane k takes piece k of 64 (the
-    // piecewise test of trajectory_box_pieces, its pieces side by side), and
-    // only if no piece proves a hit and some piece stays unsure does the wave
+    // One wave per queued (connection, box); lane k takes piece k of 64 (its
+    // hull, then its quarters', as the box stage does with 8 pieces), and only if no piece proves a hit and some piece stays unsure does the wave
     // solve for the slab crossings (all lanes in step on the same inputs).
     constexpr int kPieces = 64;
     const int lane = threadIdx.x & 63;
