@@ -101,17 +101,6 @@ __device__ __forceinline__ double bracket_root(const Quartic& q, int which, doub
     return t;
 }
 
-// Which branch steer64 takes for these boundary sums: true when f' >= 0 at its
-// inflection point ti, so f has one upward crossing and one root solve
-// settles it; false for the branch with up to four root solves.  (The same
-// arithmetic as steer64, so the two always agree.)
-__device__ __forceinline__ bool steer_one_root(const BSums& s, double r) {
-    if (s.pp == 0.0 && s.vv == 0.0) return true;
-    const Quartic q{-4.0 * r * s.vv, 24.0 * r * s.pv, -36.0 * r * s.pp};
-    const double ti = sqrt(-q.a2 * (1.0 / 6.0));
-    return q.g(ti) >= 0.0;
-}
-
 // Optimal duration and cost of the connection x0 -> x1 (FP64).  The global
 // minimiser of c over tau > 0 is one of the upward zero crossings of f
 // (local minima of c).  f is concave on (0, ti) and convex on (ti, inf) with
@@ -151,76 +140,110 @@ __device__ __forceinline__ void steer64(const float* x0, const float* x1, double
     cost = bc;
 }
 
-// Exact rejection test for Near: true only if c(tau) > R for every tau > 0,
-// so the pair cannot be an edge with c* < R.  For tau >= R, c(tau) >= tau >= R.
-// On (0, R), c(tau) < R iff g(tau) = tau^3 (c(tau) - R) < 0 with
+// Rejection test for Near: true only if c(tau) > R for every tau > 0, so the
+// pair cannot be an edge with c* < R.  For tau >= R, c(tau) >= tau >= R.  On
+// (0, R), c(tau) < R iff g(tau) = tau^3 (c(tau) - R) < 0 with
 //   g(tau) = tau^4 - R tau^3 + 4 r S_vv tau^2 - 12 r S_Pv tau + 12 r S_PP.
 // A polynomial whose Bernstein coefficients on an interval are all positive is
-// positive there; the test splits [0, R] into halves and quarters (de
-// Casteljau) where needed and demands a margin far above the rounding error.
-__device__ __forceinline__ bool bern_pos(const double* b, double m) {
-    return fmin(fmin(fmin(b[0], b[1]), fmin(b[2], b[3])), b[4]) > m;
+// positive there.  The coefficients of g / (12 r) on [0, R] come from three
+// sums (near_bern32: the first look, 28 operations), and those the bound does
+// not settle are split into halves and quarters (de Casteljau, near_split32).
+//
+// In FP32: every coefficient, also of the parts, is within some 20 units of
+// 2^-24 of the magnitudes that enter it, far below the margin of 1e-4 times
+// their sum (for those of S_Pv, whose terms can cancel,
+// sum |P sv| <= (S_PP + sum sv^2) / 2 and sum sv^2 <= 4/3 S_vv).  What it
+// keeps, the steering decides.
+struct Near32 {
+    float p1, p2, p3, p4;      // R / 4, R / 2, 3 R / 4, R: weights of S_Pv
+    float w2, w3, w4, c3;      // weights of S_vv and the constant of b3
+    float mp, mv, mc;          // the margin's
+};
+
+__device__ __forceinline__ Near32 near32(float r, float R) {
+    const float R2 = R * R, q = R2 * R2 / (12.0f * r);
+    Near32 k;
+    k.p1 = 0.25f * R;
+    k.p2 = 0.5f * R;
+    k.p3 = 0.75f * R;
+    k.p4 = R;
+    k.w2 = R2 * (1.0f / 18.0f);
+    k.w3 = R2 * (1.0f / 6.0f);
+    k.w4 = R2 * (1.0f / 3.0f);
+    k.c3 = -0.25f * q;
+    k.mp = 1e-4f * (1.0f + 0.5f * R);
+    k.mv = 1e-4f * (k.w4 + (2.0f / 3.0f) * R);
+    k.mc = 2e-4f * q;
+    return k;
 }
 
-__device__ __forceinline__ void bern_split(const double* b, double* L, double* Rr) {
-    double c[5] = {b[0], b[1], b[2], b[3], b[4]};
+struct Sums32 {
+    float pp, pv, vv;
+};
+
+__device__ __forceinline__ Sums32 near_sums32(const float* x0, const float* x1) {
+    Sums32 s{0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float P = x1[a] - x0[a], v0 = x0[3 + a], v1 = x1[3 + a], sv = v0 + v1;
+        s.pp = fmaf(P, P, s.pp);
+        s.pv = fmaf(P, sv, s.pv);
+        s.vv = fmaf(v1, sv, fmaf(v0, v0, s.vv));
+    }
+    return s;
+}
+
+__device__ __forceinline__ float min5(const float* b) {
+    return fminf(fminf(fminf(b[0], b[1]), fminf(b[2], b[3])), b[4]);
+}
+
+// Coefficients on [0, R] and the margin; true: all above it.
+__device__ __forceinline__ bool near_bern32(const Near32& k, const Sums32& s, float* b, float& m) {
+    b[0] = s.pp;
+    b[1] = fmaf(-k.p1, s.pv, s.pp);
+    b[2] = fmaf(k.w2, s.vv, fmaf(-k.p2, s.pv, s.pp));
+    b[3] = fmaf(k.w3, s.vv, fmaf(-k.p3, s.pv, s.pp)) + k.c3;
+    b[4] = fmaf(k.w4, s.vv, fmaf(-k.p4, s.pv, s.pp));
+    m = fmaf(k.mp, s.pp, fmaf(k.mv, s.vv, k.mc));
+    return min5(b) > m;
+}
+
+__device__ __forceinline__ void bern_split(const float* b, float* L, float* Rr) {
+    float c[5] = {b[0], b[1], b[2], b[3], b[4]};
     L[0] = c[0];
     Rr[4] = c[4];
+#pragma unroll
     for (int lvl = 1; lvl <= 4; ++lvl) {
-        for (int i = 0; i <= 4 - lvl; ++i) c[i] = 0.5 * (c[i] + c[i + 1]);
+#pragma unroll
+        for (int i = 0; i <= 4 - lvl; ++i) c[i] = 0.5f * (c[i] + c[i + 1]);
         L[lvl] = c[0];
         Rr[4 - lvl] = c[4 - lvl];
     }
 }
 
-__device__ __forceinline__ bool surely_not_near(const BSums& s, double r, double R) {
-    const double R2 = R * R, R4 = R2 * R2;
-    const double a0 = 12.0 * r * s.pp, a1 = -12.0 * r * s.pv * R, a2 = 4.0 * r * s.vv * R2;
-    const double a3 = -R4, a4 = R4;
-    const double m = 1e-9 * (fabs(a0) + fabs(a1) + fabs(a2) + fabs(a3) + fabs(a4));
-    double b[5] = {a0, a0 + 0.25 * a1, a0 + 0.5 * a1 + a2 * (1.0 / 6.0),
-                   a0 + 0.75 * a1 + 0.5 * a2 + 0.25 * a3, a0 + a1 + a2 + a3 + a4};
-    if (bern_pos(b, m)) return true;
-    double h[2][5];
+__device__ __forceinline__ bool near_split32(const float* b, float m) {
+    float h[2][5];
     bern_split(b, h[0], h[1]);
+#pragma unroll
     for (int k = 0; k < 2; ++k) {
-        if (bern_pos(h[k], m)) continue;
-        double q0[5], q1[5];
+        if (min5(h[k]) > m) continue;
+        float q0[5], q1[5];
         bern_split(h[k], q0, q1);
-        if (!(bern_pos(q0, m) && bern_pos(q1, m))) return false;
+        if (!(fminf(min5(q0), min5(q1)) > m)) return false;
     }
     return true;
 }
 
-// A cheap first look, in FP32, at the level-0 Bernstein bound that
-// surely_not_near starts with: true only where the FP64 test is true too.
-// Every FP32 coefficient is within about 20 units of 2^-24 of the magnitudes
-// that enter it (tv bounds those of S_Pv, whose terms can cancel), which is
-// far below the margin of 1e-4 times their sum, while the FP64 test's margin
-// is 1e-9 times a smaller sum; pairs the bound cannot settle go to the FP64
-// test.  r and R are FP32 values (the configuration's), so their casts are
-// exact.
-__device__ __forceinline__ bool surely_not_near32(const float* x0, const float* x1, float r,
-                                                  float R) {
-    float pp = 0.f, pv = 0.f, tv = 0.f, vv = 0.f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        const float P = x1[a] - x0[a];
-        const float v0 = x0[3 + a], v1 = x1[3 + a];
-        const float sv = v0 + v1;
-        pp += P * P;
-        pv += P * sv;
-        tv += fabsf(P * sv);
-        vv += v0 * v0 + v0 * v1 + v1 * v1;
-    }
-    const float R2 = R * R, R4 = R2 * R2;
-    const float a0 = 12.f * r * pp, a1 = -12.f * r * pv * R, a2 = 4.f * r * vv * R2;
-    const float m = 1e-4f * (fabsf(a0) + 12.f * r * tv * R + fabsf(a2) + 2.f * R4);
-    const float b1 = a0 + 0.25f * a1;
-    const float b2 = a0 + 0.5f * a1 + a2 * (1.f / 6.f);
-    const float b3 = a0 + 0.75f * a1 + 0.5f * a2 - 0.25f * R4;
-    const float b4 = a0 + a1 + a2;                 // + a3 + a4 = 0
-    return fminf(fminf(fminf(a0, b1), fminf(b2, b3)), b4) > m;
+__device__ __forceinline__ bool surely_not_near(const float* x0, const float* x1, float r, float R) {
+    float b[5], m;
+    return near_bern32(near32(r, R), near_sums32(x0, x1), b, m) || near_split32(b, m);
+}
+
+// Whether steer64 likely takes its one-root branch (f' >= 0 at the inflection
+// point): only sorts the work, either branch is there for every pair.
+__device__ __forceinline__ bool likely_one_root(const Sums32& s, float r) {
+    const float ti = sqrtf(4.0f * r * s.vv * (1.0f / 6.0f));
+    return 24.0f * r * s.pv >= (16.0f / 3.0f) * r * s.vv * ti;
 }
 
 // Minimum-effort nominal trajectory per axis (cubic Hermite):
@@ -240,19 +263,18 @@ __device__ __forceinline__ double recip_fast(double b) {
     return fma(fma(-b, r, 1.0), r, r);
 }
 
-// The same coefficients with it = 1 / tau given.
+// One axis's coefficients from its (p, v) at the ends, with it = 1 / tau given.
+__device__ __forceinline__ Cubic hermite_axis(float p0f, float v0f, float p1f, float v1f, double tau, double it) {
+    const double it2 = it * it, it3 = it2 * it;
+    const double p0 = (double)p0f, v0 = (double)v0f, v1 = (double)v1f;
+    const double P = (double)p1f - p0;
+    return Cubic{p0, v0, (3.0 * P - (2.0 * v0 + v1) * tau) * it2, (-2.0 * P + (v0 + v1) * tau) * it3};
+}
+
 __device__ __forceinline__ void hermite_r(const float* x0, const float* x1, double tau, double it,
                                           Cubic* out) {
-    const double it2 = it * it, it3 = it2 * it;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        double p0 = (double)x0[a], v0 = (double)x0[3 + a], v1 = (double)x1[3 + a];
-        double P = (double)x1[a] - p0;
-        out[a].c0 = p0;
-        out[a].c1 = v0;
-        out[a].c2 = (3.0 * P - (2.0 * v0 + v1) * tau) * it2;
-        out[a].c3 = (-2.0 * P + (v0 + v1) * tau) * it3;
-    }
+    for (int a = 0; a < 3; ++a) out[a] = hermite_axis(x0[a], x0[3 + a], x1[a], x1[3 + a], tau, it);
 }
 
 __device__ __forceinline__ void hermite(const float* x0, const float* x1, double tau, Cubic* out) {
@@ -274,11 +296,11 @@ __device__ __forceinline__ int stationary_points(const Cubic& c, double tau, dou
             else { r0 = 0.0; }
         }
     }
-    int n = 0;
-    if (r0 > 0.0 && r0 < tau) br[n++] = r0;
-    if (r1 > 0.0 && r1 < tau) br[n++] = r1;
-    if (n == 2 && br[1] < br[0]) { double t = br[0]; br[0] = br[1]; br[1] = t; }
-    return n;
+    const bool in0 = r0 > 0.0 && r0 < tau, in1 = r1 > 0.0 && r1 < tau;
+    const bool swap = in0 && in1 && r1 < r0;
+    br[0] = in0 && !swap ? r0 : r1;
+    br[1] = swap ? r0 : r1;
+    return (int)in0 + (int)in1;
 }
 
 // On a monotone piece [ta, tb] bracketing `level`: the crossing as a bracket
@@ -327,38 +349,30 @@ __device__ __forceinline__ void crossing(const Cubic& c, double ta, double tb, d
     }
 }
 
-// The set {t in [0, tau] : lo <= p(t) <= hi} as up to 3 closed intervals,
-// one per monotone piece between the stationary points: interval k is
-// [s[k], e[k]] when ok[k].  Fixed slots (no dynamic indexing), so the
-// intervals stay in registers.
-__device__ __forceinline__ void slab_set(const Cubic& c, double tau, double lo, double hi,
-                                         double* s, double* e, bool* ok) {
+// The set {t in [0, tau] : lo <= p(t) <= hi} is up to 3 closed intervals, one
+// per monotone piece between the stationary points: that of piece k = 0 .. 2 as
+// [s, e], or [inf, -inf] where there is none.
+__device__ __forceinline__ void slab_piece(const Cubic& c, double tau, double lo, double hi, int k,
+                                           double& s, double& e) {
     double br[2];
     const int nb = stationary_points(c, tau, br);
-    const double edge[4] = {0.0, nb > 0 ? br[0] : tau, nb > 1 ? br[1] : tau, tau};
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        ok[k] = false;
-        s[k] = 0.0;
-        e[k] = 0.0;
-        if (k > nb) continue;
-        const double ta = k == 0 ? 0.0 : edge[k], tb = k == nb ? tau : edge[k + 1];
-        const double pa = c.at(ta), pb = c.at(tb);
-        const bool rising = pb >= pa;
-        const double pmin = fmin(pa, pb), pmax = fmax(pa, pb);
-        if (!(pmax >= lo && pmin <= hi)) continue;
-        double l0, l1, h0, h1;
-        double st, en;
-        if (rising) {
-            if (pmin >= lo) st = ta; else { crossing(c, ta, tb, lo, true, l0, l1); st = l1; }
-            if (pmax <= hi) en = tb; else { crossing(c, ta, tb, hi, true, h0, h1); en = h0; }
-        } else {
-            if (pmax <= hi) st = ta; else { crossing(c, ta, tb, hi, false, h0, h1); st = h1; }
-            if (pmin >= lo) en = tb; else { crossing(c, ta, tb, lo, false, l0, l1); en = l0; }
-        }
-        s[k] = st;
-        e[k] = en;
-        ok[k] = true;
+    const double e1 = nb > 0 ? br[0] : tau, e2 = nb > 1 ? br[1] : tau;
+    s = INFINITY;
+    e = -INFINITY;
+    if (k > nb) return;
+    const double ta = k == 0 ? 0.0 : (k == 1 ? e1 : e2);
+    const double tb = k == nb ? tau : (k == 0 ? e1 : e2);
+    const double pa = c.at(ta), pb = c.at(tb);
+    const bool rising = pb >= pa;
+    const double pmin = fmin(pa, pb), pmax = fmax(pa, pb);
+    if (!(pmax >= lo && pmin <= hi)) return;
+    double l0, l1, h0, h1;
+    if (rising) {
+        if (pmin >= lo) s = ta; else { crossing(c, ta, tb, lo, true, l0, l1); s = l1; }
+        if (pmax <= hi) e = tb; else { crossing(c, ta, tb, hi, true, h0, h1); e = h0; }
+    } else {
+        if (pmax <= hi) s = ta; else { crossing(c, ta, tb, hi, false, h0, h1); s = h1; }
+        if (pmin >= lo) e = tb; else { crossing(c, ta, tb, lo, false, l0, l1); e = l0; }
     }
 }
 
@@ -373,8 +387,8 @@ __device__ __forceinline__ void cubic_range(const Cubic& c, double tau, double& 
 
 // Does the nominal trajectory (three axis cubics on [0, tau]) meet the closed
 // box? It is inside at time t iff all three coordinates are in their slabs,
-// so it meets the box iff the three per-axis in-slab sets intersect
-// (trajectory_hits_box_exact).
+// so it meets the box iff the three per-axis in-slab sets (slab_piece)
+// intersect: the exact test.
 //
 // Cheaper tests settle most cases first, over equal pieces of the trajectory
 // and their quarters: a sample point (interior piece ends) inside the box
@@ -385,56 +399,6 @@ __device__ __forceinline__ void cubic_range(const Cubic& c, double tau, double& 
 // trajectory misses the box.  They only settle cases the exact test decides
 // the same way.
 constexpr double kHullMargin = 1e-9;
-
-// Does the hull of the piece with end values (pa, da), (pb, db) and length
-// 3 * h3 miss the box on some axis?
-__device__ __forceinline__ bool piece_clear(const double* pa, const double* da, const double* pb,
-                                            const double* db, double h3, const float* box) {
-    bool sep = false;
-    for (int a = 0; a < 3; ++a) {
-        const double b1 = pa[a] + h3 * da[a], b2 = pb[a] - h3 * db[a];
-        const double lo = fmin(fmin(pa[a], pb[a]), fmin(b1, b2)) - kHullMargin;
-        const double hi = fmax(fmax(pa[a], pb[a]), fmax(b1, b2)) + kHullMargin;
-        sep |= (hi < (double)box[a]) | (lo > (double)box[3 + a]);
-    }
-    return sep;
-}
-
-__device__ __forceinline__ bool point_in_box(const double* p, const float* box) {
-    bool in = true;
-    for (int a = 0; a < 3; ++a) in &= (p[a] >= (double)box[a]) & (p[a] <= (double)box[3 + a]);
-    return in;
-}
-
-__device__ __forceinline__ void eval_pd(const Cubic* cs, double t, double* p, double* d) {
-    for (int a = 0; a < 3; ++a) {
-        p[a] = cs[a].at(t);
-        d[a] = cs[a].slope(t);
-    }
-}
-
-__device__ __forceinline__ bool trajectory_hits_box_exact(const Cubic* cs, double tau,
-                                                          const float* box) {
-    double s[3][3], e[3][3];
-    bool ok[3][3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        slab_set(cs[a], tau, (double)box[a], (double)box[3 + a], s[a], e[a], ok[a]);
-        if (!(ok[a][0] || ok[a][1] || ok[a][2])) return false;
-    }
-    bool hit = false;
-#pragma unroll
-    for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int j = 0; j < 3; ++j)
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const double st = fmax(fmax(s[0][i], s[1][j]), s[2][k]);
-                const double en = fmin(fmin(e[0][i], e[1][j]), e[2][k]);
-                hit |= ok[0][i] && ok[1][j] && ok[2][k] && st <= en;
-            }
-    return hit;
-}
 
 // ---------------------------------------------------------------------------
 // Half-Space Monte Carlo (Sec. III-B): the local convex region around a

@@ -136,30 +136,35 @@ __global__ __launch_bounds__(kBoxThreads, 4) void k_b_gw_boxes_rm(BatchQuery* qs
              gridDim.x * blockDim.x, s_raw);
 }
 
-__global__ __launch_bounds__(kNearThreads) void k_b_gw_near_rows(BatchQuery* qs) {
-    __shared__ int s_list[2 * kNearChunk];
-    __shared__ int s_cnt[3 + 17];
+__global__ __launch_bounds__(kNearThreads, 5) void k_b_gw_near_rows(BatchQuery* qs) {
+    __shared__ NearLds s;
     BatchQuery& Q = qs[blockIdx.y];
-    if ((int)blockIdx.x >= Q.n_nodes || (Q.use_rm && blockIdx.x > 0)) return;
-    gw_near_row(Q.X, Q.valid, Q.n_nodes, blockIdx.x, Q.r_steer, Q.r_conn, graph_work(Q), s_list,
-                s_cnt);
+    const int n = uniform(Q.n_nodes);
+    const bool use_rm = uniform((int)Q.use_rm) != 0;   // row 0 alone, a chunk of targets each
+    const int v0 = use_rm ? 0 : blockIdx.x * kNearRows, u0 = use_rm ? blockIdx.x * kNearChunk : 0;
+    if (v0 >= n || u0 >= n) return;
+    gw_near_rows(uniform(Q.X), uniform(Q.valid), v0, use_rm ? 1 : min(kNearRows, n - v0), u0,
+                 use_rm ? min(n, u0 + kNearChunk) : n, uniform(Q.r_steer), uniform(Q.r_conn),
+                 uniform(graph_work(Q)), s);
 }
 
 __global__ __launch_bounds__(kBoxThreads, 4) void k_b_gw_boxes(BatchQuery* qs) {
     extern __shared__ __align__(16) char s_raw[];
     BatchQuery& Q = qs[blockIdx.y];
-    const GraphWork gw = graph_work(Q);
-    const int n = min(gw.counts[0], gw.near_cap);
+    const GraphWork gw = uniform(graph_work(Q));
+    const int n = uniform(min(gw.counts[0], gw.near_cap));
     if ((int)(blockIdx.x * blockDim.x) >= n) return;
-    gw_boxes(Q.X, Q.valid, gw.near_src, gw.near_dst, gw.near_tau, nullptr, n, true, false, Q.obs, Q.ra[0].n_obs,
-             Q.ra[0].bins, gw, Q.ebits, Q.words, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x,
+    gw_boxes(uniform(Q.X), uniform(Q.valid), gw.near_src, gw.near_dst, gw.near_tau, nullptr, n, true, false,
+             uniform(Q.obs), uniform(Q.ra[0].n_obs), uniform(Q.ra[0].bins), gw, uniform(Q.ebits), uniform(Q.words), blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x,
              s_raw);
 }
 
 __global__ __launch_bounds__(256) void k_b_gw_exact(BatchQuery* qs) {
     BatchQuery& Q = qs[blockIdx.y];
-    gw_exact(Q.X, Q.obs, graph_work(Q), Q.rm.esrc, Q.rm.col, Q.rm.tau, Q.ebits, Q.words,
-             blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+    __shared__ ExactWaveLds s[4];
+    gw_exact(uniform(Q.X), uniform(Q.obs), uniform(graph_work(Q)), uniform(Q.rm.esrc), uniform(Q.rm.col),
+             uniform(Q.rm.tau), uniform(Q.ebits), uniform(Q.words), blockIdx.x * blockDim.x + threadIdx.x,
+             gridDim.x * blockDim.x, s);
 }
 
 __global__ __launch_bounds__(256) void k_b_row_deg(BatchQuery* qs) {
@@ -487,7 +492,7 @@ void launch_batch(hipStream_t s, BatchQuery* qs, int q, int N_max, int max_nodes
     k_b_valid<<<dim3((vmax + 255) / 256 + 1, q), 256, 0, s>>>(qs);
     k_b_zero_ebits<<<dim3(256, q), 256, 0, s>>>(qs);
     k_b_rm_check<<<dim3((max_nodes * 6 + 255) / 256, q), 256, 0, s>>>(qs);
-    k_b_gw_near_rows<<<dim3(max_nodes, q), kNearThreads, 0, s>>>(qs);
+    k_b_gw_near_rows<<<dim3((max_nodes + kNearRows - 1) / kNearRows, q), kNearThreads, 0, s>>>(qs);
     k_b_gw_near_col0<<<dim3((max_nodes + 255) / 256, q), 256, 0, s>>>(qs);
     k_b_gw_boxes<<<dim3(256, q), kBoxThreads, gw_boxes_lds(max_obs), s>>>(qs);
     k_b_gw_boxes_rm<<<dim3(256, q), kBoxThreads, gw_boxes_lds(max_obs), s>>>(qs);

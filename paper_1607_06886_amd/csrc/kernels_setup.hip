@@ -110,13 +110,14 @@ void launch_mark_valid(hipStream_t s, const float* X, int n_nodes, const float* 
 }
 
 // ---- BuildGraph pass 1 stages (setup_ops.hpp) ----
-__global__ __launch_bounds__(kNearThreads) void k_gw_near_rows(const float* __restrict__ X,
+// Workgroups by row group, then by parts of `part` targets; rows 0 .. rows - 1.
+__global__ __launch_bounds__(kNearThreads, 5) void k_gw_near_rows(const float* __restrict__ X,
                                                       const uint8_t* __restrict__ valid, int n,
-                                                      int row0, double r_steer, double r_conn,
+                                                      int rows, int part, double r_steer, double r_conn,
                                                       GraphWork gw) {
-    __shared__ int s_list[2 * kNearChunk];
-    __shared__ int s_cnt[3 + 17];
-    gw_near_row(X, valid, n, row0 + blockIdx.x, r_steer, r_conn, gw, s_list, s_cnt);
+    __shared__ NearLds s;
+    const int v0 = blockIdx.x * kNearRows, u0 = blockIdx.y * part;
+    gw_near_rows(X, valid, v0, min(kNearRows, rows - v0), u0, min(n, u0 + part), r_steer, r_conn, gw, s);
 }
 
 __global__ __launch_bounds__(256) void k_gw_near_col0(const float* __restrict__ X,
@@ -145,8 +146,9 @@ __global__ __launch_bounds__(256) void k_gw_exact(const float* __restrict__ X,
                                                   const int32_t* __restrict__ rm_dst,
                                                   const double* __restrict__ rm_tau,
                                                   uint32_t* __restrict__ ebits, int words) {
+    __shared__ ExactWaveLds s[4];
     gw_exact(X, obs, gw, rm_src, rm_dst, rm_tau, ebits, words, blockIdx.x * blockDim.x + threadIdx.x,
-             gridDim.x * blockDim.x);
+             gridDim.x * blockDim.x, s);
 }
 
 __global__ __launch_bounds__(256) void k_row_deg(const uint32_t* __restrict__ ebits, int n_nodes,
@@ -199,7 +201,8 @@ void launch_graph_mark(hipStream_t s, const float* X, const uint8_t* valid, int 
                        const float* obs, int n_obs, const uint32_t* bins, double r_steer, double r_conn,
                        uint32_t* ebits, int32_t* deg, int words, const GraphWork& gw) {
     (void)hipMemsetAsync(ebits, 0, (size_t)n_nodes * words * sizeof(uint32_t), s);
-    k_gw_near_rows<<<n_nodes, kNearThreads, 0, s>>>(X, valid, n_nodes, 0, r_steer, r_conn, gw);
+    k_gw_near_rows<<<(n_nodes + kNearRows - 1) / kNearRows, kNearThreads, 0, s>>>(X, valid, n_nodes, n_nodes,
+                                                                          n_nodes, r_steer, r_conn, gw);
     k_gw_boxes<<<kStageBlocks, kBoxThreads, gw_boxes_lds(n_obs), s>>>(X, valid, gw.near_src, gw.near_dst, gw.near_tau,
                                             nullptr, 0, 1, obs, n_obs, bins, gw, ebits, words);
     k_gw_exact<<<kStageBlocks, 256, 0, s>>>(X, obs, gw, nullptr, nullptr, nullptr, ebits, words);
@@ -213,7 +216,10 @@ void launch_graph_pass1_roadmap(hipStream_t s, const float* X, const uint8_t* va
                                 uint32_t* ebits, int32_t* deg, int words, const GraphWork& gw) {
     (void)hipMemsetAsync(ebits, 0, (size_t)n_nodes * words * sizeof(uint32_t), s);
     // the pairs at node 0: its row, then its column
-    k_gw_near_rows<<<1, kNearThreads, 0, s>>>(X, valid, n_nodes, 0, r_steer, r_conn, gw);
+    // (a chunk of the row's targets to a workgroup: with one for the whole row
+    // it took 154 us at 11,111 samples)
+    k_gw_near_rows<<<dim3(1, (n_nodes + kNearChunk - 1) / kNearChunk), kNearThreads, 0, s>>>(
+        X, valid, n_nodes, 1, kNearChunk, r_steer, r_conn, gw);
     const int col = n_nodes - 1;
     k_gw_near_col0<<<(col + 255) / 256 > 0 ? (col + 255) / 256 : 1, 256, 0, s>>>(
         X, valid, n_nodes, r_steer, r_conn, gw);

@@ -286,26 +286,40 @@ __device__ __forceinline__ void mark_valid_dev(const float* __restrict__ X, int 
 //
 // Pass 1 runs as stages, each its own kernel so that the register-heavy
 // exact box test does not hold down the occupancy of the others:
-//   near    one workgroup per row: every target through the exact Near
-//           rejection test into an LDS list, then the survivors steered
-//           densely (tau*, c*); near connections -> the near list;
-//   boxes   per near connection, its nominal position range against every
-//           box and, where they meet, the quick trajectory-box test; a hit
-//           blocks it, an unsure case goes to the exact queue; connections
-//           not blocked set their bit;
-//   exact   per queued (connection, box), one wave: the piecewise test with
-//           64 pieces across the lanes and, if still unsure, the exact
-//           trajectory-box test; a hit clears the bit;
+//   near    a workgroup per kNearRows rows: every target through the Near
+//           rejection test, the survivors steered densely (tau*, c*); near
+//           connections -> the near list;
+//   boxes   each near connection's pieces against the boxes in their bins; a
+//           proved hit blocks it, an unsure (connection, box) goes to the exact
+//           queue; connections not blocked set their bit;
+//   exact   the queued (connection, box) pairs in ever finer parts and, those
+//           still unsure, the exact trajectory-box test; a hit clears the bit;
 //   degree  popcount of each row.
 // A connection's bit ends set iff no box blocks it, the decision of the exact
 // test on every box its range meets.
 // ---------------------------------------------------------------------------
-constexpr int kNearChunk = 4096;   // targets per LDS survivor list
-// workgroup of the near stage: 256 threads let five workgroups share a CU
-// (registers and the 32 KB of lists); on the 20,000-sample indoor query this
-// measured faster than 128, 512 or 1024 threads and than 2048- or
-// 8192-target chunks
-constexpr int kNearThreads = 256;
+constexpr int kNearRows = 4;        // rows a workgroup takes together, one a wave in pass 2
+constexpr int kNearThreads = 64 * kNearRows;
+constexpr int kNearChunk = 1024;    // targets between two passes
+constexpr int kNearKeep = 1536;     // pairs from which they are steered
+
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// A value all lanes hold, in scalar registers (loads through a query's record
+// are not known to be uniform).
+template <typename T>
+__device__ __forceinline__ T uniform(T v) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
 
 // Append `ok` items of a wave to a list: one atomic per wave (all 64 lanes
 // call it).  Returns the slot of this lane's item.
@@ -356,70 +370,125 @@ __device__ __forceinline__ void gw_push_near_block(const GraphWork& gw, bool ok,
     __syncthreads();   // s_w is reused
 }
 
-// near: row v (whole workgroup, blockDim a multiple of 64, at most 1024;
-// s_list holds 2 * kNearChunk ints, s_cnt 3 + 17).  Per chunk of targets,
-// three passes, each over a list compacted by the one before it so that no
-// wave carries lanes the pass has no work for (a few per cent of the targets
-// pass the FP32 bound, so a wave of 64 targets taken in place would nearly
-// always run the FP64 test, and the root solve, for one or two lanes):
-//   1. the FP32 first look at the Bernstein bound over every target;
-//   2. the FP64 rejection test over the targets it could not settle;
-//   3. the root solve (tau*, c*) over the targets that test keeps, those
-//      whose solve takes steer64's one-root branch listed first and the
-//      others from the end of the list, so that a wave runs one branch.
-__device__ __forceinline__ void gw_near_row(const float* __restrict__ X,
-                                            const uint8_t* __restrict__ valid, int n, int v,
-                                            double r_steer, double r_conn, const GraphWork& gw,
-                                            int* s_list, int* s_cnt) {
-    if (!valid[v]) return;
-    int* s_l1 = s_list;                 // pass 1 -> 2
-    int* s_l2 = s_list + kNearChunk;    // pass 2 -> 3
-    float xv[6];
-    for (int k = 0; k < 6; ++k) xv[k] = X[(size_t)v * 6 + k];
-    const float r32 = (float)r_steer, R32 = (float)r_conn;
-    for (int c0 = 0; c0 < n; c0 += kNearChunk) {
-        if (threadIdx.x == 0) {
-            s_cnt[0] = 0;
-            s_cnt[1] = 0;
-            s_cnt[2] = 0;
+// near: rows v0 .. v0 + rows - 1 (at most kNearRows) against targets u0 .. u1 - 1
+// (whole workgroup).  Three passes, each over what the one before it leaves, so
+// that no wave carries lanes the pass has no work for:
+//   1. the first look at the Bernstein bound, a lane per target for all rows:
+//      the target is loaded once, and its outcome is a bit of a ballot;
+//   2. a wave per row, over the row's bits: the split bound;
+//   3. the root solve (tau*, c*) over the pairs that keeps, of all rows, those
+//      whose solve likely takes steer64's one-root branch from the front of the
+//      list and the others from its end, each in waves of their own.
+// It is bound by its instructions: of the 20,000-sample indoor query's pairs 18 %
+// pass the first look and 5 % are steered, some 900 instructions each.  A row
+// at a time, with FP64 for pass 2 and a list written from pass 1, it took 2.45
+// ms; now 1.39 (64 uneven queries: 10.5 and 5.5).
+struct NearLds {
+    unsigned long long mask[kNearRows][kNearChunk / 64];
+    uint16_t open[kNearRows][kNearChunk];                    // pass 1 -> 2
+    uint32_t keep[kNearKeep + kNearRows * kNearChunk];       // pass 2 -> 3: row << 30 | target
+    int n_one, n_many;
+    int slots[kNearRows + 1];
+};
+
+__device__ __forceinline__ void near_steer(const float* __restrict__ X, int v0, double r_steer, double r_conn,
+                                           const GraphWork& gw, NearLds& s) {
+    constexpr int kCap = kNearKeep + kNearRows * kNearChunk;
+    const int n_one = s.n_one, n_many = s.n_many;
+    const int first_many = (n_one + 63) & ~63, end = first_many + n_many;
+    for (int base = 0; base < end; base += kNearThreads) {
+        const int i = base + threadIdx.x;
+        const int at = i < n_one ? i : (i >= first_many && i < end ? kCap - 1 - (i - first_many) : -1);
+        bool ok = false;
+        int u = 0, v = 0;
+        double tau = 0.0;
+        if (at >= 0) {
+            const uint32_t e = s.keep[at];
+            u = (int)(e & 0x3fffffffu);
+            v = v0 + (int)(e >> 30);
+            double c;
+            steer64(X + (size_t)v * 6, X + (size_t)u * 6, r_steer, tau, c);
+            ok = c < r_conn && tau > kTauMin;
+        }
+        gw_push_near_block(gw, ok, v, u, tau, s.slots);
+    }
+}
+
+__device__ __forceinline__ void gw_near_rows(const float* __restrict__ X,
+                                             const uint8_t* __restrict__ valid, int v0, int rows, int u0,
+                                             int u1, double r_steer, double r_conn, const GraphWork& gw,
+                                             NearLds& s) {
+    constexpr int kCap = kNearKeep + kNearRows * kNearChunk;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const Near32 k = near32((float)r_steer, (float)r_conn);
+    float xv[kNearRows][6];
+    bool on[kNearRows];
+#pragma unroll
+    for (int r = 0; r < kNearRows; ++r) {
+        const int v = v0 + min(r, rows - 1);
+        on[r] = r < rows && valid[v];
+        for (int e = 0; e < 6; ++e) xv[r][e] = uniform(X[(size_t)v * 6 + e]);
+    }
+    const float* xw = X + (size_t)(v0 + min(wave, rows - 1)) * 6;   // this wave's row
+    if (threadIdx.x == 0) s.n_one = s.n_many = 0;
+    for (int c0 = u0; c0 < u1; c0 += kNearChunk) {
+#pragma unroll 1
+        for (int j = wave; j < kNearChunk / 64; j += kNearRows) {
+            const int u = c0 + 64 * j + lane;
+            const bool there = u < u1 && valid[min(u, u1 - 1)];
+            const float2* xu2 = reinterpret_cast<const float2*>(X + (size_t)min(u, u1 - 1) * 6);
+            const float2 p01 = xu2[0], p2v0 = xu2[1], v12 = xu2[2];
+            const float xu[6] = {p01.x, p01.y, p2v0.x, p2v0.y, v12.x, v12.y};
+#pragma unroll
+            for (int r = 0; r < kNearRows; ++r) {
+                float b[5], m;
+                const bool open = !near_bern32(k, near_sums32(xv[r], xu), b, m);
+                const unsigned long long bits = __ballot(open && there && u != v0 + r);
+                if (lane == r) s.mask[r][j] = on[r] ? bits : 0ull;
+            }
         }
         __syncthreads();
-        for (int u = c0 + threadIdx.x; u < c0 + kNearChunk && u < n; u += blockDim.x) {
-            if (u == v || !valid[u]) continue;
+        // this wave's row: its open targets side by side, then their split bound
+        int n_open = 0;
+        {
+            uint32_t bits = (uint32_t)(s.mask[wave][lane >> 2] >> (16 * (lane & 3))) & 0xffffu;
+            const int mine = __popc(bits);
+            int x = mine;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(x, o, 64);
+                if (lane >= o) x += y;
+            }
+            n_open = __shfl(x, 63, 64);
+            int at = x - mine;
+            while (bits) {
+                s.open[wave][at++] = (uint16_t)(16 * lane + __ffs((int)bits) - 1);
+                bits &= bits - 1u;
+            }
+            wave_lds_sync();
+        }
+        for (int i = lane; i < n_open; i += 64) {
+            const int u = c0 + s.open[wave][i];
             const float2* xu2 = reinterpret_cast<const float2*>(X + (size_t)u * 6);
             const float2 p01 = xu2[0], p2v0 = xu2[1], v12 = xu2[2];
             const float xu[6] = {p01.x, p01.y, p2v0.x, p2v0.y, v12.x, v12.y};
-            if (!surely_not_near32(xv, xu, r32, R32)) s_l1[atomicAdd(&s_cnt[0], 1)] = u;
-        }
-        __syncthreads();
-        const int cnt1 = s_cnt[0];
-        for (int i = threadIdx.x; i < cnt1; i += blockDim.x) {
-            const int u = s_l1[i];
-            const BSums bs = boundary_sums(xv, X + (size_t)u * 6);
-            if (!surely_not_near(bs, r_steer, r_conn)) {
-                if (steer_one_root(bs, r_steer))
-                    s_l2[atomicAdd(&s_cnt[1], 1)] = u;
+            const Sums32 sm = near_sums32(xw, xu);
+            float b[5], m;
+            near_bern32(k, sm, b, m);
+            if (!near_split32(b, m)) {
+                const uint32_t e = (uint32_t)wave << 30 | (uint32_t)u;
+                if (likely_one_root(sm, (float)r_steer))
+                    s.keep[atomicAdd(&s.n_one, 1)] = e;
                 else
-                    s_l2[kNearChunk - 1 - atomicAdd(&s_cnt[2], 1)] = u;
+                    s.keep[kCap - 1 - atomicAdd(&s.n_many, 1)] = e;
             }
         }
         __syncthreads();
-        const int n_one = s_cnt[1], n_many = s_cnt[2];
-        const int cnt2 = n_one + n_many;
-        for (int base = 0; base < cnt2; base += blockDim.x) {
-            const int i = base + threadIdx.x;
-            bool ok = false;
-            int u = 0;
-            double tau = 0.0;
-            if (i < cnt2) {
-                u = s_l2[i < n_one ? i : kNearChunk - n_many + (i - n_one)];
-                double c;
-                steer64(xv, X + (size_t)u * 6, r_steer, tau, c);
-                ok = c < r_conn && tau > kTauMin;
-            }
-            gw_push_near_block(gw, ok, v, u, tau, s_cnt + 3);
+        if (s.n_one + s.n_many > kNearKeep || c0 + kNearChunk >= u1) {
+            near_steer(X, v0, r_steer, r_conn, gw, s);
+            __syncthreads();
+            if (threadIdx.x == 0) s.n_one = s.n_many = 0;
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -432,8 +501,7 @@ __device__ __forceinline__ void gw_near_col0(const float* __restrict__ X,
     bool ok = false;
     double tau = 0.0;
     if (src < n && valid[0] && valid[src] &&
-        !surely_not_near32(X + (size_t)src * 6, X, (float)r_steer, (float)r_conn) &&
-        !surely_not_near(boundary_sums(X + (size_t)src * 6, X), r_steer, r_conn)) {
+        !surely_not_near(X + (size_t)src * 6, X, (float)r_steer, (float)r_conn)) {
         double c;
         steer64(X + (size_t)src * 6, X, r_steer, tau, c);
         ok = c < r_conn && tau > kTauMin;
@@ -467,7 +535,8 @@ __device__ __forceinline__ void gw_near_col0(const float* __restrict__ X,
 // (20.3 million connections, 6 in 10 blocked, 1.4 entries of queue 1 and 0.3 of
 // queue 2 each) took 3.53 ms in this kernel with a lane per connection for all
 // of it (29 % of the lanes with work) and a step of the exact list's counter for
-// each connection's boxes; now it takes 1.29.
+// each connection's boxes; now it takes 1.38 (1.29 while its list came a row at a
+// time from the near stage).
 constexpr int kBoxThreads = 256;
 constexpr int kBoxWaves = kBoxThreads / 64;
 constexpr int kPieces = 8;
@@ -487,11 +556,6 @@ struct BoxWaveLds {
 __host__ __device__ inline size_t gw_boxes_lds(int n_obs) {
     return sizeof(BoxWaveLds) * kBoxWaves + (size_t)kBoxThreads * ((n_obs + 63) / 64) * 8 +
            (size_t)(bin_words(n_obs) - kBinHeader) * 4 + (size_t)n_obs * 48;
-}
-
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
 }
 
 struct BoxStage {
@@ -812,59 +876,182 @@ __device__ __forceinline__ void gw_boxes(const float* __restrict__ X,
     if (g.nx) box_exact_flush(g, gw);
 }
 
-// exact: queued (connection, box) pairs; a hit clears the connection's bit
+// exact: queued (connection, box) pairs; a hit clears the connection's bit.
+// A wave takes up to 64 pairs and refines them over its lanes: the 8 pieces of 8
+// pairs at a time; 8 parts of each piece that met the box (through a queue), and
+// 4 of each part; a sample point inside the box proves a hit.  Pairs that stay
+// open -- a graze, mostly -- are solved for the slab crossings, a lane for each
+// axis and monotone piece.  With a wave per pair, its 64 parts on the lanes and
+// the crossings solved by all lanes alike, the 20,000-sample indoor query took
+// 0.40 ms here, 64 uneven queries 1.64; now 0.12 and 0.36.
+struct ExactWaveLds {
+    double c23[6][64], tau[64];
+    float c01[6][64], box[6][64];
+    uint16_t q1[kBoxQueue], q2[kBoxQueue];   // pair | part << 6
+    int state[64];                           // 1 hit, 2 open
+    int solve[kBoxQueue];                    // pairs for the crossings
+};
+
+// Part idx of `parts` of pair c: 0 clear, 1 hit, 2 open.
+__device__ __forceinline__ int exact_part(const ExactWaveLds& l, int c, int idx, int parts) {
+    const double tau = l.tau[c], inv = 1.0 / (double)parts;
+    const double h3 = (inv * tau) * (1.0 / 3.0);
+    const double ta = tau * (inv * (double)idx);
+    const double tb = idx + 1 == parts ? tau : tau * (inv * (double)(idx + 1));
+    bool sep = false, inside = idx + 1 < parts;
+#pragma unroll 1
+    for (int a = 0; a < 3; ++a) {
+        const Cubic q{(double)l.c01[2 * a][c], (double)l.c01[2 * a + 1][c], l.c23[2 * a][c], l.c23[2 * a + 1][c]};
+        const double pa = q.at(ta), pb = q.at(tb);
+        const double b1 = pa + h3 * q.slope(ta), b2 = pb - h3 * q.slope(tb);
+        const double lo = fmin(fmin(pa, pb), fmin(b1, b2)) - kHullMargin;
+        const double hi = fmax(fmax(pa, pb), fmax(b1, b2)) + kHullMargin;
+        const double blo = (double)l.box[a][c], bhi = (double)l.box[3 + a][c];
+        sep |= (hi < blo) | (lo > bhi);
+        inside &= (pb >= blo) & (pb <= bhi);
+    }
+    return inside ? 1 : (sep ? 0 : 2);
+}
+
 __device__ __forceinline__ void gw_exact(const float* __restrict__ X, const float* __restrict__ obs,
                                          const GraphWork& gw, const int32_t* __restrict__ rm_src,
                                          const int32_t* __restrict__ rm_dst,
                                          const double* __restrict__ rm_tau,
                                          uint32_t* __restrict__ ebits, int words, int gid,
-                                         int stride) {
-    // One wave per queued (connection, box); lane k takes piece k of 64 (its
-    // hull, then its quarters', as the box stage does with 8 pieces), and only if no piece proves a hit and some piece stays unsure does the wave
-    // solve for the slab crossings (all lanes in step on the same inputs).
-    constexpr int kPieces = 64;
+                                         int stride, ExactWaveLds* lds) {
     const int lane = threadIdx.x & 63;
+    ExactWaveLds& l = lds[threadIdx.x >> 6];
     const int N = min(gw.counts[1], gw.xq_cap);
-    for (int i = gid >> 6; i < N; i += stride >> 6) {
+    // pairs a wave: 64 where there are enough of them, else enough waves
+    const int waves = stride >> 6;
+    const int group = min(64, ((N + waves - 1) / waves + 7) & ~7);
+    auto ends = [&](int i, int& src, int& dst, double& tau) {
         const int tag = gw.xq_edge[i];
-        int src, dst;
-        double tau;
         if (tag >= 0) {
             src = rm_src[tag]; dst = rm_dst[tag]; tau = rm_tau[tag];
         } else {
             src = gw.near_src[-1 - tag]; dst = gw.near_dst[-1 - tag]; tau = gw.near_tau[-1 - tag];
         }
-        Cubic cs[3];
-        hermite(X + (size_t)src * 6, X + (size_t)dst * 6, tau, cs);
-        const float* box = obs + (size_t)gw.xq_box[i] * 6;
-        const double inv = 1.0 / (double)kPieces;
-        const double h = inv * tau;
-        const double h3 = h * (1.0 / 3.0), q3 = 0.25 * h3;
-        const double ta = tau * (inv * (double)lane);
-        const double tb = lane == kPieces - 1 ? tau : tau * (inv * (double)(lane + 1));
-        double pa[3], da[3], pb[3], db[3];
-        eval_pd(cs, ta, pa, da);
-        eval_pd(cs, tb, pb, db);
-        bool hit = lane < kPieces - 1 && point_in_box(pb, box);
-        bool unsure = false;
-        if (!hit && !piece_clear(pa, da, pb, db, h3, box)) {
-            double qa[3] = {pa[0], pa[1], pa[2]}, qd[3] = {da[0], da[1], da[2]};
-            for (int j = 1; j <= 4 && !hit; ++j) {
-                double qb[3], qe[3];
-                if (j == 4) {
-                    for (int a = 0; a < 3; ++a) { qb[a] = pb[a]; qe[a] = db[a]; }
-                } else {
-                    eval_pd(cs, ta + 0.25 * (double)j * h, qb, qe);
-                    hit = point_in_box(qb, box);
-                }
-                unsure |= !piece_clear(qa, qd, qb, qe, q3, box);
-                for (int a = 0; a < 3; ++a) { qa[a] = qb[a]; qd[a] = qe[a]; }
-            }
+    };
+    auto clear = [&](int src, int dst) {
+        atomicAnd(&ebits[(size_t)src * words + (dst >> 5)], ~(1u << (dst & 31)));
+    };
+    int n_solve = 0;
+    // the last (at most 4), 16 lanes each: lane 3 a + k of a pair finds the time
+    // in the slab of axis a on its monotone piece k; three of them, one an axis,
+    // that share a time are a hit
+    auto solve = [&]() {
+        wave_lds_sync();
+        const int n = min(n_solve, 4), who = lane >> 4, sub = lane & 15, first = lane & 48;
+        n_solve -= n;
+        double in = INFINITY, out = -INFINITY;
+        int src = 0, dst = 0;
+        if (who < n && sub < 9) {
+            const int i = l.solve[n_solve + who];
+            double tau;
+            ends(i, src, dst, tau);
+            const int a = sub / 3;
+            const float* x0 = X + (size_t)src * 6 + a;
+            const float* x1 = X + (size_t)dst * 6 + a;
+            const float* bx = obs + (size_t)gw.xq_box[i] * 6 + a;
+            const Cubic c = hermite_axis(x0[0], x0[3], x1[0], x1[3], tau, 1.0 / tau);
+            slab_piece(c, tau, (double)bx[0], (double)bx[3], sub - 3 * a, in, out);
         }
-        bool blocked = __ballot(hit) != 0ull;
-        if (!blocked && __ballot(unsure) != 0ull) blocked = trajectory_hits_box_exact(cs, tau, box);
-        if (blocked && lane == 0)
-            atomicAnd(&ebits[(size_t)src * words + (dst >> 5)], ~(1u << (dst & 31)));
+        const int ja = first + sub / 3, jb = first + 3 + sub % 3;
+        const double st = fmax(__shfl(in, ja, 64), __shfl(in, jb, 64));
+        const double en = fmin(__shfl(out, ja, 64), __shfl(out, jb, 64));
+        bool hit = false;
+        for (int k = 0; k < 3; ++k) {
+            const double s2 = __shfl(in, first + 6 + k, 64), e2 = __shfl(out, first + 6 + k, 64);
+            hit |= fmax(st, s2) <= fmin(en, e2);
+        }
+        const unsigned long long hits = __ballot(hit && sub < 9) >> first & 0xffffull;
+        if (who < n && sub == 0 && hits) clear(src, dst);
+        wave_lds_sync();
+    };
+    for (int base = (gid >> 6) * group; base < N; base += waves * group) {
+        const int n = min(group, N - base);
+        const bool last = base + waves * group >= N;
+        int src = 0, dst = 0;
+        if (lane < n) {
+            double tau;
+            ends(base + lane, src, dst, tau);
+            Cubic cs[3];
+            hermite(X + (size_t)src * 6, X + (size_t)dst * 6, tau, cs);
+            const float* bx = obs + (size_t)gw.xq_box[base + lane] * 6;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                l.c01[2 * a][lane] = (float)cs[a].c0;
+                l.c01[2 * a + 1][lane] = (float)cs[a].c1;
+                l.c23[2 * a][lane] = cs[a].c2;
+                l.c23[2 * a + 1][lane] = cs[a].c3;
+                l.box[a][lane] = bx[a];
+                l.box[3 + a][lane] = bx[3 + a];
+            }
+            l.tau[lane] = tau;
+            l.state[lane] = 0;
+        }
+        wave_lds_sync();
+        int n1 = 0, n2 = 0;
+        auto quarters = [&]() {   // the last (at most 16) of q2, 4 lanes each
+            wave_lds_sync();
+            const int m = min(n2, 16);
+            n2 -= m;
+            if ((lane >> 2) < m) {
+                const int e = l.q2[n2 + (lane >> 2)], c = e & 63;
+                if (l.state[c] != 1) {
+                    const int r = exact_part(l, c, 4 * (e >> 6) + (lane & 3), 256);
+                    if (r == 1) atomicExch(&l.state[c], 1);
+                    if (r == 2) atomicCAS(&l.state[c], 0, 2);
+                }
+            }
+            wave_lds_sync();
+        };
+        auto eighths = [&]() {    // the last (at most 8) of q1, 8 lanes each
+            wave_lds_sync();
+            const int m = min(n1, 8);
+            n1 -= m;
+            bool open = false;
+            int c = 0, idx = 0;
+            if ((lane >> 3) < m) {
+                const int e = l.q1[n1 + (lane >> 3)];
+                c = e & 63;
+                idx = 8 * (e >> 6) + (lane & 7);
+                if (l.state[c] != 1) {
+                    const int r = exact_part(l, c, idx, 64);
+                    if (r == 1) l.state[c] = 1;
+                    open = r == 2;
+                }
+            }
+            const int at = n2 + wave_rank(open);
+            if (open) l.q2[at] = (uint16_t)(c | idx << 6);
+            n2 += (int)__popcll(__ballot(open));
+            while (n2 >= 64) quarters();
+            wave_lds_sync();
+        };
+        for (int b0 = 0; b0 < n; b0 += 8) {
+            const int c = b0 + (lane >> 3), idx = lane & 7;
+            bool open = false;
+            if (c < n) {
+                const int r = exact_part(l, c, idx, 8);
+                if (r == 1) l.state[c] = 1;
+                open = r == 2;
+            }
+            const int at = n1 + wave_rank(open);
+            if (open) l.q1[at] = (uint16_t)(c | idx << 6);
+            n1 += (int)__popcll(__ballot(open));
+            while (n1 >= 64) eighths();
+        }
+        while (n1 > 0) eighths();
+        while (n2 > 0) quarters();
+        wave_lds_sync();
+        const int st = lane < n ? l.state[lane] : 0;
+        if (st == 1) clear(src, dst);
+        const int at = n_solve + wave_rank(st == 2);
+        if (st == 2) l.solve[at] = base + lane;
+        n_solve += (int)__popcll(__ballot(st == 2));
+        while (n_solve >= (last ? 1 : 4)) solve();
+        wave_lds_sync();
     }
 }
 
