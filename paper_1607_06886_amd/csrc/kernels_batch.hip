@@ -17,9 +17,10 @@ namespace pump {
 // Pareto-front entries kept per query: as many as the single-query path
 // keeps, so a batched query's result is the one pump_plan returns; the
 // certification grid has kBatchMcRows rows of front plans and strides over
-// larger fronts.
+// larger fronts (64 uneven queries: 4 rows 1.07 ms, 2 rows 0.94).
 constexpr int kBatchFront = kMaxFront;
-constexpr int kBatchMcRows = 32;
+constexpr int kBatchMcRows = 2;
+constexpr int kBatchSmoothRows = 1;   // of the smoothing's candidates
 
 // ----------------------------- setup ---------------------------------------
 __global__ void k_b_load(BatchQuery* qs) {
@@ -333,18 +334,10 @@ __global__ void k_b_waypoints(BatchQuery* qs) {
 }
 
 __global__ __launch_bounds__(kMcThreads) void k_b_mc(BatchQuery* qs) {
-    __shared__ float s_obs[kMaxObs * 6];
-    __shared__ int s_hit[kMcParticles];
+    __shared__ McLds l;
     const BatchQuery& Q = qs[blockIdx.z];
     if (Q.bad || Q.ra[0].ctl->err || (int)blockIdx.y >= Q.ra[0].ctl->n_front) return;   // uniform per block
-    const int nf = Q.ra[0].ctl->n_front;
-    for (int t = threadIdx.x; t < Q.s.n_obs * 6; t += blockDim.x) s_obs[t] = Q.s.obs[t];
-    __syncthreads();
-    for (int f = blockIdx.y; f < nf; f += gridDim.y) {   // trip count uniform per block
-        mc_block_count(Q.s, Q.s.wp + (size_t)f * (Q.s.S_max + 1) * 3, Q.s.wp_len[f],
-                       blockIdx.x * kMcParticles, s_obs, s_hit, &Q.s.mc_counts[f]);
-        __syncthreads();   // the next plan's clear of s_hit waits for this plan's ballot
-    }
+    mc_front(Q.s, blockIdx.x * kMcParticles, Q.ra[0].ctl->n_front, blockIdx.y, gridDim.y, l);
 }
 
 // Alg. 5 bisection on the certified counts, and the per-query outcome.
@@ -419,15 +412,9 @@ __global__ __launch_bounds__(256) void k_b_smooth_wp(BatchQuery* qs, int r) {
 }
 
 __global__ __launch_bounds__(kMcThreads) void k_b_smooth_mc(BatchQuery* qs, int r) {
-    __shared__ float s_obs[kMaxObs * 6];
-    __shared__ int s_hit[kMcParticles];
+    __shared__ McLds l;
     const BatchQuery& Q = qs[blockIdx.z];
-    const int c = blockIdx.y;
-    if (smooth_beta(*Q.sm.st, r, c) < 0.0 || Q.sm.st->K[c] < 0) return;   // uniform per block
-    for (int t = threadIdx.x; t < Q.s.n_obs * 6; t += blockDim.x) s_obs[t] = Q.s.obs[t];
-    __syncthreads();
-    mc_block_count(Q.s, Q.sm.wp + (size_t)c * (Q.s.S_max + 1) * 3, Q.sm.st->K[c],
-                   blockIdx.x * kMcParticles, s_obs, s_hit, &Q.sm.st->cnt[c]);
+    smooth_mc(Q.s, Q.sm, r, blockIdx.x * kMcParticles, blockIdx.y, gridDim.y, l);
 }
 
 __global__ void k_b_smooth_resolve(BatchQuery* qs, int q, int r) {
@@ -522,7 +509,7 @@ void launch_batch(hipStream_t s, BatchQuery* qs, int q, int N_max, int max_nodes
         k_b_smooth_prep<<<q, 256, 0, s>>>(qs, out);
         for (int r = 0; r < kSmoothRounds; ++r) {
             k_b_smooth_wp<<<dim3((S_max + 1 + 255) / 256, kSmoothCands, q), 256, 0, s>>>(qs, r);
-            k_b_smooth_mc<<<dim3((M + kMcParticles - 1) / kMcParticles, kSmoothCands, q), kMcThreads,
+            k_b_smooth_mc<<<dim3((M + kMcParticles - 1) / kMcParticles, kBatchSmoothRows, q), kMcThreads,
                             0, s>>>(qs, r);
             k_b_smooth_resolve<<<(q + 63) / 64, 64, 0, s>>>(qs, q, r);
         }

@@ -69,27 +69,22 @@ void launch_waypoints(hipStream_t s, const SelectArgs& a, int32_t n_paths) {
     k_waypoints<<<n, 64, 0, s>>>(a, n_paths);
 }
 
-// Rows of the MC grid when the front size is read on the device: each row
-// of workgroups takes front plans blockIdx.y, + kMcRows, ...
-constexpr int kMcRows = 16;
+// Rows of the MC grid: a workgroup takes front plans blockIdx.y, + gridDim.y,
+// ...; the deviations of a workgroup serve all of its plans, and too few workgroups
+// leave CUs idle.  Measured with 16, 8 and 4 rows: 66, 63 and 50 us on the
+// 20,000-sample indoor query, 25 to 24 on smaller fronts.
+constexpr int kMcRows = 4;
 
 __global__ __launch_bounds__(kMcThreads) void k_mc(SelectArgs a, int n_paths) {
-    __shared__ float s_obs[kMaxObs * 6];
-    __shared__ int s_hit[kMcParticles];
+    __shared__ McLds l;
     const int n = n_paths < 0 ? a.ctl->n_front : n_paths;
     if ((int)blockIdx.y >= n) return;   // uniform per workgroup
-    for (int t = threadIdx.x; t < a.n_obs * 6; t += blockDim.x) s_obs[t] = a.obs[t];
-    __syncthreads();
-    for (int f = blockIdx.y; f < n; f += gridDim.y) {
-        mc_block_count(a, a.wp + (size_t)f * (a.S_max + 1) * 3, a.wp_len[f],
-                       blockIdx.x * kMcParticles, s_obs, s_hit, &a.mc_counts[f]);
-        __syncthreads();   // s_hit is reused by the next plan
-    }
+    mc_front(a, blockIdx.x * kMcParticles, n, blockIdx.y, gridDim.y, l);
 }
 
 void launch_mc(hipStream_t s, const SelectArgs& a, int32_t n_paths) {
     if (n_paths == 0) return;
-    const int rows = n_paths < 0 ? kMcRows : n_paths;
+    const int rows = n_paths < 0 || n_paths > kMcRows ? kMcRows : n_paths;
     dim3 grid((a.M + kMcParticles - 1) / kMcParticles, rows);
     k_mc<<<grid, kMcThreads, 0, s>>>(a, n_paths);
 }
@@ -147,15 +142,13 @@ __global__ __launch_bounds__(256) void k_smooth_wp(SelectArgs a, SmoothBuf b, in
     smooth_wp_one(a, b, r, blockIdx.y, blockIdx.x * blockDim.x + threadIdx.x);
 }
 
+// Rows of the smoothing's MC grid (8, 4 and 2: 82, 54 and 62 us a round of the
+// LQG query).
+constexpr int kSmoothMcRows = 4;
+
 __global__ __launch_bounds__(kMcThreads) void k_smooth_mc(SelectArgs a, SmoothBuf b, int r) {
-    __shared__ float s_obs[kMaxObs * 6];
-    __shared__ int s_hit[kMcParticles];
-    const int c = blockIdx.y;
-    if (smooth_beta(*b.st, r, c) < 0.0 || b.st->K[c] < 0) return;   // uniform per block
-    for (int t = threadIdx.x; t < a.n_obs * 6; t += blockDim.x) s_obs[t] = a.obs[t];
-    __syncthreads();
-    mc_block_count(a, b.wp + (size_t)c * (a.S_max + 1) * 3, b.st->K[c], blockIdx.x * kMcParticles,
-                   s_obs, s_hit, &b.st->cnt[c]);
+    __shared__ McLds l;
+    smooth_mc(a, b, r, blockIdx.x * kMcParticles, blockIdx.y, gridDim.y, l);
 }
 
 __global__ void k_smooth_resolve(SelectArgs a, SmoothBuf b, double alpha, int r) {
@@ -172,7 +165,7 @@ void launch_smooth(hipStream_t s, const SelectArgs& a, const SmoothBuf& b, int f
     k_smooth_prep<<<1, 256, 0, s>>>(a, b, f_best, plan_cost);
     for (int r = 0; r < kSmoothRounds; ++r) {
         k_smooth_wp<<<dim3((a.S_max + 1 + 255) / 256, kSmoothCands), 256, 0, s>>>(a, b, r);
-        k_smooth_mc<<<dim3((a.M + kMcParticles - 1) / kMcParticles, kSmoothCands), kMcThreads, 0,
+        k_smooth_mc<<<dim3((a.M + kMcParticles - 1) / kMcParticles, kSmoothMcRows), kMcThreads, 0,
                       s>>>(a, b, r);
         k_smooth_resolve<<<1, 64, 0, s>>>(a, b, alpha, r);
     }

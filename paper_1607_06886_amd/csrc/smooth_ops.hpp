@@ -136,6 +136,26 @@ __device__ __forceinline__ void smooth_wp_one(const SelectArgs& a, const SmoothB
     o[0] = p[0]; o[1] = p[1]; o[2] = p[2];
 }
 
+// Collisions of round r's candidates row, row + rows, ... (one workgroup of
+// kMcThreads, 64 particles).
+__device__ __forceinline__ void smooth_mc(const SelectArgs& a, const SmoothBuf& b, int r, int m_base, int row,
+                                          int rows, McLds& l) {
+    static_assert(kSmoothCands <= kMcPlans, "a row's candidates in one pass");
+    auto len_of = [&](int i) {
+        const int c = row + i * rows;
+        return smooth_beta(*b.st, r, c) < 0.0 ? -1 : b.st->K[c];
+    };
+    const int n_p = (kSmoothCands - row + rows - 1) / rows;
+    bool any = false;
+    for (int i = 0; i < n_p; ++i) any |= len_of(i) >= 0;
+    if (!any) return;   // uniform per workgroup
+    for (int t = threadIdx.x; t < a.n_obs * 6; t += kMcThreads) l.obs[t] = a.obs[t];
+    __syncthreads();
+    mc_plans(
+        a, m_base, n_p, [&](int i) { return b.wp + (size_t)(row + i * rows) * (a.S_max + 1) * 3; }, len_of,
+        [&](int i) { return &b.st->cnt[row + i * rows]; }, l);
+}
+
 // Replay of round r's three bisection levels (one thread).
 __device__ __forceinline__ void smooth_resolve_one(const SelectArgs& a, double alpha,
                                                    const SmoothBuf& b, int r) {
