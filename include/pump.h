@@ -318,7 +318,7 @@ int pump_sample_halton(int32_t n, int32_t n_goal, const float* lo, const float* 
  * bracketed by HIP events on the context's stream and the elapsed times are
  * accumulated per kind:
  *   0 deviation table   1 graph pass 1 (all pairs)   2 graph pass 2 (fill)
- *   3 expand, pair stage (per-phase mode, half-space model)
+ *   3 expand, headers (per-phase mode, half-space model)
  *   4 prune (staircase update + mark)
  *   5 compact (scans + scatter)   6 next group (min, flags, scans)
  *   7 front selection   8 MC certification   9 Explore as one launch
@@ -326,8 +326,8 @@ int pump_sample_halton(int32_t n, int32_t n_goal, const float* lo, const float* 
  *   workgroup (expand, simulate, staircase, marks, scans + compaction,
  *   next group, group scatter + pair offsets; each includes its barrier;
  *   "launches" counts rounds)   17 Smooth (all of its launches)
- *   18 expand, particle stage (per-phase mode; with the box model the whole
- *   expansion, and nothing is timed under 3)
+ *   18 expand, batches of queued pairs (per-phase mode; with the box model
+ *   the whole expansion, and nothing is timed under 3)
  * pump_set_timing(ctx, on) switches it and clears the totals;
  * pump_get_timing copies min(n, PUMP_TIMING_KINDS) totals (ms) and launch
  * counts (either pointer may be NULL). */

@@ -408,56 +408,72 @@ constexpr double kHullMargin = 1e-9;
 // half-space d.(z - y) >= d.d (always the box that gave d).  `rem` holds the
 // remaining boxes as bits; returns false when none remains.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool hs_next(const double* y, const float* boxes, int n_obs,
-                                        unsigned long long* rem, double* d) {
+// A step for a wave whose lanes hold points of their own (all lanes call it; a
+// lane without boxes left only lends its place): boxes that no lane has left are
+// passed over, so the others are read once for all lanes.  boxes: FP64 (lo xyz,
+// hi xyz).  n_obs at most 64 nw.
+__device__ __forceinline__ bool hs_next_lanes(const double* y, const double* boxes, int nw,
+                                              unsigned long long* rem, double* d) {
 #pragma clang fp contract(off)
     int best = -1;
     double best_d2 = INFINITY;
-    double bd[3] = {0.0, 0.0, 0.0};
-    for (int w = 0; w * 64 < n_obs; ++w) {
-        unsigned long long m = rem[w];
+    double b0 = 0.0, b1 = 0.0, b2 = 0.0;
+    unsigned long long any[kMaxObsWords];
+#pragma unroll
+    for (int w = 0; w < kMaxObsWords; ++w) {
+        any[w] = 0ull;
+        if (w < nw) {
+            unsigned long long u = rem[w];
+            for (int o = 32; o > 0; o >>= 1) u |= __shfl_xor(u, o, 64);
+            any[w] = u;
+        }
+    }
+#pragma unroll
+    for (int w = 0; w < kMaxObsWords; ++w) {
+        unsigned long long m = any[w];
         while (m) {
-            const int o = w * 64 + __ffsll((long long)m) - 1;
+            const int i = __builtin_amdgcn_readfirstlane(__ffsll((long long)m) - 1);
             m &= m - 1ull;
-            const float* b = boxes + o * 6;
-            double dv[3];
-            for (int a = 0; a < 3; ++a)
-                dv[a] = fmin(fmax(y[a], (double)b[a]), (double)b[3 + a]) - y[a];
-            const double d2 = (dv[0] * dv[0] + dv[1] * dv[1]) + dv[2] * dv[2];
-            if (d2 < best_d2) {
-                best_d2 = d2;
-                best = o;
-                bd[0] = dv[0]; bd[1] = dv[1]; bd[2] = dv[2];
+            const double* b = boxes + (w * 64 + i) * 6;
+            const double d0 = fmin(fmax(y[0], b[0]), b[3]) - y[0];
+            const double d1 = fmin(fmax(y[1], b[1]), b[4]) - y[1];
+            const double d2 = fmin(fmax(y[2], b[2]), b[5]) - y[2];
+            const double dd = (d0 * d0 + d1 * d1) + d2 * d2;
+            if (((rem[w] >> i) & 1ull) && dd < best_d2) {
+                best_d2 = dd;
+                best = w * 64 + i;
+                b0 = d0; b1 = d1; b2 = d2;
             }
         }
     }
-    if (best < 0) return false;
-    d[0] = bd[0]; d[1] = bd[1]; d[2] = bd[2];
-    const double dd = (bd[0] * bd[0] + bd[1] * bd[1]) + bd[2] * bd[2];
-    const double dy = (bd[0] * y[0] + bd[1] * y[1]) + bd[2] * y[2];
-    for (int w = 0; w * 64 < n_obs; ++w) {
-        unsigned long long m = rem[w];
+    d[0] = b0; d[1] = b1; d[2] = b2;
+    const double dd = (b0 * b0 + b1 * b1) + b2 * b2;
+    const double dy = (b0 * y[0] + b1 * y[1]) + b2 * y[2];
+#pragma unroll
+    for (int w = 0; w < kMaxObsWords; ++w) {
+        unsigned long long m = any[w];
         while (m) {
-            const int o = w * 64 + __ffsll((long long)m) - 1;
+            const int i = __builtin_amdgcn_readfirstlane(__ffsll((long long)m) - 1);
             m &= m - 1ull;
-            const float* b = boxes + o * 6;
-            double lo_part = 0.0;
-            for (int a = 0; a < 3; ++a)
-                lo_part += fmin(bd[a] * (double)b[a], bd[a] * (double)b[3 + a]);
-            if (o == best || lo_part - dy >= dd) rem[w] &= ~(1ull << (o & 63));
+            const double* b = boxes + (w * 64 + i) * 6;
+            double lo_part = fmin(b0 * b[0], b0 * b[3]);
+            lo_part = lo_part + fmin(b1 * b[1], b1 * b[4]);
+            lo_part = lo_part + fmin(b2 * b[2], b2 * b[5]);
+            if (w * 64 + i == best || lo_part - dy >= dd) rem[w] &= ~(1ull << i);
         }
     }
-    return true;
+    if (best < 0)   // (nothing near: a point that is not finite)
+        for (int w = 0; w < kMaxObsWords; ++w) rem[w] = 0ull;
+    return best >= 0;
 }
 
-// hs_next for a wave whose lanes share y and rem (all 64 lanes call it, in
+// The same for a wave whose lanes share y and rem (all 64 lanes call it, in
 // uniform control flow): lane l takes box w * 64 + l, the nearest box is the
 // wave minimum of the same squared distances, taken at its lowest box index
-// (as the loop above, which keeps the first strict minimum in box order), and
-// the boxes the new plane removes are one ballot per word.  Every value is
-// the same expression as in hs_next, so the planes and the boxes left are
-// identical.
-__device__ __forceinline__ bool hs_next_wave(const double* y, const float* boxes, int n_obs,
+// (as above, where the first strict minimum in box order is kept), and the
+// boxes the new plane removes are one ballot per word.  Every value is the
+// same expression as above, so the planes and the boxes left are identical.
+__device__ __forceinline__ bool hs_next_wave(const double* y, const double* boxes, int n_obs,
                                              unsigned long long* rem, double* d) {
 #pragma clang fp contract(off)
     const int lane = threadIdx.x & 63;
@@ -466,10 +482,10 @@ __device__ __forceinline__ bool hs_next_wave(const double* y, const float* boxes
     for (int w = 0; w * 64 < n_obs; ++w) {
         double d2 = INFINITY;
         if ((rem[w] >> lane) & 1ull) {
-            const float* b = boxes + (w * 64 + lane) * 6;
+            const double* b = boxes + (w * 64 + lane) * 6;
             double dv[3];
             for (int a = 0; a < 3; ++a)
-                dv[a] = fmin(fmax(y[a], (double)b[a]), (double)b[3 + a]) - y[a];
+                dv[a] = fmin(fmax(y[a], b[a]), b[3 + a]) - y[a];
             d2 = (dv[0] * dv[0] + dv[1] * dv[1]) + dv[2] * dv[2];
             if (!(d2 < INFINITY)) d2 = INFINITY;   // never chosen, as in the loop
         }
@@ -483,8 +499,8 @@ __device__ __forceinline__ bool hs_next_wave(const double* y, const float* boxes
     if (best < 0) return false;
     double bd[3];
     {
-        const float* b = boxes + best * 6;
-        for (int a = 0; a < 3; ++a) bd[a] = fmin(fmax(y[a], (double)b[a]), (double)b[3 + a]) - y[a];
+        const double* b = boxes + best * 6;
+        for (int a = 0; a < 3; ++a) bd[a] = fmin(fmax(y[a], b[a]), b[3 + a]) - y[a];
     }
     d[0] = bd[0]; d[1] = bd[1]; d[2] = bd[2];
     const double dd = (bd[0] * bd[0] + bd[1] * bd[1]) + bd[2] * bd[2];
@@ -493,10 +509,10 @@ __device__ __forceinline__ bool hs_next_wave(const double* y, const float* boxes
         const int o = w * 64 + lane;
         bool drop = false;
         if ((rem[w] >> lane) & 1ull) {
-            const float* b = boxes + o * 6;
+            const double* b = boxes + o * 6;
             double lo_part = 0.0;
             for (int a = 0; a < 3; ++a)
-                lo_part += fmin(bd[a] * (double)b[a], bd[a] * (double)b[3 + a]);
+                lo_part += fmin(bd[a] * b[a], bd[a] * b[3 + a]);
             drop = o == best || lo_part - dy >= dd;
         }
         rem[w] &= ~__ballot(drop);

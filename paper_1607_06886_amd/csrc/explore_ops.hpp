@@ -32,11 +32,6 @@ __device__ __forceinline__ bool boxes_overlap(const float* lo3, const float* hi3
            (lo3[2] <= b[5]) & (hi3[2] >= b[2]);
 }
 
-// Obstacles into LDS, by the whole workgroup (a barrier must follow).
-__device__ __forceinline__ void stage_obstacles_block(const float* obs, int n_obs, float* s_raw) {
-    for (int t = threadIdx.x; t < n_obs * 6; t += blockDim.x) s_raw[t] = obs[t];
-}
-
 // Root plan and empty staircases (Alg. 4 first lines).  `t0`/`stride`
 // distribute the staircase fill; the root itself is written by thread t0 == 0.
 __device__ __forceinline__ void explore_init_fill(const RoundArgs& a, int n_nodes, size_t t0,
@@ -115,241 +110,6 @@ __device__ __forceinline__ int wave_group_of(const int32_t* __restrict__ b_off, 
     }
     return lo + cnt;
 }
-
-// ---------------------------------------------------------------------------
-// Expansion with the half-space model (the box model: explore_lane.hpp),
-// first part (one pair per lane): pair q (q < n_pairs) of group lo
-// (wave_group_of), written to candidate slot q - a.q0, its edge and parent
-// plan; cost, step count and K_e waypoints; drop it past S_max; resolve it if
-// the parent's own cp_hat already makes it dominated; otherwise mark the
-// waypoints where some particle of the cloud's bounding box can reach a plane
-// of the local region.  Returns 1 if q keeps the parent's bits (written
-// here), 2 if its particles must be simulated (its queue record in tk), 0 if
-// resolved.
-// ---------------------------------------------------------------------------
-template <int N>
-__device__ __forceinline__ int expand_pair_hsmc(const RoundArgs& a, int q, int lo, const float* s_raw,
-                                                long long& n_sim, long long& n_pre,
-                                                long long& n_drop, SimTask& tk) {
-    constexpr int W = N / 32;
-    const int n_obs = a.n_obs;
-    const int p = a.b_ids[lo];
-    const int head = a.p_head[p];
-    const int e = a.row_ptr[head] + (q - a.b_off[lo]);
-    const int x = a.col[e];
-    const int sl = q - a.q0;   // candidate slot
-    a.c_parent[sl] = p;   // every formed pair records its identity
-    a.c_head[sl] = x;
-    const double tau = a.etau[e];
-    const double cost = a.p_cost[p] + a.ecost[e];
-    const int K = max(1, (int)ceil(tau / a.dt));
-    const int s_p = a.p_step[p];
-    const int pop_p = a.p_pop[p];
-    if (s_p + K > a.S_max) {
-        a.c_flag[sl] = 0;
-        a.c_pop[sl] = -2;
-        ++n_drop;
-        return 0;
-    }
-    if (a.preprune && stair_get(a.stair, a.stair_w, x, pop_p) < cost) {
-        a.c_flag[sl] = 0;
-        a.c_pop[sl] = -1;
-        ++n_pre;
-        return 0;
-    }
-    ++n_sim;
-    Cubic cs[3];
-    hermite(a.X + (size_t)head * 6, a.X + (size_t)x * 6, tau, cs);
-    {
-        // mark the waypoints where some particle of the cloud box can reach
-        // a plane of the local region, or come within the flag distance
-        unsigned near = 0u;
-        for (int k = 1; k <= K; ++k) {
-            const double t = ((double)k * tau) / (double)K;
-            double y[3], v[3];
-            for (int ax = 0; ax < 3; ++ax) {
-                y[ax] = cs[ax].at(t);
-                v[ax] = cs[ax].c1 + t * (2.0 * cs[ax].c2 + t * 3.0 * cs[ax].c3);
-            }
-            const float* cl = a.cloud + (size_t)(s_p + k) * 6;
-            unsigned long long rem[kMaxObsWords];
-            all_boxes(n_obs, rem);
-            double dd[3];
-            while (hs_next(y, s_raw, n_obs, rem, dd)) {
-                double av[3], b;
-                hs_project(dd, v, av, b);
-                double reach = 0.0;
-                for (int ax = 0; ax < 3; ++ax)
-                    reach += fmax(av[ax] * (double)cl[ax], av[ax] * (double)cl[3 + ax]);
-                if (reach > b - kFlagEps * sqrt(b) - 1e-12 * (b + 1.0)) {
-                    near |= 1u << (k - 1);
-                    break;
-                }
-            }
-        }
-        a.c_edge[sl] = e;
-        a.c_cost[sl] = cost;
-        a.c_step[sl] = s_p + K;
-        if (near == 0u) {
-            a.c_flag[sl] = 1;
-            a.c_pop[sl] = pop_p;
-            for (int w = 0; w < W; ++w) a.c_mask[(size_t)sl * W + w] = a.p_mask[(size_t)p * W + w];
-            return 1;
-        }
-        tk = SimTask{sl, p, K, near, (uint32_t)head | ((uint32_t)x << 16), s_p, tau};
-        return 2;
-    }
-}
-
-// Append the workgroup's pairs with st == 2 (records tk) to the simulation
-// queue (all threads call it): one global atomic per workgroup.
-// s_w: [blockDim.x / 64].
-__device__ __forceinline__ void queue_pairs_block(const RoundArgs& a, int st, const SimTask& tk,
-                                                  int* s_w) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const unsigned long long need = __ballot(st == 2);
-    if (lane == 0) s_w[w] = (int)__popcll(need);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int tot = 0;
-        for (int k = 0; k < nw; ++k) {
-            const int c = s_w[k];
-            s_w[k] = tot;
-            tot += c;
-        }
-        const int base = tot ? atomicAdd(&a.ctl->n_tasks, tot) : 0;
-        for (int k = 0; k < nw; ++k) s_w[k] += base;
-    }
-    __syncthreads();
-    if (st == 2) a.tasks[s_w[w] + (int)__popcll(need & lanemask_lt(lane))] = tk;
-    __syncthreads();   // s_w is reused
-}
-
-// Broadcast of lane k's double to the whole wave (wave-uniform result).
-__device__ __forceinline__ double readlane_f64(double v, int k) {
-    const long long bits = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(unsigned)(bits & 0xFFFFFFFFll), k);
-    const int hi = __builtin_amdgcn_readlane((int)(bits >> 32), k);
-    return __longlong_as_double(((long long)(unsigned)hi << 32) | (unsigned)lo);
-}
-
-// ---------------------------------------------------------------------------
-// Second part of the half-space expansion (one queued pair per wave,
-// particles across lanes; Sec. III-B, eq. (7)): per marked waypoint the planes
-// of the local convex region against every particle, in FP64.  Hits are
-// gathered into the N-bit mask, ORed with the parent's bits and counted; the
-// pair is cut if pop >= c_cut.  Counters are wave-uniform (n_wp: waypoints
-// tested, n_bt: waypoint-plane tests, each over all particles).  Lane l holds
-// particles l, l + 64, ..., so the hit bits of particle row r are one wave
-// ballot (mask words 2r and 2r+1 as they stand).
-// ---------------------------------------------------------------------------
-template <int N>
-__device__ __forceinline__ void simulate_pair_hsmc(const RoundArgs& a, int task, const float* s_raw,
-                                              long long& n_pre, long long& n_flag, long long& n_wp,
-                                              long long& n_bt) {
-    constexpr int W = N / 32;                      // u32 mask words
-    constexpr int PPL = N >= 64 ? N / 64 : 1;      // particles per lane
-    const int n_obs = a.n_obs;
-    const int lane = threadIdx.x & 63;
-    const bool valid_lane = (N >= 64) || (lane < N);
-    const SimTask tk = a.tasks[task];
-    const int qj = tk.q, pj = tk.p;
-    const int hj = (int)(tk.nodes & 0xFFFFu), xj = (int)(tk.nodes >> 16);
-    const double tj = tk.tau, cj = a.c_cost[qj];
-    const int Kj = tk.K;
-    const int spj = tk.s_p;
-    const unsigned nj = tk.near;
-    Cubic cs[3];
-    hermite(a.X + (size_t)hj * 6, a.X + (size_t)xj * 6, tj, cs);
-    bool hit[PPL], deep[PPL], nearp[PPL];
-    for (int r = 0; r < PPL; ++r) { hit[r] = false; deep[r] = false; nearp[r] = false; }
-    // the parent's bit of each of this lane's particles (particle r * 64 + lane)
-    bool par[PPL];
-    for (int r = 0; r < PPL; ++r) {
-        const int j = valid_lane ? r * 64 + lane : 0;
-        par[r] = valid_lane && ((a.p_mask[(size_t)pj * W + (j >> 5)] >> (j & 31)) & 1u);
-    }
-    unsigned wm = nj;
-    {
-        // at each marked waypoint, every plane of the local region against
-        // every particle's deviation, in FP64; as with the box model, the
-        // pair stops at the waypoint where its count reaches c_cut
-        while (wm) {
-            ++n_wp;   // waypoints whose cloud box meets an obstacle (or a plane)
-            const int k = __ffs((int)wm);
-            wm &= wm - 1u;
-            const int s = spj + k;
-            const double t = ((double)k * tj) / (double)Kj;
-            double y[3], v[3];
-            for (int ax = 0; ax < 3; ++ax) {
-                y[ax] = cs[ax].at(t);
-                v[ax] = cs[ax].c1 + t * (2.0 * cs[ax].c2 + t * 3.0 * cs[ax].c3);
-            }
-            double dy[PPL][3];
-            for (int r = 0; r < PPL; ++r) {
-                const int jj = valid_lane ? r * 64 + lane : 0;
-                for (int ax = 0; ax < 3; ++ax) dy[r][ax] = (double)a.D[((size_t)s * 3 + ax) * N + jj];
-            }
-            unsigned long long rem[kMaxObsWords];
-            all_boxes(n_obs, rem);
-            double dd[3];
-            while (hs_next_wave(y, s_raw, n_obs, rem, dd)) {
-                double av[3], b;
-                hs_project(dd, v, av, b);
-                ++n_bt;
-                const double na = sqrt(b);
-                if (!(na > 0.0)) continue;
-                for (int r = 0; r < PPL; ++r) {
-                    const double g = (av[0] * dy[r][0] + av[1] * dy[r][1]) + av[2] * dy[r][2];
-                    const double mg = (g - b) / na;
-                    if (g > b) hit[r] = true;
-                    if (mg >= kFlagEps) deep[r] = true;
-                    if (fabs(mg) < kFlagEps) nearp[r] = true;
-                }
-            }
-            int cnt = 0;
-            for (int r = 0; r < PPL; ++r) cnt += (int)__popcll(__ballot(valid_lane && (hit[r] || par[r])));
-            if (cnt >= a.c_cut) break;
-        }
-    }
-    // gather hits into the N-bit mask and OR with the parent's bits
-    uint32_t words[W];
-    int popc = 0;
-    long long flg = 0;
-    for (int r = 0; r < PPL; ++r) {
-        const unsigned long long hb = __ballot(hit[r] && valid_lane);
-        const unsigned long long fb = __ballot(nearp[r] && !deep[r] && valid_lane);
-        if (N >= 64) {
-            const uint32_t pm0 = a.p_mask[(size_t)pj * W + 2 * r];
-            const uint32_t pm1 = a.p_mask[(size_t)pj * W + 2 * r + 1];
-            words[2 * r] = pm0 | (uint32_t)hb;
-            words[2 * r + 1] = pm1 | (uint32_t)(hb >> 32);
-            flg += __popc((uint32_t)fb & ~pm0) + __popc((uint32_t)(fb >> 32) & ~pm1);
-        } else {
-            const uint32_t pm0 = a.p_mask[(size_t)pj * W];
-            words[0] = pm0 | (uint32_t)hb;
-            flg += __popc((uint32_t)fb & ~pm0);
-        }
-    }
-    for (int w = 0; w < W; ++w) popc += __popc(words[w]);
-    bool keep = popc < a.c_cut;
-    if (keep && a.preprune && stair_get(a.stair, a.stair_w, xj, popc) < cj) {
-        keep = false;
-        ++n_pre;
-    }
-    if (lane == 0) {
-        a.c_flag[qj] = keep ? 1 : 0;
-        a.c_pop[qj] = popc;
-    }
-    if (keep && lane < W) {
-        uint32_t v = 0;
-        for (int w = 0; w < W; ++w)
-            if (w == lane) v = words[w];
-        a.c_mask[(size_t)qj * W + lane] = v;
-    }
-    if (popc < a.c_cut) n_flag += flg;   // flagged decisions of pairs below the cut
-}
-
 
 // ---------------------------------------------------------------------------
 // RemoveDominated (Sec. IV): remove every open plan p for which some plan d

@@ -7,21 +7,22 @@
 // same index ranges), so the plan store is identical to the one the
 // per-round path builds, whatever the team size.
 //
-// Work split: expansion strides over pairs by workgroup pass, the half-space
-// model's particle queue by wave, the staircase update by thread.  Marking, compaction and the next
-// group use contiguous chunks of the pair and open lists, one chunk per
+// Work split: expansion strides over pairs by workgroup pass, the staircase
+// update by thread.  Marking, compaction and the next group use contiguous chunks of the pair and open lists, one chunk per
 // member, so each scan needs one exchange of chunk totals: a member publishes
 // its totals and then adds those of the members before it.
 #pragma once
 
+#include "explore_half.hpp"
 #include "explore_lane.hpp"
 #include "explore_ops.hpp"
 
 namespace pump {
 
-// Dynamic LDS of a team kernel: the boxes of the largest query.
+// Dynamic LDS of a team kernel: the boxes of the largest query (and the
+// half-space model's planes).
 __host__ __device__ constexpr size_t team_lds_bytes(int cp_model, int n_obs) {
-    return cp_model == 0 ? box_lds_bytes(n_obs) : (size_t)n_obs * 6 * sizeof(float);
+    return cp_model == 0 ? box_lds_bytes(n_obs) : half_lds_bytes(n_obs);
 }
 
 __device__ __forceinline__ unsigned long long rt_ticks() { return __builtin_amdgcn_s_memrealtime(); }
@@ -270,13 +271,12 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
     unsigned epoch = 0;
     const int G = g.size, b = g.rank, T = blockDim.x, tid = threadIdx.x;
     const int lane = tid & 63;
-    const int gwave = b * (T >> 6) + (tid >> 6), n_gwaves = G * (T >> 6);
     Ctl* c = ra[0].ctl;
     const bool leader = (b == 0 && tid == 0);
     BoxLds box;
-    float* s_raw = reinterpret_cast<float*>(s_box);
+    HalfStage half;
     if constexpr (CP == 0) box = stage_box_lds(ra[0], s_box);
-    else stage_obstacles_block(ra[0].obs, ra[0].n_obs, s_raw);
+    else half = stage_half_lds(ra[0], s_box);
     if (CP == 0 && tid < 3) pl.cnt[tid] = 0;
     if (init) {
         // the root goes to the list the first round reads (ra[1].open_out)
@@ -295,10 +295,8 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
     int32_t* cur = g.open_cur;
     int32_t* nxt = g.open_next;
     int par = 0;
-    long long n_sim = 0, n_pre = 0, n_drop = 0, kept = 0;
-    PairCounts n;                                            // box model, wave-uniform
-    long long w_pre = 0, w_flag = 0, w_wp = 0, w_bt = 0;     // wave-uniform
-    long long partial = 0;
+    long long kept = 0, partial = 0;
+    PairCounts n;                                            // wave-uniform
     int rounds = 0, err = 0;
     int fail_surv = 0;            // survivors of the round that overflowed the plan store
     // phase wall times seen by the leader (constant-rate real-time counter)
@@ -323,36 +321,22 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         partial += n_pairs;
         ++rounds;
         if (leader) t_prev = __builtin_amdgcn_s_memrealtime();
-        // (1) expansion, one pair per lane, the workgroup's passes strided
-        //     over the team; the leader resets the cheapest-open-cost
+        // (1) expansion, the workgroup's passes strided over the team; the
+        //     leader resets the cheapest-open-cost
         //     accumulator of phase 5 (its store is written back at the next
-        //     barrier).  The box model takes each pair to its particle bits
-        //     here; the half-space model queues the pairs whose particles
-        //     must be simulated, with one atomic per workgroup and pass.
+        //     barrier).
         if (leader) c->min_cost_bits = 0x7FF0000000000000ull;
         if constexpr (CP == 0) {
             expand_box_block<N>(a, 0, n_pairs, b, G, n_B, box, gl, gh, pl, n);
             if (leader) tick(0);
         } else {
-            for (int base = b * T; base < n_pairs; base += G * T) {
-                const int tile = base + (tid & ~63);
-                const int q = base + tid;
-                SimTask tk;
-                int st = 0;
-                if (tile < n_pairs) {   // the wave's pairs
-                    const int grp = wave_group_of(a.b_off, n_B, tile, q);
-                    st = q < n_pairs ? expand_pair_hsmc<N>(a, q, grp, s_raw, n_sim, n_pre, n_drop, tk)
-                                     : 0;
-                }
-                queue_pairs_block(a, st, tk, s_w);
-            }
+            half_headers(a, 0, n_pairs, b, G, n_B, n);
             if (team_barrier(g, epoch, s_fail_p)) break;
             if (leader) tick(0);
-            // (2) particle simulation, one queued pair per wave
+            // (2) the queued pairs' planes and particles
             const int n_tasks =
                 uni(__hip_atomic_load(&c->n_tasks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            for (int task = gwave; task < n_tasks; task += n_gwaves)
-                simulate_pair_hsmc<N>(a, task, s_raw, w_pre, w_flag, w_wp, w_bt);
+            half_batches<N>(a, n_tasks, b, G, half, n);
         }
         if (team_barrier(g, epoch, s_fail_p)) break;
         if (leader) tick(1);
@@ -448,8 +432,8 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         if (team_barrier(g, epoch, s_fail_p)) break;
         if (leader) tick(4);
         // (6) next group index; flag the group and count it per chunk.  The
-        //     leader empties the simulation queue for the next round (written
-        //     back at the barrier after phase 7).
+        //     leader empties the queue for the next round (written back at the
+        //     barrier after phase 7).
         if (leader) c->n_tasks = 0;
         if (n_open == 0) {
             done = 1;
@@ -523,12 +507,12 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         if (leader) tick(6);
     }
     // counters and the final loop state
-    const long long s_sim = block_sum_ll2(n_sim + (lane == 0 ? n.sim : 0), s_ll);
-    const long long s_pre = block_sum_ll2(n_pre + (lane == 0 ? w_pre + n.pre : 0), s_ll);
-    const long long s_drop = block_sum_ll2(n_drop + (lane == 0 ? n.drop : 0), s_ll);
-    const long long s_flag = block_sum_ll2(lane == 0 ? w_flag + n.flag : 0, s_ll);
-    const long long s_wp = block_sum_ll2(lane == 0 ? w_wp + n.wp : 0, s_ll);
-    const long long s_bt = block_sum_ll2(lane == 0 ? w_bt + n.bt : 0, s_ll);
+    const long long s_sim = block_sum_ll2(lane == 0 ? n.sim : 0, s_ll);
+    const long long s_pre = block_sum_ll2(lane == 0 ? n.pre : 0, s_ll);
+    const long long s_drop = block_sum_ll2(lane == 0 ? n.drop : 0, s_ll);
+    const long long s_flag = block_sum_ll2(lane == 0 ? n.flag : 0, s_ll);
+    const long long s_wp = block_sum_ll2(lane == 0 ? n.wp : 0, s_ll);
+    const long long s_bt = block_sum_ll2(lane == 0 ? n.bt : 0, s_ll);
     const long long s_kept = block_sum_ll2(kept, s_ll);
     if (tid == 0) {
         if (s_sim) atomicAdd((unsigned long long*)&c->simulated, (unsigned long long)s_sim);

@@ -71,7 +71,7 @@ struct pump_ctx {
     // candidates
     int32_t *c_head = nullptr, *c_parent = nullptr, *c_edge = nullptr, *c_step = nullptr,
             *c_pop = nullptr, *c_pos = nullptr;
-    SimTask* tasks = nullptr;          // simulation queue records
+    HalfPair* tasks = nullptr;          // simulation queue records
     double* c_cost = nullptr;
     uint32_t* c_mask = nullptr;
     uint8_t* c_flag = nullptr;

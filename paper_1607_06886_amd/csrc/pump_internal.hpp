@@ -94,19 +94,13 @@ struct Ctl {
     int32_t chunk_base;
 };
 
-// A pair queued for particle simulation, with what the simulation needs of
-// it (written by the expansion, so the simulation reads one record instead of
-// chasing the pair's parent and edge through the plan store and the graph).
-struct SimTask {
-    int32_t q;                 // pair index
-    int32_t p;                 // parent plan
-    int32_t K;                 // waypoints on the edge, ceil(tau / dt) (at most 32)
-    uint32_t near;             // waypoints whose cloud box meets an obstacle (bit k-1)
-    uint32_t nodes;            // edge endpoints: head | x << 16 (node ids < 65536)
-    int32_t s_p;               // parent's step count
+// A pair of the half-space model whose particles matter (explore_half.hpp).
+struct HalfPair {
     double tau;                // edge duration
+    int32_t sl, p;             // candidate slot, parent plan
+    uint32_t nodes;            // edge endpoints: head | x << 16 (node ids < 65536)
+    int32_t K, s_p;            // waypoints on the edge (at most 32), parent's step count
 };
-static_assert(sizeof(SimTask) == 32, "SimTask is two 16-byte loads");
 
 // Counter partials of the per-phase Explore kernels: workgroup b of a kernel
 // adds its sums to part[b * kPartK + k] (its own slot, no atomics), and one
@@ -174,7 +168,7 @@ struct RoundArgs {
     uint32_t* c_mask;
     uint8_t* c_flag;
     int32_t* c_pos;            // scan input/output over the pairs
-    SimTask* tasks;            // pairs queued for particle simulation
+    HalfPair* tasks;            // pairs queued for particle simulation
     Ctl* ctl;
     // a round run in chunks (more pairs than candidate slots): pair q of the
     // round is slot q - q0 (q0 = 0 otherwise); quiet = 1 in the second pass
