@@ -347,6 +347,7 @@ __global__ void k_b_finalize(BatchQuery* qs, int q, BatchOut* outs) {
     const BatchQuery& Q = qs[i];
     BatchOut& o = outs[i];
     const Ctl* c = Q.ra[0].ctl;
+    o.ctl = *c;
     o.bad = Q.bad;
     o.best = -1;
     o.best_plan = -1;

@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -90,6 +91,8 @@ struct pump_ctx {
     Ctl* ctl_h = nullptr;  // pinned mirror
     int32_t* stage_h = nullptr;   // pinned: [0] n_nodes up; [4..9) flags, counters and edges down
     float* xinit_h = nullptr;     // pinned: x_init on its way to node 0
+    int32_t* path_h = nullptr;    // pinned: a path read back (1 + max_steps + 2)
+    std::mutex path_mutex;        // (paths may be read by several threads)
     // selection
     int32_t *goal_ids = nullptr, *front_ids = nullptr, *paths = nullptr, *path_len = nullptr,
             *wp_len = nullptr, *mc_counts = nullptr;
@@ -356,6 +359,7 @@ int pump_destroy(pump_ctx* ctx) {
     if (ctx->ra_h) (void)hipHostFree(ctx->ra_h);
     if (ctx->stage_h) (void)hipHostFree(ctx->stage_h);
     if (ctx->xinit_h) (void)hipHostFree(ctx->xinit_h);
+    if (ctx->path_h) (void)hipHostFree(ctx->path_h);
     for (auto& e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
     for (auto& p : ctx->pending) ctx->pool.push_back({p.a, p.b});
@@ -499,6 +503,7 @@ int pump_create(const pump_config* cfg_in, void* hip_stream, pump_ctx** out) {
     A(hipHostMalloc((void**)&ctx->ctl_h, sizeof(Ctl), hipHostMallocDefault));
     A(hipHostMalloc((void**)&ctx->stage_h, 16 * sizeof(int32_t), hipHostMallocDefault));
     A(hipHostMalloc((void**)&ctx->xinit_h, 8 * sizeof(float), hipHostMallocDefault));
+    A(hipHostMalloc((void**)&ctx->path_h, ((size_t)cfg.max_steps + 3) * sizeof(int32_t), hipHostMallocDefault));
     for (auto& e : ctx->ev) A(hipEventCreate(&e));
     if (!ok) {
         pump_destroy(ctx);
@@ -1258,19 +1263,17 @@ int pump_get_front(pump_ctx* ctx, int32_t* plan_ids, int32_t* mc_counts, int32_t
 int pump_get_path(pump_ctx* ctx, int32_t plan, int32_t* nodes, int32_t cap, int32_t* len) {
     if (!ctx || !nodes || !len) return PUMP_E_ARG;
     if (!ctx->have_explore) return fail(ctx, PUMP_E_STATE, "pump_explore_begin first");
-    const int n = ctx->ctl_h->n_plans;
-    if (plan < 0 || plan >= n) return fail(ctx, PUMP_E_ARG, "plan id out of range");
-    std::vector<int32_t> par(n), head(n);
-    HIPCHK(hipMemcpy(par.data(), ctx->p_parent, (size_t)n * 4, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(head.data(), ctx->p_head, (size_t)n * 4, hipMemcpyDeviceToHost));
-    std::vector<int32_t> rev;
-    for (int q = plan; q >= 0; q = par[q]) {
-        rev.push_back(head[q]);
-        if ((int)rev.size() > n) return fail(ctx, PUMP_E_STATE, "parent cycle");
-    }
-    if ((int)rev.size() > cap) return fail(ctx, PUMP_E_ARG, "output too small");
-    *len = (int32_t)rev.size();
-    for (size_t i = 0; i < rev.size(); ++i) nodes[i] = rev[rev.size() - 1 - i];
+    if (plan < 0 || plan >= ctx->ctl_h->n_plans) return fail(ctx, PUMP_E_ARG, "plan id out of range");
+    std::lock_guard<std::mutex> lock(ctx->path_mutex);
+    const int most = ctx->S_max + 2;   // (an edge is at least a step)
+    launch_plan_path(ctx->stream, ctx->p_parent, ctx->p_head, ctx->ctl, plan, ctx->path_h, most);
+    HIPCHK(hipStreamSynchronize(ctx->stream));
+    HIPCHK(hipGetLastError());
+    const int n = ctx->path_h[0];
+    if (n < 0 || n > most) return fail(ctx, PUMP_E_STATE, "parent cycle");
+    if (n > cap) return fail(ctx, PUMP_E_ARG, "output too small");
+    *len = n;
+    for (int i = 0; i < n; ++i) nodes[i] = ctx->path_h[n - i];
     return PUMP_OK;
 }
 

@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstddef>
 #include <cstdio>
+#include <mutex>
 #include <string>
 #include <type_traits>
 #include <vector>
@@ -62,6 +63,8 @@ struct pump_batch {
     std::vector<BatchQuery> qs;
     std::vector<BatchOut> outs;
     std::vector<const pump_roadmap*> rms;   // per query (pump_batch_set_roadmaps)
+    int32_t* path_h = nullptr;     // pinned: a path read back (1 + max_steps + 2)
+    std::mutex path_mutex;         // (paths may be read by several threads)
     std::string err;
 };
 
@@ -88,6 +91,7 @@ int pump_batch_destroy(pump_batch* b) {
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     for (void* p : b->allocs)
         if (p) (void)hipFree(p);
+    if (b->path_h) (void)hipHostFree(b->path_h);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;
     return PUMP_OK;
@@ -130,6 +134,10 @@ int pump_batch_create(const pump_config* cfg_in, int32_t max_queries, void* hip_
     const size_t P = (size_t)cfg.cap_plans, Q = (size_t)cfg.cap_pairs, E = (size_t)cfg.cap_edges;
     const size_t W = (size_t)N / 32;
     b->words = (int)(((nn + 63) / 64) * 2);
+    if (hipHostMalloc((void**)&b->path_h, (S + 3) * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+        pump_batch_destroy(b);
+        return PUMP_E_HIP;
+    }
     // One arena holds every slot (same layout per slot, 256-byte aligned
     // arrays) and the batch descriptors; slots are sized for the largest
     // query the configuration admits.
@@ -386,14 +394,12 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
     }
     BCHK(hipGetLastError());
     BCHK(hipMemcpyAsync(b->outs.data(), b->out_dev, sizeof(BatchOut) * q, hipMemcpyDeviceToHost, b->stream));
-    std::vector<Ctl> ctls(q);
-    for (int i = 0; i < q; ++i)
-        BCHK(hipMemcpyAsync(&ctls[i], b->slots[i].ctl, sizeof(Ctl), hipMemcpyDeviceToHost, b->stream));
     BCHK(hipStreamSynchronize(b->stream));
     const float ms = std::chrono::duration<float, std::milli>(std::chrono::steady_clock::now() - t0).count();
     int worst = PUMP_OK;
     for (int i = 0; i < q; ++i) {
         const BatchOut& o = b->outs[i];
+        const Ctl& ctl = o.ctl;
         pump_result r;
         memset(&r, 0, sizeof(r));
         r.status = o.status;
@@ -407,17 +413,17 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         r.best_cost = o.best_cost;
         r.best_cp_mc = o.best_cp_mc;
         r.partial_plans = o.partial_plans;
-        r.simulated = ctls[i].simulated;
-        r.preprune = ctls[i].preprune;
-        r.inserted = ctls[i].inserted;
-        r.survivors = ctls[i].n_plans - 1;
-        r.dropped_steps = ctls[i].dropped_steps;
-        r.flagged = ctls[i].flagged;
-        r.sim_waypoints = ctls[i].sim_waypoints;
-        r.sim_box_tests = ctls[i].sim_box_tests;
+        r.simulated = ctl.simulated;
+        r.preprune = ctl.preprune;
+        r.inserted = ctl.inserted;
+        r.survivors = ctl.n_plans - 1;
+        r.dropped_steps = ctl.dropped_steps;
+        r.flagged = ctl.flagged;
+        r.sim_waypoints = ctl.sim_waypoints;
+        r.sim_box_tests = ctl.sim_box_tests;
         r.rounds = o.rounds;
-        r.final_i = ctls[i].i;
-        r.n_plans = ctls[i].n_plans;
+        r.final_i = ctl.i;
+        r.n_plans = ctl.n_plans;
         r.n_edges = o.n_edges;
         r.c_cut = b->qs[i].ra[0].c_cut;
         r.c_min = b->qs[i].ra[0].c_min;
@@ -439,20 +445,17 @@ int pump_batch_get_path(pump_batch* b, int32_t query, int32_t plan, int32_t* nod
                         int32_t* len) {
     if (!b || !nodes || !len || query < 0 || query >= (int)b->qs.size()) return PUMP_E_ARG;
     const Slot& s = b->slots[query];
-    Ctl c;
-    BCHK(hipMemcpy(&c, s.ctl, sizeof(Ctl), hipMemcpyDeviceToHost));
-    if (plan < 0 || plan >= c.n_plans) return bfail(b, PUMP_E_ARG, "plan id out of range");
-    std::vector<int32_t> par(c.n_plans), head(c.n_plans);
-    BCHK(hipMemcpy(par.data(), s.p_parent, (size_t)c.n_plans * 4, hipMemcpyDeviceToHost));
-    BCHK(hipMemcpy(head.data(), s.p_head, (size_t)c.n_plans * 4, hipMemcpyDeviceToHost));
-    std::vector<int32_t> rev;
-    for (int p = plan; p >= 0; p = par[p]) {
-        rev.push_back(head[p]);
-        if ((int)rev.size() > c.n_plans) return bfail(b, PUMP_E_STATE, "parent cycle");
-    }
-    if ((int)rev.size() > cap) return bfail(b, PUMP_E_ARG, "output too small");
-    *len = (int32_t)rev.size();
-    for (size_t i = 0; i < rev.size(); ++i) nodes[i] = rev[rev.size() - 1 - i];
+    std::lock_guard<std::mutex> lock(b->path_mutex);
+    const int most = b->cfg.max_steps + 2;   // (an edge is at least a step)
+    launch_plan_path(b->stream, s.p_parent, s.p_head, s.ctl, plan, b->path_h, most);
+    BCHK(hipStreamSynchronize(b->stream));
+    BCHK(hipGetLastError());
+    const int n = b->path_h[0];
+    if (n < 0) return bfail(b, PUMP_E_ARG, "plan id out of range");
+    if (n > most) return bfail(b, PUMP_E_STATE, "parent cycle");
+    if (n > cap) return bfail(b, PUMP_E_ARG, "output too small");
+    *len = n;
+    for (int i = 0; i < n; ++i) nodes[i] = b->path_h[n - i];
     return PUMP_OK;
 }
 
