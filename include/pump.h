@@ -471,7 +471,8 @@ int pump_batch_destroy(pump_batch* b);
  * the device, read only, kept alive until the call returns); n_particles[i]
  * is that query's N (32/64/128/256, at most cfg.n_particles; noise arrays are
  * [S_max][6][N] for that N).  tune may be NULL (256 threads, 2 per CU,
- * largest first, graph on, team_scale 64).  out[i] receives query i's result; the returned
+ * largest first, graph on, team_scale 64, with
+ * smaller teams where a team's queries share the device).  out[i] receives query i's result; the returned
  * code is PUMP_OK or the first negative per-query status.  ms_total holds the
  * wall time of the whole batch. */
 int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_particles,

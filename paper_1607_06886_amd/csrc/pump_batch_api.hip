@@ -324,7 +324,13 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
     // entries in input order or largest first; entry i gets a team of
     // workgroups in proportion to its share of its group's estimated work
     // (team_scale / 4 times the proportional share; 0 = one workgroup per
-    // query).  Teams need every workgroup of a launch resident at once, so
+    // query).  Without a tuning a team is also no larger than three times that
+    // share, or than its query has use for beside others (16 workgroups at 2000
+    // samples, and with their square), whichever is more: what a round's
+    // barriers cost grows with the team.  With 16 times the share throughout, 96
+    // queries of 2000 samples took 11.1 ms, now 7.7 (1.5 times the share: 7.2;
+    // but 64 queries of 1000 to 8000 samples then take 29.3 instead of 28.3, as
+    // now, since a heavy one ends last); few queries keep the whole device.  Teams need every workgroup of a launch resident at once, so
     // each launch is capped by its kernel's occupancy.
     std::vector<int> order, off;
     order.reserve(q);
@@ -355,6 +361,11 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
             if (t.team_scale > 0 && wsum > 0.0) {
                 const double share = 0.25 * t.team_scale * grid * work[i] / wsum;
                 size = (int)std::min<double>(std::max(1.0, floor(share + 0.5)), (double)team_cap);
+                if (!tune) {
+                    const double prop = 3.0 * grid * work[i] / wsum;
+                    const double useful = (double)b->qs[i].n_nodes * b->qs[i].n_nodes / 2.5e5;
+                    size = std::min(size, (int)std::max(1.0, std::max(prop, useful)));
+                }
             }
             order.push_back(i);
             off.push_back(off.back() + size);
