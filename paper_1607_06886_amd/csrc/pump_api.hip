@@ -811,6 +811,16 @@ int pump_explore_round(pump_ctx* ctx, int32_t* done) {
     return PUMP_OK;
 }
 
+// Workgroups of the single launch: one per 512 edges of the graph, as far as
+// they fit on the device.  On small graphs the barriers and exchanges are most
+// of a round, and cost more with each member; measured with 64, 128 and 256
+// workgroups (ms of Explore): 10,700 edges 0.30, 0.32, 0.36 (0.29 with 21);
+// 37,000 edges 0.37, 0.39, 0.43; 92,000 edges 0.41, 0.36, 0.39; 149,000 edges
+// 0.60, 0.52, 0.48.
+static int single_blocks(const pump_ctx* ctx) {
+    return (int)std::min<long long>(ctx->coop_blocks, std::max<long long>(16, (ctx->n_edges + 511ll) / 512));
+}
+
 // Remaining rounds in one launch (see kernels_coop.hip).
 // The single launch in two halves: enqueue, and the bookkeeping once the
 // control block has been read back.
@@ -820,10 +830,11 @@ static int explore_single_enqueue(pump_ctx* ctx) {
     ca.sync.release = ctx->coop_sync;
     ca.sync.fail = reinterpret_cast<int*>(ctx->coop_sync + 1);
     ca.sync.arrive = ctx->coop_sync + 64;
-    ca.sync.n_blocks = (unsigned)ctx->coop_blocks;
+    const int blocks = single_blocks(ctx);
+    ca.sync.n_blocks = (unsigned)blocks;
     ca.sync.patience = ctx->patience;
     ca.xa = reinterpret_cast<unsigned long long*>(ctx->coop_sync + 64 + 4096);
-    ca.xb = ca.xa + ctx->coop_blocks;
+    ca.xb = ca.xa + blocks;
     ca.b_deg = ctx->b_deg;
     ca.open_cur = ctx->open_cur;
     ca.open_next = ctx->open_next;
@@ -839,7 +850,7 @@ static int explore_single_enqueue(pump_ctx* ctx) {
     HIPCHK(hipMemcpyAsync(ctx->ra_dev, ctx->ra_h, 2 * sizeof(RoundArgs), hipMemcpyHostToDevice,
                           ctx->stream));
     HIPCHK(launch_explore_coop(ctx->stream, ctx->ra_dev, ca, ctx->N, ctx->cfg.cp_model, ctx->n_obs,
-                               ctx->coop_blocks));
+                               blocks));
     tend(ctx);
     return PUMP_OK;
 }
