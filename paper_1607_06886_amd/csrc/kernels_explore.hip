@@ -28,76 +28,100 @@ __device__ __forceinline__ int block_exclusive_sum(int v, int* s_tmp, int& total
     return off + x - v;
 }
 
-__global__ __launch_bounds__(256) void k_scan_reduce(const int32_t* __restrict__ in,
-                                                     const int32_t* __restrict__ n_dev,
-                                                     int32_t* __restrict__ blk) {
+// One or two arrays (grid.y) per launch.
+__global__ __launch_bounds__(256) void k_scan_reduce(ScanJob j0, ScanJob j1) {
     __shared__ int s_tmp[4];
-    const int n = *n_dev;
+    const ScanJob& j = blockIdx.y ? j1 : j0;
+    const int n = *j.n;
     const int base = blockIdx.x * kScanBlock;
     if (base >= n) {
-        if (threadIdx.x == 0) blk[blockIdx.x] = 0;
+        if (threadIdx.x == 0) j.blk[blockIdx.x] = 0;
         return;
     }
     int sum = 0;
     for (int k = 0; k < 4; ++k) {
         int idx = base + threadIdx.x * 4 + k;
-        if (idx < n) sum += in[idx];
+        if (idx < n) sum += j.in[idx];
     }
     int total;
     block_exclusive_sum(sum, s_tmp, total);
-    if (threadIdx.x == 0) blk[blockIdx.x] = total;
+    if (threadIdx.x == 0) j.blk[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(256) void k_scan_blocks(int32_t* __restrict__ blk, int nblk,
-                                                     int32_t* __restrict__ total_dev,
-                                                     int32_t* __restrict__ total2_dev) {
+// Block totals to their exclusive sums (one workgroup an array).
+__global__ __launch_bounds__(256) void k_scan_blocks(ScanJob j0, ScanJob j1, int nblk) {
     __shared__ int s_tmp[4];
+    const ScanJob& j = blockIdx.y ? j1 : j0;
     int carry = 0;
     for (int b0 = 0; b0 < nblk; b0 += 256) {
         int idx = b0 + threadIdx.x;
-        int v = idx < nblk ? blk[idx] : 0;
+        int v = idx < nblk ? j.blk[idx] : 0;
         int total;
         int ex = block_exclusive_sum(v, s_tmp, total);
-        if (idx < nblk) blk[idx] = carry + ex;
+        if (idx < nblk) j.blk[idx] = carry + ex;
         carry += total;
-    }
-    if (threadIdx.x == 0) {
-        *total_dev = carry;
-        if (total2_dev) *total2_dev = carry;
     }
 }
 
-__global__ __launch_bounds__(256) void k_scan_down(const int32_t* __restrict__ in,
-                                                   int32_t* __restrict__ out,
-                                                   const int32_t* __restrict__ n_dev,
-                                                   const int32_t* __restrict__ blk) {
+// summed: blk holds exclusive sums, else totals, which every workgroup adds up
+// to its own place.  The last workgroup writes the array's total.
+__global__ __launch_bounds__(256) void k_scan_down(ScanJob j0, ScanJob j1, int summed) {
     __shared__ int s_tmp[4];
-    const int n = *n_dev;
+    const ScanJob& j = blockIdx.y ? j1 : j0;
+    const int n = *j.n;
     const int base = blockIdx.x * kScanBlock;
-    if (base >= n) return;
+    const bool last = blockIdx.x == gridDim.x - 1;
+    if (base >= n && !last) return;
+    int before = 0;
+    if (summed) {
+        before = j.blk[blockIdx.x];
+    } else {
+        for (int k = threadIdx.x; k < (int)blockIdx.x; k += 256) before += j.blk[k];
+        int total;
+        block_exclusive_sum(before, s_tmp, total);
+        before = total;
+    }
     int v[4];
     int sum = 0;
     for (int k = 0; k < 4; ++k) {
         int idx = base + threadIdx.x * 4 + k;
-        v[k] = idx < n ? in[idx] : 0;
+        v[k] = idx < n ? j.in[idx] : 0;
         sum += v[k];
     }
     int total;
-    int ex = block_exclusive_sum(sum, s_tmp, total) + blk[blockIdx.x];
+    int ex = block_exclusive_sum(sum, s_tmp, total) + before;
     for (int k = 0; k < 4; ++k) {
         int idx = base + threadIdx.x * 4 + k;
-        if (idx < n) out[idx] = ex;
+        if (idx < n) j.out[idx] = ex;
         ex += v[k];
     }
+    if (last && threadIdx.x == 0) {
+        *j.total = before + total;
+        if (j.total2) *j.total2 = before + total;
+    }
+}
+
+// Each of these kernels takes some 4 us whatever it does, so two arrays of a
+// step share their launches, and up to kScanDirect workgroups add up the totals
+// before them by themselves (a launch less; at 1,250 of them, the indoor
+// query's rounds, 4.4 us against 4.3 + 5.4).  Beyond, those reads would grow
+// with the square of the length.
+constexpr int kScanDirect = 2048;
+
+void scan_exclusive2(hipStream_t s, const ScanJob& j0, const ScanJob* j1, int32_t n_upper) {
+    int nblk = (n_upper + kScanBlock - 1) / kScanBlock;
+    if (nblk < 1) nblk = 1;
+    const dim3 grid(nblk, j1 ? 2 : 1);
+    const ScanJob b = j1 ? *j1 : j0;
+    k_scan_reduce<<<grid, 256, 0, s>>>(j0, b);
+    const bool summed = nblk > kScanDirect;
+    if (summed) k_scan_blocks<<<dim3(1, grid.y), 256, 0, s>>>(j0, b, nblk);
+    k_scan_down<<<grid, 256, 0, s>>>(j0, b, summed ? 1 : 0);
 }
 
 void scan_exclusive(hipStream_t s, const int32_t* in, int32_t* out, const int32_t* n_dev,
                     int32_t n_upper, int32_t* total_dev, int32_t* blk, int32_t* total2_dev) {
-    int nblk = (n_upper + kScanBlock - 1) / kScanBlock;
-    if (nblk < 1) nblk = 1;
-    k_scan_reduce<<<nblk, 256, 0, s>>>(in, n_dev, blk);
-    k_scan_blocks<<<1, 256, 0, s>>>(blk, nblk, total_dev, total2_dev);
-    k_scan_down<<<nblk, 256, 0, s>>>(in, out, n_dev, blk);
+    scan_exclusive2(s, ScanJob{in, out, n_dev, total_dev, total2_dev, blk}, nullptr, n_upper);
 }
 
 // ---------------------------------------------------------------------------
@@ -359,9 +383,9 @@ __global__ void k_compact_finalize(Ctl* c, int64_t cap) { compact_finalize(c, ca
 
 void launch_compact(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, int32_t n_open,
                     int32_t* blk) {
-    scan_exclusive(s, a.c_pos, a.c_pos, &a.ctl->n_pairs, n_pairs, &a.ctl->scan_total[0], blk);
-    scan_exclusive(s, a.o_keep, a.o_keep, &a.ctl->n_open, n_open,
-                   &a.ctl->scan_total[1], blk + 65536);
+    const ScanJob opens{a.o_keep, a.o_keep, &a.ctl->n_open, &a.ctl->scan_total[1], nullptr, blk + 65536};
+    scan_exclusive2(s, ScanJob{a.c_pos, a.c_pos, &a.ctl->n_pairs, &a.ctl->scan_total[0], nullptr, blk}, &opens,
+                    n_pairs > n_open ? n_pairs : n_open);
     int b = (n_pairs + n_open + 255) / 256;
     if (b < 1) b = 1;
     if (b > 16384) b = 16384;
@@ -504,21 +528,33 @@ __global__ __launch_bounds__(256) void k_open_min(RoundArgs a) {
 
 __global__ void k_pick_i(RoundArgs a) { pick_next_i(a.ctl, a.h); }
 
-__global__ __launch_bounds__(256) void k_flag_group(RoundArgs a) {
+__global__ __launch_bounds__(256) void k_flag_group(RoundArgs a, int32_t* __restrict__ deg) {
     const int n_open = a.ctl->n_open;
     if (a.ctl->done) return;
     const double thr = (double)a.ctl->i * a.h;
     int stop = 0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_open; i += gridDim.x * blockDim.x)
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_open; i += gridDim.x * blockDim.x) {
         stop |= flag_group_one(a, i, thr) ? 1 : 0;
+        int d = 0;
+        if (a.o_inB[i]) {
+            const int h = a.p_head[a.open_out[i]];
+            d = a.row_ptr[h + 1] - a.row_ptr[h];
+        }
+        deg[i] = d;
+    }
     if (__any(stop) && (threadIdx.x & 63) == 0) atomicOr(&a.ctl->goal_stop, 1);
 }
 
-__global__ __launch_bounds__(256) void k_scatter_group(RoundArgs a, int32_t* deg) {
+// The group in open-list order and its pair offsets (o_keep and deg scanned).
+__global__ __launch_bounds__(256) void k_scatter_group(RoundArgs a, const int32_t* deg) {
     const int n_open = a.ctl->n_open;
     if (a.ctl->done) return;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_open; i += gridDim.x * blockDim.x)
-        scatter_group_one(a, i, deg);
+    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_open; i += gridDim.x * blockDim.x) {
+        if (!a.o_inB[i]) continue;
+        const int pos = a.o_keep[i];
+        a.b_ids[pos] = a.open_out[i];
+        a.b_off[pos] = deg[i];
+    }
 }
 
 __global__ void k_group_finalize(RoundArgs a) {
@@ -535,12 +571,6 @@ __global__ void k_group_finalize(RoundArgs a) {
     c->done = c->goal_stop ? 1 : 0;
 }
 
-__global__ void k_copy_ngroup(Ctl* c) {
-    // the degree scan runs over n_B entries; publish it before the scan
-    if (!c->done) c->n_B = c->scan_total[2];
-    else c->n_B = 0;
-}
-
 void launch_next_group(hipStream_t s, const RoundArgs& a, int32_t n_open_upper, int32_t* deg,
                        int32_t* blk) {
     int b = (n_open_upper + 255) / 256;
@@ -550,13 +580,12 @@ void launch_next_group(hipStream_t s, const RoundArgs& a, int32_t n_open_upper, 
     // shorter, so the minimum strides over it with at most 512 workgroups)
     k_open_min<<<b < 512 ? b : 512, 256, 0, s>>>(a);
     k_pick_i<<<1, 1, 0, s>>>(a);
-    k_flag_group<<<b, 256, 0, s>>>(a);
-    scan_exclusive(s, a.o_keep, a.o_keep, &a.ctl->n_open, n_open_upper, &a.ctl->scan_total[2],
-                   blk);
+    k_flag_group<<<b, 256, 0, s>>>(a, deg);
+    // (places in the group and pair offsets, both over the open list)
+    const ScanJob off{deg, deg, &a.ctl->n_open, &a.ctl->scan_total[3], nullptr, blk + 65536};
+    scan_exclusive2(s, ScanJob{a.o_keep, a.o_keep, &a.ctl->n_open, &a.ctl->scan_total[2], nullptr, blk}, &off,
+                    n_open_upper);
     k_scatter_group<<<b, 256, 0, s>>>(a, deg);
-    k_copy_ngroup<<<1, 1, 0, s>>>(a.ctl);
-    scan_exclusive(s, deg, a.b_off, &a.ctl->n_B, n_open_upper, &a.ctl->scan_total[3],
-                   blk + 65536);
     k_group_finalize<<<1, 1, 0, s>>>(a);
 }
 

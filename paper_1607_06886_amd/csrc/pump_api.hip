@@ -72,7 +72,7 @@ struct pump_ctx {
     // candidates
     int32_t *c_head = nullptr, *c_parent = nullptr, *c_edge = nullptr, *c_step = nullptr,
             *c_pop = nullptr, *c_pos = nullptr;
-    HalfPair* tasks = nullptr;          // simulation queue records
+    HalfPair* tasks = nullptr;          // half-space model: queued pairs
     double* c_cost = nullptr;
     uint32_t* c_mask = nullptr;
     uint8_t* c_flag = nullptr;
@@ -902,13 +902,12 @@ static int explore_single_launch(pump_ctx* ctx) {
 // Mode 2 picks per query: the single launch holds every phase in one kernel
 // at two waves per SIMD and meets at grid barriers, which pays on graphs of
 // a few million edges or less (one query then is a short chain of dependent
-// steps); on larger graphs the particle simulation dominates and its own
-// kernel, at four waves per SIMD with dynamically scheduled workgroups, is
-// faster than the single launch despite a host round trip per round
-// (indoor 20,000-sample query: 13.3 against 19.3 ms; 4,000-sample query:
-// 1.38 against 1.24 ms).  The half-space model's particle work is heavy at
-// any size (4,000-sample query: 9.2 ms per phase against 11.3 ms in one
-// launch), so with it the per-phase kernels are taken throughout.
+// steps); on larger graphs the expansion dominates and its own kernel, at
+// three waves per SIMD, is faster than the single launch despite a host round
+// trip per round (Explore, per phase and in one launch: 7.4 million edges 2.8
+// and 3.6 ms; 11,111-sample roadmap 1.48 and 1.38; 600,000 edges 0.65 and
+// 0.56).  The half-space model's expansion is heavy at any size (600,000 edges:
+// 1.37 and 1.63 ms), so with it the per-phase kernels are taken throughout.
 constexpr long long kPerPhaseEdges = 4ll << 20;
 
 static int effective_mode(const pump_ctx* ctx) {

@@ -268,7 +268,16 @@ void launch_graph_fill_near(hipStream_t s, const float* X, int n_nodes, double r
                             int32_t* esrc, double* etau, double* ecost, int32_t* wstart, int words,
                             int n_edges, const GraphWork& gw);
 
-// The total goes to *total_dev and, if given, also to *total2_dev.
+struct ScanJob {               // an exclusive scan: n entries (on the device) of in to out
+    const int32_t* in;
+    int32_t* out;
+    const int32_t* n;
+    int32_t *total, *total2;   // (total2 may be null)
+    int32_t* blk;              // a word per 1024 entries
+};
+// j0 and, if given, j1 at once; n_upper bounds both lengths.
+void scan_exclusive2(hipStream_t s, const ScanJob& j0, const ScanJob* j1, int32_t n_upper);
+// One array.  The total goes to *total_dev and, if given, also to *total2_dev.
 void scan_exclusive(hipStream_t s, const int32_t* in, int32_t* out, const int32_t* n_dev,
                     int32_t n_upper, int32_t* total_dev, int32_t* blk_scratch,
                     int32_t* total2_dev = nullptr);
@@ -277,7 +286,7 @@ void scan_exclusive(hipStream_t s, const int32_t* in, int32_t* out, const int32_
 // launch's barrier words).
 void launch_explore_init(hipStream_t s, const RoundArgs& a, int n_nodes, int N, unsigned* zero,
                          int n_zero);
-// Half-space model: part 1 the pair stage, 2 the particle stage.  Box model:
+// Half-space model: part 1 the headers, 2 the queued pairs.  Box model:
 // one kernel, in part 2.
 void launch_expand(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, int part);
 void launch_prune(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, int32_t n_open);
@@ -286,7 +295,7 @@ void launch_compact(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs,
 void launch_next_group(hipStream_t s, const RoundArgs& a, int32_t n_open_upper,
                        int32_t* deg_scratch, int32_t* blk_scratch);
 // A round in chunks (a.chunked = 1): chunk_begin sets the chunk's pair count
-// (and empties the simulation queue) before its expansion; stair_update after
+// (and empties the queue of pairs) before its expansion; stair_update after
 // each pass-1 expansion; open_compact once between the passes; chunk_compact
 // after each pass-2 expansion; chunks_finalize at the end.
 void launch_chunk_begin(hipStream_t s, const RoundArgs& a, int32_t n);
