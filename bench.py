@@ -72,13 +72,13 @@ VALU_PEAK_TLANEOPS = 39.3          # 256 CU x 64 lanes x 2.4 GHz (one lane-op pe
 # steer + K (18 + 12 n_obs) + K N (3 + 6 n_near) + K N / 64 with K ~ 10.
 SCOPE_OPS_PER_PAIR = {3: 1.9e3, 20: 8.2e3, 60: 31e3}
 
-# Executed lane-operations of the particle stage, per unit:
+# Algorithmic lane-operations of the expansion's particle tests, per unit:
 OPS_SIM_PAIR = 50      # Hermite coefficients of the queued pair's edge
 OPS_SIM_WP_UNIFORM = 18    # nominal point and cloud box of a tested waypoint ...
 OPS_SIM_WP_PER_BOX = 12    # ... and its overlap test with each obstacle
 OPS_PARTICLE_WP = 3    # particle position at a tested waypoint
 OPS_PARTICLE_BOX = 6   # point-in-box test of a particle (6 compares)
-# ... and of the pair stage / the single launch, per pair:
+# ... and of its pair terms:
 OPS_PAIR = 40          # locate the pair in its group, edge, cost, steps, cutoff, pre-prune lookup
 OPS_GEOM = 150         # + Hermite coefficients, three cubic ranges, cloud boxes per waypoint ...
 OPS_GEOM_PER_BOX = 12  # ... and one box-overlap test per obstacle (pairs past the pre-prune)
@@ -86,7 +86,7 @@ OPS_GEOM_PER_BOX = 12  # ... and one box-overlap test per obstacle (pairs past t
 
 def kernel_models(sc, res, N):
     """Algorithmic lane-operations per query of the kernels the roofline may
-    name (all VALU-bound: see the design doc), from the library's counters of that
+    name (all VALU-bound), from the library's counters of that
     query:
 
     expand_sim (the expansion, per-phase mode): the pair terms below, and per
@@ -101,7 +101,7 @@ def kernel_models(sc, res, N):
            + res["sim_waypoints"] * (OPS_SIM_WP_UNIFORM + OPS_SIM_WP_PER_BOX * sc.n_obs
                                      + N * OPS_PARTICLE_WP)
            + res["sim_box_tests"] * N * OPS_PARTICLE_BOX)
-    # pairs past the pair stage's pre-prune (the particle stage's own
+    # pairs past the headers' pre-prune (the expansion's later
     # pre-prunes are counted with them, so this is a slight undercount)
     geom = max(res["simulated"], res["partial_plans"] - res["preprune"] - res["dropped_steps"])
     pairs = OPS_PAIR * res["partial_plans"] + (OPS_GEOM + OPS_GEOM_PER_BOX * sc.n_obs) * geom
@@ -202,8 +202,8 @@ TRAFFIC_FILES = {
     "explore_single": os.path.join(ROOT, "profiles", "explore_single_indoor_traffic.txt"),
 }
 TRAFFIC_SOURCES = ["paper_1607_06886_amd/csrc/" + f for f in (
-    "kernels_coop.hip", "kernels_explore.hip", "explore_team.hpp", "explore_ops.hpp",
-    "device_math.hpp", "pump_internal.hpp")]
+    "kernels_coop.hip", "kernels_explore.hip", "explore_team.hpp", "explore_ops.hpp", "explore_lane.hpp",
+    "rank_tables.hpp", "box_bins.hpp", "device_math.hpp", "pump_internal.hpp")]
 
 
 def sources_digest():
@@ -517,10 +517,10 @@ def main():
     avg_s = ms_total / 1e3 / launches
     work_launch = work[dom] * args.steps / launches
     achieved = work_launch / avg_s / 1e12
-    # algorithmic HBM bytes of the particle stage per simulated pair: queue
-    # record 32, parent bits N/8, cost 8, count and flag 5, the kept bits N/8,
-    # the head's staircase entries c_cut x 8
-    sim_bytes = r0["simulated"] * (32 + sc.N / 8 + 8 + 5 + sc.N / 8 + 8 * r0["c_cut"])
+    # algorithmic HBM bytes of the expansion per simulated pair: parent bits
+    # N/8, cost 8, count and flag 5, the kept bits N/8, the head's staircase
+    # entries c_cut x 8
+    sim_bytes = r0["simulated"] * (sc.N / 8 + 8 + 5 + sc.N / 8 + 8 * r0["c_cut"])
     expl_ms = sum(kt[k][0] for k in ("expand", "expand_sim", "explore_single")) / args.steps
     roofline = {"bound": "alu", "kernel": dom, "achieved": achieved, "peak": VALU_PEAK_TLANEOPS,
                 "unit": "T lane-ops/s", "frac": achieved / VALU_PEAK_TLANEOPS,
