@@ -900,15 +900,16 @@ static int explore_single_launch(pump_ctx* ctx) {
 }
 
 // Mode 2 picks per query: the single launch holds every phase in one kernel
-// at two waves per SIMD and meets at grid barriers, which pays on graphs of
-// a few million edges or less (one query then is a short chain of dependent
-// steps); on larger graphs the expansion dominates and its own kernel, at
-// three waves per SIMD, is faster than the single launch despite a host round
-// trip per round (Explore, per phase and in one launch: 7.4 million edges 2.8
-// and 3.6 ms; 11,111-sample roadmap 1.48 and 1.38; 600,000 edges 0.65 and
-// 0.56).  The half-space model's expansion is heavy at any size (600,000 edges:
-// 1.37 and 1.63 ms), so with it the per-phase kernels are taken throughout.
-constexpr long long kPerPhaseEdges = 4ll << 20;
+// at two waves per SIMD and meets at grid barriers, which pays on small graphs
+// (one query then is a short chain of dependent steps); on larger ones the
+// expansion dominates and its own kernel, at three waves per SIMD, is faster
+// despite the launches and a host round trip per round.  Whole queries, in one
+// launch and per phase, in ms: 150,000 edges 1.20 and 1.29; 600,000 edges 1.19
+// and 1.21; 930,000 edges 1.39 and 1.35; 1.2 million 2.41 and 2.27; 1.8 million
+// 3.20 and 2.95; 7.4 million 7.2 and 6.1.  The half-space model's expansion is
+// heavy at any size (600,000 edges: Explore 1.63 and 1.37), so with it the
+// per-phase kernels are taken throughout.
+constexpr long long kPerPhaseEdges = 900000;
 
 static int effective_mode(const pump_ctx* ctx) {
     if (ctx->explore_mode != 2) return ctx->explore_mode;
