@@ -27,14 +27,15 @@ __host__ __device__ constexpr size_t team_lds_bytes(int cp_model, int n_obs) {
 
 __device__ __forceinline__ unsigned long long rt_ticks() { return __builtin_amdgcn_s_memrealtime(); }
 
-// Deadline of one wait: the counter is read once every 64 polls.
+// Deadline of one wait: the counter is read at the first poll (a small team's
+// wait may end before the 64th) and then once every 64.
 struct WaitClock {
     unsigned long long t0, limit;
     unsigned polls;
     __device__ __forceinline__ explicit WaitClock(unsigned long long patience)
         : t0(rt_ticks()), limit(patience), polls(0) {}
     __device__ __forceinline__ bool expired() {
-        return (++polls & 63u) == 0u && rt_ticks() - t0 > limit;
+        return (polls++ & 63u) == 0u && rt_ticks() - t0 > limit;
     }
 };
 
