@@ -143,9 +143,12 @@ __device__ __forceinline__ void half_planes(const RoundArgs& a, const HalfStage&
             double reach = 0.0;
             for (int ax = 0; ax < 3; ++ax)
                 reach += fmax(av[ax] * (double)cl[ax], av[ax] * (double)cl[3 + ax]);
-            const double na = sqrt(b);
-            if (reach > b - kFlagEps * na - 1e-12 * (b + 1.0)) {
-                near = true;
+            const double na = sqrt(b), least = b - kFlagEps * na - 1e-12 * (b + 1.0);
+            // (a plane at a right angle to an axis on which the cloud has no
+            // bounds has no reach, 0 times infinity: it marks no waypoint, but at
+            // a marked one the particles are tested against it)
+            near |= reach > least;
+            if (!(reach <= least)) {
                 if (na > 0.0 && first != kRebuild) {
                     const int at = atomicAdd(&l.n_pool, 1);
                     if (at < kHalfPool) {
