@@ -89,27 +89,33 @@ void launch_mc(hipStream_t s, const SelectArgs& a, int32_t n_paths) {
     k_mc<<<grid, kMcThreads, 0, s>>>(a, n_paths);
 }
 
+// A plan's parent has a lower id, so a walk that does not descend ends with no
+// place in the store read past the plan it started from (the store of a query
+// that was refused or gave up is not written throughout).
 __global__ void k_plan_path(const int32_t* __restrict__ p_parent, const int32_t* __restrict__ p_head,
-                            const Ctl* __restrict__ ctl, int32_t plan, int32_t* __restrict__ out,
-                            int32_t cap) {
+                            const Ctl* __restrict__ ctl, int64_t cap_plans, int32_t plan,
+                            int32_t* __restrict__ out, int32_t cap) {
     if (threadIdx.x != 0) return;
-    const int n_plans = ctl->n_plans;
     int n = 0;
-    if (plan < 0 || plan >= n_plans) {
+    if (plan < 0 || plan >= ctl->n_plans || plan >= cap_plans) {
         n = -1;
     } else {
-        for (int p = plan; p >= 0 && n <= n_plans; ++n) {
-            const int head = p_head[p];
+        for (int p = plan, above = plan + 1; p >= 0; ++n) {
+            if (p >= above || n >= cap) {
+                n = cap + 1;
+                break;
+            }
+            above = p;
+            out[1 + n] = p_head[p];
             p = p_parent[p];
-            if (n < cap) out[1 + n] = head;
         }
     }
     out[0] = n;
 }
 
 void launch_plan_path(hipStream_t s, const int32_t* p_parent, const int32_t* p_head, const Ctl* ctl,
-                      int32_t plan, int32_t* out, int32_t cap) {
-    k_plan_path<<<1, 64, 0, s>>>(p_parent, p_head, ctl, plan, out, cap);
+                      int64_t cap_plans, int32_t plan, int32_t* out, int32_t cap) {
+    k_plan_path<<<1, 64, 0, s>>>(p_parent, p_head, ctl, cap_plans, plan, out, cap);
 }
 
 // Alg. 5: with the front sorted by cp_hat, bisect (1-based m) on

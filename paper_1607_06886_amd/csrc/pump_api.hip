@@ -1277,7 +1277,8 @@ int pump_get_path(pump_ctx* ctx, int32_t plan, int32_t* nodes, int32_t cap, int3
     if (plan < 0 || plan >= ctx->ctl_h->n_plans) return fail(ctx, PUMP_E_ARG, "plan id out of range");
     std::lock_guard<std::mutex> lock(ctx->path_mutex);
     const int most = ctx->S_max + 2;   // (an edge is at least a step)
-    launch_plan_path(ctx->stream, ctx->p_parent, ctx->p_head, ctx->ctl, plan, ctx->path_h, most);
+    launch_plan_path(ctx->stream, ctx->p_parent, ctx->p_head, ctx->ctl, ctx->cfg.cap_plans, plan,
+                     ctx->path_h, most);
     HIPCHK(hipStreamSynchronize(ctx->stream));
     HIPCHK(hipGetLastError());
     const int n = ctx->path_h[0];

@@ -190,6 +190,12 @@ int pump_batch_create(const pump_config* cfg_in, int32_t max_queries, void* hip_
         return PUMP_E_HIP;
     }
     b->allocs.push_back(base);
+    // a slot holds no plans until a query of it has been planned
+    if (hipMemset2DAsync(base + (size_t)lay.ctl, slot_bytes, 0, sizeof(Ctl), (size_t)max_queries, b->stream) !=
+        hipSuccess) {
+        pump_batch_destroy(b);
+        return PUMP_E_HIP;
+    }
     b->slots.resize(max_queries);
     for (int i = 0; i < max_queries; ++i) {
         char* sb = base + slot_bytes * (size_t)i;
@@ -458,7 +464,7 @@ int pump_batch_get_path(pump_batch* b, int32_t query, int32_t plan, int32_t* nod
     const Slot& s = b->slots[query];
     std::lock_guard<std::mutex> lock(b->path_mutex);
     const int most = b->cfg.max_steps + 2;   // (an edge is at least a step)
-    launch_plan_path(b->stream, s.p_parent, s.p_head, s.ctl, plan, b->path_h, most);
+    launch_plan_path(b->stream, s.p_parent, s.p_head, s.ctl, b->cfg.cap_plans, plan, b->path_h, most);
     BCHK(hipStreamSynchronize(b->stream));
     BCHK(hipGetLastError());
     const int n = b->path_h[0];

@@ -466,12 +466,12 @@ struct BatchOut {
 };
 
 // Nodes of plan `plan`, last first, to host memory the device can write:
-// out[0] their number (-1: no such plan; over n_plans: a parent cycle), then
-// the first `cap` of them.  With a plan store of 10^5 plans, copying its parent
+// out[0] their number (-1: no such plan; cap + 1: more than `cap`, or a parent
+// that is no earlier plan), then the nodes, at most `cap`.  With a plan store of 10^5 plans, copying its parent
 // and node arrays to walk them on the host took some 50 us a path; the walk
 // here waits for one load a node.
 void launch_plan_path(hipStream_t s, const int32_t* p_parent, const int32_t* p_head, const Ctl* ctl,
-                      int32_t plan, int32_t* out, int32_t cap);
+                      int64_t cap_plans, int32_t plan, int32_t* out, int32_t cap);
 
 // The persistent Explore runs once per particle count present: group g
 // plans the queries of its schedule with `blocks` workgroups of the kernel
