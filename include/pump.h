@@ -400,7 +400,8 @@ int pump_mlp_set_state(pump_mlp* m, const float* params, const float* m1, const 
  * corrections at step t + 1) on the given gradient vector grads [n] (host or
  * device per mem) instead of the network's own; the training step's update. */
 int pump_mlp_adam_step(pump_mlp* m, const float* grads, int64_t n, float lr, int32_t mem);
-/* out [B][208] = network outputs for cond [B][396]. */
+/* out [B][208] = network outputs for cond [B][396]; out may share memory with
+ * cond, whose rows are read before any output is written. */
 int pump_mlp_forward(pump_mlp* m, const float* cond, int32_t B, float* out, int32_t mem);
 /* Mean mixture negative log-likelihood of target states [B][6] and its
  * gradient (flat, same layout as the parameters; grads may be NULL). */

@@ -55,6 +55,12 @@ void forward(pump_mlp* m, const float* X, int B) {
     launch_mlp_forward(m->stream, m->d, X, B, m->Y, kOutPad, kOutPad, B);
 }
 
+// Do the arrays share memory?
+bool overlap(const float* a, size_t na, const float* b, size_t nb) {
+    const uintptr_t pa = reinterpret_cast<uintptr_t>(a), pb = reinterpret_cast<uintptr_t>(b);
+    return pa < pb + nb * sizeof(float) && pb < pa + na * sizeof(float);
+}
+
 // Device address of `scratch` on the current device, looked up on the first
 // call per device and kept for the life of the process.
 constexpr int kMaxDevices = 64;
@@ -235,12 +241,15 @@ int pump_mlp_forward(pump_mlp* m, const float* cond, int32_t B, float* out, int3
     hipError_t e;
     const float* X = stage(m, cond, m->xbuf, (size_t)B * kIn, mem, &e);
     MCHK(e);
-    // (device rows are written where the caller wants them; host rows go
-    // through a packed copy)
-    float* dst = mem == PUMP_MEM_DEVICE ? out : m->Y;
-    launch_mlp_forward(m->stream, m->d, X, B, dst, kOut, kOut, B);
-    if (mem != PUMP_MEM_DEVICE)
-        MCHK(hipMemcpyAsync(out, m->Y, (size_t)B * kOut * 4, hipMemcpyDeviceToHost, m->stream));
+    // Device rows are written where the caller wants them, unless that memory
+    // holds condition rows, which other workgroups may still have to read; those
+    // and host rows go through a packed copy.
+    const bool direct = mem == PUMP_MEM_DEVICE && !overlap(X, (size_t)B * kIn, out, (size_t)B * kOut);
+    launch_mlp_forward(m->stream, m->d, X, B, direct ? out : m->Y, kOut, kOut, B);
+    if (!direct)
+        MCHK(hipMemcpyAsync(out, m->Y, (size_t)B * kOut * 4,
+                            mem == PUMP_MEM_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
+                            m->stream));
     MCHK(hipStreamSynchronize(m->stream));
     MCHK(hipGetLastError());
     return PUMP_OK;
