@@ -75,12 +75,11 @@ __global__ void k_b_cloud(BatchQuery* qs) {
 }
 
 __global__ __launch_bounds__(256) void k_b_rank_tables(BatchQuery* qs, int S1) {
-    __shared__ float s_v[256], s_o[256];
-    __shared__ int s_r[256];
+    __shared__ RankLds s;
     BatchQuery& Q = qs[blockIdx.y];
     if ((int)blockIdx.x * (256 / Q.N) >= 3 * S1) return;
     rank_tables_dev(Q.ra[0].D, Q.ra[0].cloud, const_cast<float*>(Q.ra[0].rank),
-                    const_cast<uint32_t*>(Q.ra[0].prefix), &Q.rank_nan, Q.N, S1, blockIdx.x, s_v, s_o, s_r);
+                    const_cast<uint32_t*>(Q.ra[0].prefix), &Q.rank_nan, Q.N, S1, blockIdx.x, s);
 }
 
 __global__ void k_b_gcloud(BatchQuery* qs, int S1) {

@@ -49,9 +49,8 @@ __global__ __launch_bounds__(256) void k_rank_tables(const float* __restrict__ D
                                                      float* __restrict__ rank,
                                                      uint32_t* __restrict__ prefix,
                                                      int32_t* __restrict__ has_nan, int N, int S1) {
-    __shared__ float s_v[256], s_o[256];
-    __shared__ int s_r[256];
-    rank_tables_dev(D, cloud, rank, prefix, has_nan, N, S1, blockIdx.x, s_v, s_o, s_r);
+    __shared__ RankLds s;
+    rank_tables_dev(D, cloud, rank, prefix, has_nan, N, S1, blockIdx.x, s);
 }
 
 void launch_rank_tables(hipStream_t s, const float* D, const float* cloud, float* rank,

@@ -20,6 +20,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include "pump_internal.hpp"
@@ -46,15 +47,23 @@ struct RankCells {
     }
 };
 
+// LDS of rank_tables_dev (keys and ranks are read 16 bytes at a time).
+struct alignas(16) RankLds {
+    uint32_t key[256];
+    float sorted[256];
+    int rank[256];
+};
+static_assert(offsetof(RankLds, rank) % 16 == 0, "16-byte reads of the ranks");
+
 // The tables of 256 / N columns by one workgroup of 256 threads, thread c * N
-// + j on particle j of the workgroup's column c.  s_v, s_o: 256 floats each,
-// s_r: 256 ints.  cloud: the columns' spans.  *has_nan gets 1 when a deviation is NaN (such a particle is
-// in no prefix set; zeroed before).
+// + j on particle j of the workgroup's column c.  cloud: the columns' spans.
+// *has_nan gets 1 when a deviation is NaN (such a particle is in no prefix set;
+// zeroed before).
 __device__ __forceinline__ void rank_tables_dev(const float* __restrict__ D,
                                                 const float* __restrict__ cloud, float* __restrict__ rank,
                                                 uint32_t* __restrict__ prefix,
                                                 int32_t* __restrict__ has_nan, int N, int S1,
-                                                int block, float* s_v, float* s_o, int* s_r) {
+                                                int block, RankLds& s) {
     const int t = threadIdx.x, c = t / N, j = t - c * N, W = N / 32;
     const int col = block * (256 / N) + c;
     const bool on = col < S1 * 3;
@@ -65,10 +74,9 @@ __device__ __forceinline__ void rank_tables_dev(const float* __restrict__ D,
     const uint32_t u = __float_as_uint(v + 0.0f);
     const uint32_t key = nan ? 0xFFFFFFFFu : (u & 0x80000000u ? ~u : u | 0x80000000u);
     if (nan) atomicOr(has_nan, 1);
-    uint32_t* s_k = reinterpret_cast<uint32_t*>(s_v);
-    s_k[t] = key;
+    s.key[t] = key;
     __syncthreads();
-    const uint4* ck = reinterpret_cast<const uint4*>(s_k + c * N);
+    const uint4* ck = reinterpret_cast<const uint4*>(s.key + c * N);
     int r = 0;
     for (int i = 0; i < N / 4; ++i) {
         const uint4 w = ck[i];
@@ -77,26 +85,26 @@ __device__ __forceinline__ void rank_tables_dev(const float* __restrict__ D,
             r += (w.x == key && 4 * i < j ? 1 : 0) + (w.y == key && 4 * i + 1 < j ? 1 : 0) +
                  (w.z == key && 4 * i + 2 < j ? 1 : 0) + (w.w == key && 4 * i + 3 < j ? 1 : 0);
     }
-    s_o[c * N + r] = nan ? INFINITY : v;
-    s_r[t] = nan ? N : r;   // (prefix sets take particles with s_r < rank)
+    s.sorted[c * N + r] = nan ? INFINITY : v;
+    s.rank[t] = nan ? N : r;   // (prefix sets take the particles below their rank)
     __syncthreads();
     if (!on) return;
     float* row = rank + (size_t)col * rank_row(N);
-    row[j] = s_o[t];
+    row[j] = s.sorted[t];
     // cells after the one of the particle of rank j - 1, up to its own, start
     // at rank j
     {
         const float* cl = cloud + (size_t)(col / 3) * 6 + col % 3;
         const RankCells cells(N, cl[0], cl[3]);
         uint16_t* start = reinterpret_cast<uint16_t*>(row + N);
-        const int mine = cells.of(s_o[t]);
-        const int prev = j > 0 ? cells.of(s_o[t - 1]) : -1;
+        const int mine = cells.of(s.sorted[t]);
+        const int prev = j > 0 ? cells.of(s.sorted[t - 1]) : -1;
         for (int k = prev + 1; k <= mine; ++k) start[k] = (uint16_t)j;
         if (j == N - 1)
             for (int k = mine + 1; k < N; ++k) start[k] = (uint16_t)N;
     }
     // prefix set of rank j, and (threads 0 .. W-1 of the column) of rank N
-    const int4* cr = reinterpret_cast<const int4*>(s_r + c * N);
+    const int4* cr = reinterpret_cast<const int4*>(s.rank + c * N);
     uint32_t* m = prefix + (size_t)col * (N + 1) * W;
     auto word = [&](int w, int rk) {
         uint32_t b = 0u;
