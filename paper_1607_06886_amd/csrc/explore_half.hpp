@@ -284,7 +284,8 @@ __device__ __forceinline__ void half_particles(const RoundArgs& a, const HalfSta
 
 // 1. for pairs [q0, q_end) of the round: the workgroup's passes, strided over G.
 __device__ __forceinline__ void half_headers(const RoundArgs& a, int q0, int q_end, int b, int G, int n_B,
-                                             PairCounts& n) {
+                                             PairTotals* tot) {
+    PairCounts n;
     const int tid = threadIdx.x, lane = tid & 63, T = blockDim.x;
     for (int base = q0 + b * T; base < q_end; base += G * T) {
         const int tile = base + (tid & ~63), q = base + tid;
@@ -301,6 +302,7 @@ __device__ __forceinline__ void half_headers(const RoundArgs& a, int q0, int q_e
         if (lane == 0 && m) at = atomicAdd(&a.ctl->n_tasks, (int)__popcll(m));
         at = __shfl(at, 0, 64) + (int)__popcll(m & lanemask_lt(lane));
         if (go) a.tasks[at] = h;
+        add_counts(tot, n);
     }
 }
 
@@ -308,8 +310,9 @@ __device__ __forceinline__ void half_headers(const RoundArgs& a, int q0, int q_e
 // of the workgroup call it.
 template <int N>
 __device__ __forceinline__ void half_batches(const RoundArgs& a, int n_tasks, int b, int G, const HalfStage& s,
-                                             PairCounts& n) {
+                                             PairTotals* tot) {
     constexpr int W = N / 32;
+    PairCounts n;
     HalfLds& l = *s.l;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, T = blockDim.x;
     // pairs enough for every workgroup, else fewer of them each; some ten
@@ -360,6 +363,7 @@ __device__ __forceinline__ void half_batches(const RoundArgs& a, int n_tasks, in
         }
         for (int i = wave; i < np; i += T >> 6)
             if (l.near[i] != 0u) half_particles<N>(a, s, i, n);
+        add_counts(tot, n);
         __syncthreads();
     }
 }

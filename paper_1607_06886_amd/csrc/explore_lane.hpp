@@ -34,11 +34,31 @@ struct PairRec {
 };
 static_assert(sizeof(PairRec) == 32, "PairRec is two 16-byte LDS words");
 
-// Counters of one wave (the same in every lane, so they stay in scalar
-// registers: sums of ballots).
+// Counters of one wave over a pass (the same in every lane: sums of ballots), and
+// a workgroup's totals, in LDS: a workgroup may carry a whole query, whose
+// waypoints and box tests go past 32 bits (2^26 pairs a round, 32 waypoints each,
+// up to 256 boxes at each).
 struct PairCounts {
     int sim = 0, pre = 0, drop = 0, wp = 0, bt = 0, flag = 0;
 };
+struct PairTotals {
+    unsigned long long sim, pre, drop, wp, bt, flag;
+};
+// (of a pass's at most 1024 records; a few more are carried over)
+static_assert(2048ll * kMaxWaypoints * kMaxObs < (1ll << 31), "a pass's counts fit 32 bits");
+
+// A wave's counters to the totals; they start over.
+__device__ __forceinline__ void add_counts(PairTotals* tot, PairCounts& n) {
+    if ((threadIdx.x & 63) == 0) {
+        if (n.sim) atomicAdd(&tot->sim, (unsigned long long)n.sim);
+        if (n.pre) atomicAdd(&tot->pre, (unsigned long long)n.pre);
+        if (n.drop) atomicAdd(&tot->drop, (unsigned long long)n.drop);
+        if (n.wp) atomicAdd(&tot->wp, (unsigned long long)n.wp);
+        if (n.bt) atomicAdd(&tot->bt, (unsigned long long)n.bt);
+        if (n.flag) atomicAdd(&tot->flag, (unsigned long long)n.flag);
+    }
+    n = PairCounts();
+}
 
 __device__ __forceinline__ int lanes_of(bool b) { return (int)__popcll(__ballot(b)); }
 
@@ -735,13 +755,14 @@ __device__ __forceinline__ void mark_pass(const RoundArgs& a, int first, int tak
 // With fewer, one short pass each, so that every workgroup has some (a few
 // hundred pairs make a whole round of a small query), and several lanes for
 // each record it gets (test_records_wide).  l.cnt is zero on entry and on
-// return.
+// return; the counts are added to tot.
 template <int N>
 __device__ __forceinline__ void expand_box_block(const RoundArgs& a, int q0, int q_end, int rank,
                                                  int size, int n_B, const BoxLds& s, const float* gl,
-                                                 const float* gh, const PairLds& l, PairCounts& n) {
+                                                 const float* gh, const PairLds& l, PairTotals* tot) {
     constexpr int W = N / 32;
     constexpr int kLeast = 8;   // pairs of a short pass
+    PairCounts n;
     const int T = blockDim.x, tid = threadIdx.x;
     const int per = max((q_end - q0 + size - 1) / size, kLeast);
     const bool all_faces = *a.rank_nan != 0;
@@ -757,6 +778,7 @@ __device__ __forceinline__ void expand_box_block(const RoundArgs& a, int q0, int
         int wide = 0;
         while (wide < 4 && (n_list << (wide + 1)) <= T) ++wide;
         test_records_wide<N>(a, s, l, n_list, wide, all_faces, n);
+        add_counts(tot, n);
         __syncthreads();
         if (tid < 3) l.cnt[tid] = 0;
         __syncthreads();
@@ -786,6 +808,7 @@ __device__ __forceinline__ void expand_box_block(const RoundArgs& a, int q0, int
         __syncthreads();
         test_records<N>(a, s, l, l.cnt[1], base < q_end || have > 0, all_faces, nom, c6, acc, hit,
                         cand, wm, st, box, cw, faces, active, close, n);
+        add_counts(tot, n);
         __syncthreads();
         if (tid == 0) {
             l.cnt[0] = have;

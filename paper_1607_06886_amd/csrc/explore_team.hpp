@@ -263,15 +263,14 @@ __device__ __forceinline__ long long block_sum_ll2(long long v, long long* s) {
 // (open_cur -> open_next) and (open_next -> open_cur); they are read through
 // the pointer, so they stay in memory rather than in registers.  The LDS
 // arrays are the caller's: the boxes (s_box, team_lds_bytes), the box model's
-// pair records (pl) and small reduction scratch.
+// pair records (pl), the counters' totals (tot) and small reduction scratch.
 template <int N, int CP>
 __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g, bool init,
-                             int n_nodes, char* s_box, const PairLds& pl, int* s_w,
+                             int n_nodes, char* s_box, const PairLds& pl, PairTotals* tot, int* s_w,
                              unsigned long long* s_m, long long* s_ll, int* s_fail_p) {
     constexpr int W = N / 32;
     unsigned epoch = 0;
     const int G = g.size, b = g.rank, T = blockDim.x, tid = threadIdx.x;
-    const int lane = tid & 63;
     Ctl* c = ra[0].ctl;
     const bool leader = (b == 0 && tid == 0);
     BoxLds box;
@@ -279,6 +278,7 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
     if constexpr (CP == 0) box = stage_box_lds(ra[0], s_box);
     else half = stage_half_lds(ra[0], s_box);
     if (CP == 0 && tid < 3) pl.cnt[tid] = 0;
+    if (tid == 0) *tot = PairTotals{};
     if (init) {
         // the root goes to the list the first round reads (ra[1].open_out)
         explore_init_fill(ra[1], n_nodes, (size_t)b * T + tid, (size_t)G * T);
@@ -297,7 +297,6 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
     int32_t* nxt = g.open_next;
     int par = 0;
     long long kept = 0, partial = 0;
-    PairCounts n;                                            // wave-uniform
     int rounds = 0, err = 0;
     int fail_surv = 0;            // survivors of the round that overflowed the plan store
     // phase wall times seen by the leader (constant-rate real-time counter)
@@ -328,16 +327,16 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         //     barrier).
         if (leader) c->min_cost_bits = 0x7FF0000000000000ull;
         if constexpr (CP == 0) {
-            expand_box_block<N>(a, 0, n_pairs, b, G, n_B, box, gl, gh, pl, n);
+            expand_box_block<N>(a, 0, n_pairs, b, G, n_B, box, gl, gh, pl, tot);
             if (leader) tick(0);
         } else {
-            half_headers(a, 0, n_pairs, b, G, n_B, n);
+            half_headers(a, 0, n_pairs, b, G, n_B, tot);
             if (team_barrier(g, epoch, s_fail_p)) break;
             if (leader) tick(0);
             // (2) the queued pairs' planes and particles
             const int n_tasks =
                 uni(__hip_atomic_load(&c->n_tasks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            half_batches<N>(a, n_tasks, b, G, half, n);
+            half_batches<N>(a, n_tasks, b, G, half, tot);
         }
         if (team_barrier(g, epoch, s_fail_p)) break;
         if (leader) tick(1);
@@ -508,20 +507,14 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         if (leader) tick(6);
     }
     // counters and the final loop state
-    const long long s_sim = block_sum_ll2(lane == 0 ? n.sim : 0, s_ll);
-    const long long s_pre = block_sum_ll2(lane == 0 ? n.pre : 0, s_ll);
-    const long long s_drop = block_sum_ll2(lane == 0 ? n.drop : 0, s_ll);
-    const long long s_flag = block_sum_ll2(lane == 0 ? n.flag : 0, s_ll);
-    const long long s_wp = block_sum_ll2(lane == 0 ? n.wp : 0, s_ll);
-    const long long s_bt = block_sum_ll2(lane == 0 ? n.bt : 0, s_ll);
-    const long long s_kept = block_sum_ll2(kept, s_ll);
+    const long long s_kept = block_sum_ll2(kept, s_ll);   // (and every wave's counts are in)
     if (tid == 0) {
-        if (s_sim) atomicAdd((unsigned long long*)&c->simulated, (unsigned long long)s_sim);
-        if (s_pre) atomicAdd((unsigned long long*)&c->preprune, (unsigned long long)s_pre);
-        if (s_drop) atomicAdd((unsigned long long*)&c->dropped_steps, (unsigned long long)s_drop);
-        if (s_flag) atomicAdd((unsigned long long*)&c->flagged, (unsigned long long)s_flag);
-        if (s_wp) atomicAdd((unsigned long long*)&c->sim_waypoints, (unsigned long long)s_wp);
-        if (s_bt) atomicAdd((unsigned long long*)&c->sim_box_tests, (unsigned long long)s_bt);
+        if (tot->sim) atomicAdd((unsigned long long*)&c->simulated, tot->sim);
+        if (tot->pre) atomicAdd((unsigned long long*)&c->preprune, tot->pre);
+        if (tot->drop) atomicAdd((unsigned long long*)&c->dropped_steps, tot->drop);
+        if (tot->flag) atomicAdd((unsigned long long*)&c->flagged, tot->flag);
+        if (tot->wp) atomicAdd((unsigned long long*)&c->sim_waypoints, tot->wp);
+        if (tot->bt) atomicAdd((unsigned long long*)&c->sim_box_tests, tot->bt);
         if (s_kept) atomicAdd((unsigned long long*)&c->inserted, (unsigned long long)s_kept);
     }
     if (leader) {

@@ -257,6 +257,7 @@ __global__ __launch_bounds__(256, 2) void k_b_explore(BatchQuery* qs, BatchSched
                                                                     int* counter, BatchOut* outs) {
     extern __shared__ __align__(16) char s_box[];
     __shared__ __align__(16) char s_pair[CP == 0 ? pair_lds_bytes(256) : 16];
+    __shared__ PairTotals s_tot;
     __shared__ int s_w[16];
     __shared__ unsigned long long s_m[16];
     __shared__ long long s_ll[16];
@@ -292,7 +293,7 @@ __global__ __launch_bounds__(256, 2) void k_b_explore(BatchQuery* qs, BatchSched
         t.open_cur = Q.open_a;
         t.open_next = Q.open_b;
         t.cap_pairs = Q.cap_pairs;
-        explore_team<N, CP>(Q.ra, t, true, Q.n_nodes, s_box, pair_lds(s_pair, 256), s_w, s_m, s_ll, &s_fail);
+        explore_team<N, CP>(Q.ra, t, true, Q.n_nodes, s_box, pair_lds(s_pair, 256), &s_tot, s_w, s_m, s_ll, &s_fail);
         if (t.rank == 0 && threadIdx.x == 0) {
             const Ctl* c = Q.ra[0].ctl;
             BatchOut& o = outs[qi];

@@ -17,6 +17,7 @@ __global__ __launch_bounds__(coop_threads<N>()) void k_explore_coop(const RoundA
                                                                    CoopArgs ca) {
     extern __shared__ __align__(16) char s_box[];
     __shared__ __align__(16) char s_pair[CP == 0 ? pair_lds_bytes(coop_threads<N>()) : 16];
+    __shared__ PairTotals s_tot;
     __shared__ int s_w[16];
     __shared__ unsigned long long s_m[16];
     __shared__ long long s_ll[16];
@@ -34,7 +35,8 @@ __global__ __launch_bounds__(coop_threads<N>()) void k_explore_coop(const RoundA
     t.open_cur = ca.open_cur;
     t.open_next = ca.open_next;
     t.cap_pairs = ca.cap_pairs;
-    explore_team<N, CP>(ra, t, false, 0, s_box, pair_lds(s_pair, coop_threads<N>()), s_w, s_m, s_ll, &s_fail);
+    explore_team<N, CP>(ra, t, false, 0, s_box, pair_lds(s_pair, coop_threads<N>()), &s_tot, s_w, s_m, s_ll,
+                        &s_fail);
 }
 
 namespace {

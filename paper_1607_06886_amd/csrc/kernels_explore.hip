@@ -231,22 +231,16 @@ static int part_grid(long long n, int per_block) {
 // Cost and CP_hat, then the CP cutoff): explore_lane.hpp (box model),
 // explore_half.hpp (half-space model).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void expand_counts(const RoundArgs& a, const PairCounts& n, long long* s_ll) {
-    // (wave-uniform counts: one lane of each wave brings them)
-    const bool first = (threadIdx.x & 63) == 0;
-    const long long t_sim = block_sum(first ? n.sim : 0, s_ll);
-    const long long t_pre = block_sum(first ? n.pre : 0, s_ll);
-    const long long t_drop = block_sum(first ? n.drop : 0, s_ll);
-    const long long t_flag = block_sum(first ? n.flag : 0, s_ll);
-    const long long t_wp = block_sum(first ? n.wp : 0, s_ll);
-    const long long t_bt = block_sum(first ? n.bt : 0, s_ll);
+// The workgroup's totals to its counter slots (after all of its waves' counts).
+__device__ __forceinline__ void expand_counts(const RoundArgs& a, const PairTotals& tot) {
+    __syncthreads();
     if (threadIdx.x == 0 && !a.quiet) {
-        part_add(a, kPartSimulated, t_sim);
-        part_add(a, kPartPreprune, t_pre);
-        part_add(a, kPartDropped, t_drop);
-        part_add(a, kPartFlagged, t_flag);
-        part_add(a, kPartWaypoints, t_wp);
-        part_add(a, kPartBoxTests, t_bt);
+        part_add(a, kPartSimulated, (long long)tot.sim);
+        part_add(a, kPartPreprune, (long long)tot.pre);
+        part_add(a, kPartDropped, (long long)tot.drop);
+        part_add(a, kPartFlagged, (long long)tot.flag);
+        part_add(a, kPartWaypoints, (long long)tot.wp);
+        part_add(a, kPartBoxTests, (long long)tot.bt);
     }
 }
 
@@ -254,40 +248,41 @@ template <int N>
 __global__ __launch_bounds__(256, 3) void k_expand_box(RoundArgs a) {
     extern __shared__ __align__(16) char s_box[];
     __shared__ __align__(16) char s_pair[pair_lds_bytes(256)];
-    __shared__ long long s_ll[4];
+    __shared__ PairTotals s_tot;
     const BoxLds box = stage_box_lds(a, s_box);
     const PairLds pl = pair_lds(s_pair, 256);
     if (threadIdx.x < 3) pl.cnt[threadIdx.x] = 0;
+    if (threadIdx.x == 0) s_tot = PairTotals{};
     __syncthreads();
     // pairs [a.q0, q_end) of the round: all of them, or one chunk
     const int q_end = a.chunked ? a.q0 + a.ctl->chunk_n : a.ctl->n_pairs;
     float gl[3], gh[3];
     for (int k = 0; k < 3; ++k) { gl[k] = a.gcloud[k]; gh[k] = a.gcloud[3 + k]; }
-    PairCounts n;
-    expand_box_block<N>(a, a.q0, q_end, blockIdx.x, gridDim.x, a.ctl->n_B, box, gl, gh, pl, n);
-    expand_counts(a, n, s_ll);
+    expand_box_block<N>(a, a.q0, q_end, blockIdx.x, gridDim.x, a.ctl->n_B, box, gl, gh, pl, &s_tot);
+    expand_counts(a, s_tot);
 }
 
 __global__ __launch_bounds__(256) void k_half_headers(RoundArgs a) {
-    __shared__ long long s_ll[4];
+    __shared__ PairTotals s_tot;
+    if (threadIdx.x == 0) s_tot = PairTotals{};
+    __syncthreads();
     // pairs [a.q0, q_end) of the round: all of them, or one chunk
     const int q_end = a.chunked ? a.q0 + a.ctl->chunk_n : a.ctl->n_pairs;
-    PairCounts n;
-    half_headers(a, a.q0, q_end, blockIdx.x, gridDim.x, a.ctl->n_B, n);
-    expand_counts(a, n, s_ll);
+    half_headers(a, a.q0, q_end, blockIdx.x, gridDim.x, a.ctl->n_B, &s_tot);
+    expand_counts(a, s_tot);
 }
 
 template <int N>
 __global__ __launch_bounds__(256, N == 256 ? 3 : 4) void k_half_batches(RoundArgs a) {
     extern __shared__ __align__(16) char s_half[];
-    __shared__ long long s_ll[4];
+    __shared__ PairTotals s_tot;
     const int n_tasks = a.ctl->n_tasks;
     if ((int)blockIdx.x * 4 >= n_tasks) return;   // (a batch is at least 4 pairs)
     const HalfStage half = stage_half_lds(a, s_half);
+    if (threadIdx.x == 0) s_tot = PairTotals{};
     __syncthreads();
-    PairCounts n;
-    half_batches<N>(a, n_tasks, blockIdx.x, gridDim.x, half, n);
-    expand_counts(a, n, s_ll);
+    half_batches<N>(a, n_tasks, blockIdx.x, gridDim.x, half, &s_tot);
+    expand_counts(a, s_tot);
 }
 
 // Workgroups of the second part: as many as the CUs hold at once, so that its

@@ -28,3 +28,10 @@ needs_hipcc = pytest.mark.skipif(not os.path.exists(HIPCC), reason="no hipcc")
 def test_rank_table_lds_is_read_16_bytes_at_a_time(tmp_path):
     _holds(tmp_path, "rank_tables.hpp", "alignof(pump::RankLds) >= 16",
            "offsetof(pump::RankLds, key) % 16 == 0", "offsetof(pump::RankLds, rank) % 16 == 0")
+
+
+@needs_hipcc
+def test_expansion_counters_are_64_bits_wide(tmp_path):
+    """One workgroup may carry a whole query (pump_batch_tuning.team_scale 0)."""
+    _holds(tmp_path, "explore_lane.hpp",
+           *[f"sizeof(pump::PairTotals::{k}) == 8" for k in ("sim", "pre", "drop", "wp", "bt", "flag")])
