@@ -9,6 +9,19 @@ namespace pump {
 
 constexpr int kMaxObsWords = 4;   // 64-bit words of a box bit set (256 boxes)
 
+// A value all lanes hold, in scalar registers (loads through a query's record
+// are not known to be uniform).
+template <typename T>
+__device__ __forceinline__ T uniform(T v) {
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+    uint32_t w[sizeof(T) / 4];
+    __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
+    __builtin_memcpy(&v, w, sizeof(T));
+    return v;
+}
+
 // Boundary sums of a connection x0 -> x1:
 //   S_PP = sum P_a^2, S_Pv = sum P_a (v0_a + v1_a), S_vv = sum v0^2 + v0 v1 + v1^2
 // with P = p1 - p0.  The minimum-effort cost of duration tau is

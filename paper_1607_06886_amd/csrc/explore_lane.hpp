@@ -9,7 +9,8 @@
 // pairs reach it.  pair_particles marks a record's waypoints where the
 // particle cloud can meet a box, then takes the marked ones in order: each
 // box's hits come from the rank tables (rank_tables.hpp), a few lane
-// operations per face instead of a test per particle.
+// operations per face instead of a test per particle.  Wide records, whose
+// clouds meet many boxes, are tested by particle all the same (by_particle).
 //
 // Measured on the 20,000-sample indoor query (N = 256, 60 boxes; 1.0e7 pairs,
 // 9.5e6 tested waypoints, 1.1e7 box tests): expansion took 5.5 ms as a pair
@@ -64,16 +65,19 @@ __device__ __forceinline__ int lanes_of(bool b) { return (int)__popcll(__ballot(
 
 enum PairFate : int { kPairGoes = 0, kPairDropped = 1, kPairDominated = 2, kPairNone = 3 };
 
-// The boxes in dynamic LDS: raw faces, faces grown by the guard band, bins.
+// The boxes in dynamic LDS: raw faces, faces grown by the guard band, centres and
+// half extents shrunk by it (c xyz, h - kGuard xyz; their rounding is far below
+// the band), bins.
 struct BoxLds {
     const float* raw;
     const float* out;
+    const float* in;
     BinView bins;
     int n_obs;
 };
 
 __host__ __device__ constexpr size_t box_lds_bytes(int n_obs) {
-    return (size_t)(12 * n_obs + bin_words(n_obs) + 2) * 4;
+    return (size_t)(18 * n_obs + bin_words(n_obs) + 2) * 4;
 }
 
 // Fill by the whole workgroup; a barrier must follow before use.
@@ -84,11 +88,15 @@ __device__ __forceinline__ BoxLds stage_box_lds(const RoundArgs& a, char* mem) {
     const int n_set = bin_words(n_obs) - kBinHeader;
     float* raw = reinterpret_cast<float*>(set + n_set);
     float* out = raw + 6 * n_obs;
+    float* in = out + 6 * n_obs;
     for (int t = threadIdx.x; t < n_set; t += blockDim.x) set[t] = a.bins[kBinHeader + t];
     for (int t = threadIdx.x; t < 6 * n_obs; t += blockDim.x) {
         const float v = a.obs[t];
+        const bool is_lo = t % 6 < 3;
         raw[t] = v;
-        out[t] = t % 6 < 3 ? v - kGuard : v + kGuard;
+        out[t] = is_lo ? v - kGuard : v + kGuard;
+        const float lo = is_lo ? v : a.obs[t - 3], hi = is_lo ? a.obs[t + 3] : v;
+        in[t] = is_lo ? 0.5f * (lo + hi) : 0.5f * (hi - lo) - kGuard;
     }
     for (int k = 0; k < 3; ++k) {
         s.bins.org[k] = __uint_as_float(a.bins[k]);
@@ -98,6 +106,7 @@ __device__ __forceinline__ BoxLds stage_box_lds(const RoundArgs& a, char* mem) {
     s.bins.nw = nw;
     s.raw = raw;
     s.out = out;
+    s.in = in;
     s.n_obs = n_obs;
     return s;
 }
@@ -208,10 +217,13 @@ __device__ __forceinline__ double record_cubics(const RoundArgs& a, const PairRe
 // of particles the parent has not lost, near some face at a marked waypoint
 // and inside no box by more than kFlagEps there.  One pair by the whole wave
 // (wave-uniform arguments), particles l, l + 64, ... on lane l; the pair's
-// cutoff has not been reached, so every marked waypoint counts.
+// cutoff has not been reached, so every marked waypoint counts.  close: the
+// marked waypoints where a face has a particle within kFlagEps.  Mostly such a
+// particle lies far outside the box on another axis, so those waypoints are taken
+// first, and the others only if a particle stays.
 template <int N>
 __device__ __forceinline__ int flagged_count(const RoundArgs& a, const PairRec& rec, uint32_t near,
-                                             const BoxLds& s) {
+                                             uint32_t close, const BoxLds& s) {
     constexpr int W = N / 32, PPL = N >= 64 ? N / 64 : 1;
     const int lane = threadIdx.x & 63;
     const int j0 = N >= 64 ? lane : (lane & (N - 1));
@@ -219,7 +231,14 @@ __device__ __forceinline__ int flagged_count(const RoundArgs& a, const PairRec& 
     Cubic cs[3];
     const double dtk = record_cubics(a, rec, cs);
     uint32_t nm = 0u, dm = 0u;
-    for (uint32_t m = near; m; m &= m - 1u) {
+    bool rest = false;   // past the close waypoints
+    for (uint32_t m = near & close; m || !rest; m &= m - 1u) {
+        if (!m) {
+            if (__ballot(nm != 0u) == 0ull) return 0;
+            rest = true;
+            m = near & ~close;
+            if (!m) break;
+        }
         const int k = __ffs((int)m), st = s_p + k;
         double nom[3];
         float c6[6], lo3[3], hi3[3];
@@ -263,6 +282,206 @@ __device__ __forceinline__ int flagged_count(const RoundArgs& a, const PairRec& 
     return n;
 }
 
+// Lane k's value in every lane (k wave-uniform).
+__device__ __forceinline__ int lane_int(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
+__device__ __forceinline__ double lane_double(double v, int k) {
+    const long long b = __double_as_longlong(v);
+    const int lo = lane_int((int)(unsigned)(b & 0xFFFFFFFFll), k), hi = lane_int((int)(b >> 32), k);
+    return __longlong_as_double(((long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+// ---------------------------------------------------------------------------
+// A record by the whole wave, particles across its lanes (lane l has particles
+// l, l + 64, ..., so the hits of particle row r are one ballot): at each marked
+// waypoint every particle against the boxes that the cloud meets, in FP32 with an
+// FP64 re-test inside the guard band, until the pair reaches the cutoff.  The next
+// waypoint's deviations are asked for before a waypoint is tested.
+//
+// For wide records.  A rank test takes a lane three dependent gathers for each face
+// that cuts the cloud; where a cloud is wider than a box that is most of its six
+// faces, and the lanes of a wave differ in how many boxes they have.  A test by
+// particle is some 14 instructions of the wave for each box and 64 particles.
+// kWideBoxes, the boxes a marked waypoint's bins hold on average from which a record
+// is wide: with 1, 2, 3, 4, 6 and 10, a query with 4.2 boxes a waypoint (3000
+// samples, 60 boxes, 256 particles, sigma 0.08, alpha 0.3) took 13.1, 13.2, 13.2,
+// 13.6, 15.0 and 17.2 ms, one with 1.2 (8000-sample indoor, sigma 0.02) 3.6, 2.8,
+// 2.5, 2.5, 2.5 and 2.5.
+//
+// A round's wide records lie together (pairs of the same plans), so that some
+// workgroups had far more of them than others.  Where half of a round's marked
+// records were wide (Ctl::wide), the next round's go through a queue that the whole
+// device shares, all of them, since a few left to the rank test would end last:
+// that query then takes 8.1 ms, and with sigma 0.2 (18 boxes a waypoint) 6.9 where
+// the rank test alone took 27.5.  Other rounds are spared the further launch or
+// barrier.
+// ---------------------------------------------------------------------------
+template <int N>
+__device__ __forceinline__ void by_particle(const RoundArgs& a, const BoxLds& s, const PairRec& rec, uint32_t near,
+                                            PairCounts& n) {
+    constexpr int W = N / 32, PPL = N >= 64 ? N / 64 : 1;
+    const int lane = threadIdx.x & 63;
+    const bool valid = N >= 64 || lane < N;
+    const int j0 = N >= 64 ? lane : (lane & (N - 1));
+    const int s_p = rec.ks >> 8;
+    uint32_t wm = near;
+    float d[PPL][3], dn[PPL][3];
+    auto ask = [&](int k) {
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax)
+#pragma unroll
+            for (int r = 0; r < PPL; ++r) dn[r][ax] = a.D[((size_t)(s_p + k) * 3 + ax) * N + r * 64 + j0];
+    };
+    ask(__ffs((int)wm));
+    // lane k - 1 holds waypoint k's nominal point
+    double my_nom[3];
+    {
+        Cubic cs[3];
+        const double dtk = record_cubics(a, rec, cs);
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) my_nom[ax] = cs[ax].at((double)(lane + 1) * dtk);
+    }
+    uint32_t par = 0u;   // the parent's bits of this lane's particles
+#pragma unroll
+    for (int r = 0; r < PPL; ++r) {
+        const int j = r * 64 + j0;
+        par |= ((a.p_mask[(size_t)rec.p * W + (j >> 5)] >> (j & 31)) & 1u) << r;
+    }
+    if (!valid) par = 0u;
+    uint32_t hm = 0u, dm = 0u, nm = 0u;   // per particle r: hit, deep, near a face
+    for (;;) {
+        const int k = __ffs((int)wm);
+        wm &= wm - 1u;
+#pragma unroll
+        for (int r = 0; r < PPL; ++r)
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) d[r][ax] = dn[r][ax];
+        if (wm) ask(__ffs((int)wm));
+        ++n.wp;
+        double nom[3];
+        float c6[6], lo3[3], hi3[3];
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) nom[ax] = lane_double(my_nom[ax], k - 1);
+        load_cloud(a.cloud + (size_t)(s_p + k) * 6, c6);
+        cloud_box(nom, c6, lo3, hi3);
+        float y[PPL][3];
+#pragma unroll
+        for (int ax = 0; ax < 3; ++ax) {
+            const float n32 = (float)nom[ax];
+#pragma unroll
+            for (int r = 0; r < PPL; ++r) y[r][ax] = n32 + d[r][ax];
+        }
+        for (int c0 = 0; c0 < s.n_obs; c0 += 64) {
+            const int o = c0 + lane;
+            unsigned long long om = __ballot(o < s.n_obs && boxes_overlap(lo3, hi3, s.out + o * 6));
+            n.bt += (int)__popcll(om);
+            while (om) {
+                const int ob = c0 + __ffsll((long long)om) - 1;
+                om &= om - 1ull;
+                // u = max over axes of |y - c| - (h - g): u <= 0, inside by more
+                // than the guard band (a hit, deep); 0 < u <= 2 g, within it,
+                // decided in FP64 (rare)
+                const float* bc = s.in + ob * 6;
+                const float cx = bc[0], cy = bc[1], cz = bc[2], hx = bc[3], hy = bc[4], hz = bc[5];
+                uint32_t inb = 0u, bnd = 0u;
+#pragma unroll
+                for (int r = 0; r < PPL; ++r) {
+                    const float u = fmaxf(fmaxf(fabsf(y[r][0] - cx) - hx, fabsf(y[r][1] - cy) - hy),
+                                          fabsf(y[r][2] - cz) - hz);
+                    inb |= (u <= 0.0f ? 1u : 0u) << r;
+                    bnd |= (u > 0.0f && u <= 2.0f * kGuard ? 1u : 0u) << r;
+                }
+                hm |= inb;
+                dm |= inb;
+                if (!valid) bnd = 0u;
+                if (__ballot(bnd != 0u) == 0ull) continue;
+                const float* b = s.raw + ob * 6;
+#pragma unroll
+                for (int r = 0; r < PPL; ++r) {
+                    if (!(bnd & (1u << r))) continue;
+                    double dmin = INFINITY;
+#pragma unroll
+                    for (int ax = 0; ax < 3; ++ax) {
+                        // (kept in this branch: without the empty asm the compiler
+                        // takes these FP64 sums before the box loop, for every
+                        // waypoint)
+                        float dv = d[r][ax];
+                        asm volatile("" : "+v"(dv));
+                        const double yy = nom[ax] + (double)dv;
+                        dmin = fmin(dmin, fmin(yy - (double)b[ax], (double)b[3 + ax] - yy));
+                    }
+                    if (dmin >= 0.0) hm |= 1u << r;
+                    if (dmin >= kFlagEps) dm |= 1u << r;
+                    if (fabs(dmin) < kFlagEps) nm |= 1u << r;
+                }
+            }
+        }
+        int cnt = 0;
+#pragma unroll
+        for (int r = 0; r < PPL; ++r) cnt += (int)__popcll(__ballot(valid && (((hm | par) >> r) & 1u)));
+        if (!wm || cnt >= a.c_cut) break;
+    }
+    uint32_t words[W];
+    int popc = 0, flg = 0;
+#pragma unroll
+    for (int r = 0; r < PPL; ++r) {
+        const unsigned long long hb = __ballot(valid && (((hm | par) >> r) & 1u));
+        flg += (int)__popcll(__ballot(valid && (((nm & ~dm & ~par) >> r) & 1u)));
+        popc += (int)__popcll(hb);
+        words[(2 * r) % W] = (uint32_t)hb;
+        if (N >= 64) words[(2 * r + 1) % W] = (uint32_t)(hb >> 32);
+    }
+    const int sl = rec.sl;
+    bool keep = popc < a.c_cut;
+    if (keep) n.flag += flg;   // flagged decisions of pairs below the cut
+    if (keep && a.preprune && stair_get(a.stair, a.stair_w, (int)(rec.nodes >> 16), popc) < rec.cost) {
+        keep = false;
+        ++n.pre;
+    }
+    if (lane == 0) {
+        a.c_flag[sl] = keep ? 1 : 0;
+        a.c_pop[sl] = popc;
+        if (keep) store_set<W>(a.c_mask + (size_t)sl * W, words);
+    }
+}
+
+// The queue's n_tasks records by the waves of G workgroups (this one is b): each
+// wave gathers up to 64 of its records at once, a lane each, from what pair_front
+// and mark_pass left in their slots.
+template <int N>
+__device__ __forceinline__ void queued_by_particle(const RoundArgs& a, int n_tasks, int b, int G, const BoxLds& s,
+                                             PairTotals* tot) {
+    const int lane = threadIdx.x & 63, nw = blockDim.x >> 6;
+    const int waves = G * nw, me = b * nw + (threadIdx.x >> 6);
+    PairCounts n;
+    for (long long base = me; base < n_tasks; base += 64ll * waves) {
+        const long long mine = base + (long long)lane * waves;
+        PairRec r{0.0, 0.0, 0, 0, 0u, 0};
+        int near = 0;
+        if (mine < n_tasks) {
+            r.sl = a.c_pos[mine];
+            near = a.c_pop[r.sl];
+            r.p = a.c_parent[r.sl];
+            r.cost = a.c_cost[r.sl];
+            r.tau = a.etau[a.c_edge[r.sl]];
+            r.nodes = (uint32_t)a.p_head[r.p] | (uint32_t)a.c_head[r.sl] << 16;
+            const int s_p = a.p_step[r.p];
+            r.ks = (a.c_step[r.sl] - s_p) | (s_p << 8);
+        }
+        const int m = (int)min(64ll, (n_tasks - base + waves - 1) / waves);
+        for (int i = 0; i < m; ++i) {
+            PairRec rec;
+            rec.tau = lane_double(r.tau, i);
+            rec.cost = lane_double(r.cost, i);
+            rec.sl = lane_int(r.sl, i);
+            rec.p = lane_int(r.p, i);
+            rec.nodes = (uint32_t)lane_int((int)r.nodes, i);
+            rec.ks = lane_int(r.ks, i);
+            by_particle<N>(a, s, rec, (uint32_t)lane_int(near, i), n);
+        }
+        add_counts(tot, n);
+    }
+}
+
 // Candidate boxes of a waypoint's cloud box, from the bins queried a guard
 // band wider than the grown faces.
 __device__ __forceinline__ void cloud_bins(const BoxLds& s, const float* lo3, const float* hi3,
@@ -288,10 +507,11 @@ __device__ __forceinline__ int next_box(const BoxLds& s, const float* lo3, const
 }
 
 // Marked waypoints of a record, those whose cloud box meets an obstacle, among
-// waypoints k0, k0 + dk, ...
+// waypoints k0, k0 + dk, ...; weight: how many boxes their bins hold (from the
+// first word of the sets with one that the cloud meets).
 __device__ __forceinline__ uint32_t mark_waypoints(const RoundArgs& a, const PairRec& rec,
                                                    const BoxLds& s, const float* gl, const float* gh,
-                                                   int k0, int dk) {
+                                                   int k0, int dk, int& weight) {
     const int K = rec.ks & 255, s_p = rec.ks >> 8;
     const float* cloud = a.cloud + (size_t)s_p * 6;
     float x0[6], x1[6], c6[6];
@@ -330,7 +550,9 @@ __device__ __forceinline__ uint32_t mark_waypoints(const RoundArgs& a, const Pai
         bool meets = false;
         for (int w = 0; w < s.bins.nw && !meets; ++w) {
             unsigned long long m = bin_candidates(s.bins, br, w);
+            const int held = (int)__popcll(m);
             meets = next_box(s, lo3, hi3, w, m) >= 0;
+            weight += meets ? held * (s.bins.nw - w) : 0;
         }
         near |= (meets ? 1u : 0u) << (k - 1);
 #pragma unroll
@@ -393,13 +615,16 @@ __device__ __forceinline__ void face_hits(const RoundArgs& a, const BoxLds& s, c
 // LDS of expand_box_block for a workgroup of T threads.
 struct PairLds {
     PairRec* front;            // [2 T] pairs that passed pair_front (a stack)
-    PairRec* list;             // [T] records whose particles are tested, ...
+    PairRec* list;             // [T] records whose particles are tested (from its end:
+                               // the wide ones), ...
     uint32_t* near;            // [T] ... and their marked waypoints
     PairRec* mine;             // [T] the record each lane is at
     uint32_t* mine_near;       // [T]
-    int* cnt;                  // [3]: stack, list entries, entries taken
+    int* cnt;                  // [6]: stack, list entries, entries taken, the same two of
+                               // the wide records, and the share of those (Ctl::wide)
 };
-constexpr int pair_lds_bytes(int T) { return T * (4 * (int)sizeof(PairRec) + 8) + 16; }
+constexpr int kPairCounters = 6;
+constexpr int pair_lds_bytes(int T) { return T * (4 * (int)sizeof(PairRec) + 8) + 32; }
 
 __device__ __forceinline__ PairLds pair_lds(char* mem, int T) {
     PairLds l;
@@ -425,7 +650,8 @@ __device__ __forceinline__ PairLds pair_lds(char* mem, int T) {
 // A lane's place in its record: nom, c6 the waypoint (step st) and its cloud
 // row; wm the marked waypoints left; cand the boxes of the waypoint still to
 // test in word cw; box, faces the box it is at and its faces still to search;
-// hit that box's hits, acc the parent's bits and the hits so far.  (The
+// hit that box's hits, acc the parent's bits and the hits so far; close the steps
+// (modulo 32) at which a face has a particle within kFlagEps.  (The
 // record's fields stay in LDS and the edge's cubic is taken anew at each
 // waypoint: with both held, 34 registers more, the kernel spilled.)
 //
@@ -439,7 +665,7 @@ __device__ __forceinline__ void test_records(const RoundArgs& a, const BoxLds& s
                                              uint32_t (&acc)[N / 32], uint32_t (&hit)[N / 32],
                                              unsigned long long& cand, uint32_t& wm, int& st,
                                              int& box, int& cw, int& faces, bool& active,
-                                             bool& close, PairCounts& n) {
+                                             uint32_t& close, PairCounts& n) {
     constexpr int W = N / 32;
     constexpr int kRefill = 8, kLow = 40;
     const int lane = threadIdx.x & 63;
@@ -496,12 +722,13 @@ __device__ __forceinline__ void test_records(const RoundArgs& a, const BoxLds& s
         n.pre += lanes_of(dominated);
         // flagged decisions of the pairs below the cut with a particle close
         // to a face, one pair at a time
-        unsigned long long todo = __ballot(ends && close && popc < a.c_cut);
+        unsigned long long todo = __ballot(ends && close != 0u && popc < a.c_cut);
         while (todo) {
             const int src = __ffsll((long long)todo) - 1;
             todo &= todo - 1ull;
-            const int i = (threadIdx.x & ~63) + src;
-            n.flag += flagged_count<N>(a, l.mine[i], l.mine_near[i], s);
+            const int i = (threadIdx.x & ~63) + src, from = ((l.mine[i].ks >> 8) + 1) & 31;
+            const uint32_t c = (uint32_t)__shfl((int)close, src, 64);   // (by step)
+            n.flag += flagged_count<N>(a, l.mine[i], l.mine_near[i], c >> from | c << ((32 - from) & 31), s);
         }
         // new records
         const unsigned long long idle = __ballot(!active);
@@ -518,7 +745,7 @@ __device__ __forceinline__ void test_records(const RoundArgs& a, const BoxLds& s
                 l.mine_near[threadIdx.x] = wm;
                 load_set<W>(a.p_mask + (size_t)rec.p * W, acc);
                 active = true;
-                close = false;
+                close = 0u;
                 box = -1;
             }
         }
@@ -554,7 +781,9 @@ __device__ __forceinline__ void test_records(const RoundArgs& a, const BoxLds& s
         if (active && faces != 0) {
             const int f = __ffs(faces) - 1;
             faces &= faces - 1;
-            face_hits<N>(a, s, nom, c6, st, box, f, hit, close);
+            bool c = false;
+            face_hits<N>(a, s, nom, c6, st, box, f, hit, c);
+            close |= (c ? 1u : 0u) << (st & 31);
         }
     }
     nomv = Vec4d{nom[0], nom[1], nom[2], 0.0};
@@ -570,7 +799,7 @@ __device__ __forceinline__ void test_records(const RoundArgs& a, const BoxLds& s
 // query's expansion (147,743 waypoints of 42,813 pairs in seven rounds) took
 // 1.16 ms a record per lane.
 template <int N>
-__device__ __forceinline__ void test_records_wide(const RoundArgs& a, const BoxLds& s,
+__device__ __forceinline__ void test_records_several(const RoundArgs& a, const BoxLds& s,
                                                   const PairLds& l, int n_list, int sh,
                                                   bool all_faces, PairCounts& n) {
     constexpr int W = N / 32;
@@ -582,7 +811,7 @@ __device__ __forceinline__ void test_records_wide(const RoundArgs& a, const BoxL
     uint32_t wm = go ? l.near[rec_i] : 0u;   // marked waypoints left
     uint32_t acc[W];                         // the parent's bits and the hits so far
     load_set<W>(a.p_mask + (size_t)rec.p * W, acc);
-    bool close_any = false;
+    uint32_t close_at = 0u;                  // waypoints with a particle close to a face
     while (__ballot(go) != 0ull) {
         // this lane's waypoint: the g-th marked one from here on
         uint32_t m = wm;
@@ -650,7 +879,11 @@ __device__ __forceinline__ void test_records_wide(const RoundArgs& a, const BoxL
             for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
             n.bt += v;
         }
-        close_any |= ((uint32_t)(__ballot(counts && close) >> g0) & all) != 0u;
+        if (__ballot(counts && close) != 0ull) {
+            uint32_t c = counts && close ? 1u << (k - 1) : 0u;
+            for (int o = 1; o < G; o <<= 1) c |= (uint32_t)__shfl_xor((int)c, o, 64);
+            close_at |= c;
+        }
 #pragma unroll
         for (int i = 0; i < W; ++i) {
             const uint32_t y = (uint32_t)__shfl((int)sum[i], g0 + max(stop, 0), 64);
@@ -672,12 +905,12 @@ __device__ __forceinline__ void test_records_wide(const RoundArgs& a, const BoxL
             if (keep) store_set<W>(a.c_mask + (size_t)rec.sl * W, acc);
         }
         n.pre += lanes_of(dominated);
-        unsigned long long todo = __ballot(lead && close_any && popc < a.c_cut);
+        unsigned long long todo = __ballot(lead && close_at != 0u && popc < a.c_cut);
         while (todo) {
             const int src = __ffsll((long long)todo) - 1;
             todo &= todo - 1ull;
             const int i = ((threadIdx.x & ~63) + src) >> sh;
-            n.flag += flagged_count<N>(a, l.list[i], l.near[i], s);
+            n.flag += flagged_count<N>(a, l.list[i], l.near[i], (uint32_t)__shfl((int)close_at, src, 64), s);
         }
         go &= !ends;
     }
@@ -705,12 +938,16 @@ __device__ __forceinline__ void front_pass(const RoundArgs& a, int base, int q_e
     if (go) l.front[wb + (int)__popcll(m & lanemask_lt(lane))] = r;
 }
 
+constexpr int kWideBoxes = 3;   // (see by_particle)
+
 // Stack entries first .. first + take - 1 (take <= blockDim.x), 2^sh lanes a
 // record where there are few: their marked waypoints.  Without one the pair
-// keeps its parent's bits and is settled here; the others go to the list.
+// keeps its parent's bits and is settled here; the others go to the list, wide ones
+// to its end (with `ranked` there are none), or with `queue` to the round's queue.
 template <int N>
 __device__ __forceinline__ void mark_pass(const RoundArgs& a, int first, int take, const BoxLds& s,
-                                          const float* gl, const float* gh, const PairLds& l) {
+                                          const float* gl, const float* gh, const PairLds& l,
+                                          bool queue, bool ranked) {
     constexpr int W = N / 32;
     const int T = blockDim.x, tid = threadIdx.x, lane = tid & 63;
     int sh = 0;
@@ -720,11 +957,15 @@ __device__ __forceinline__ void mark_pass(const RoundArgs& a, int first, int tak
     const bool on = i < take;
     PairRec rec;
     uint32_t near = 0u;
+    int weight = 0;
     if (on) {
         rec = l.front[first + i];
-        near = mark_waypoints(a, rec, s, gl, gh, 1 + g, 1 << sh);
+        near = mark_waypoints(a, rec, s, gl, gh, 1 + g, 1 << sh, weight);
     }
-    for (int o = 1; o < (1 << sh); o <<= 1) near |= (uint32_t)__shfl_xor((int)near, o, 64);
+    for (int o = 1; o < (1 << sh); o <<= 1) {
+        near |= (uint32_t)__shfl_xor((int)near, o, 64);
+        weight += __shfl_xor(weight, o, 64);
+    }
     const bool lead = on && g == 0;
     if (lead && near == 0u) {
         uint32_t bits[W];
@@ -734,14 +975,47 @@ __device__ __forceinline__ void mark_pass(const RoundArgs& a, int first, int tak
         store_set<W>(a.c_mask + (size_t)rec.sl * W, bits);
     }
     const bool test = lead && near != 0u;
-    const unsigned long long m = __ballot(test);
+    const bool wide = test && !ranked && weight >= kWideBoxes * (int)__popc(near);
+    const bool front = test && !wide;
+    const unsigned long long m = __ballot(front), wides = __ballot(wide);
+    if (queue) {
+        const unsigned long long all = m | wides;
+        int at = 0;
+        if (lane == 0 && all) {
+            at = atomicAdd(&a.ctl->n_tasks, (int)__popcll(all));
+            atomicAdd(l.cnt + 5, kWideShare * (int)__popcll(wides) - (int)__popcll(all));
+        }
+        at = __shfl(at, 0, 64) + (int)__popcll(all & lanemask_lt(lane));
+        if (test) {
+            a.c_pos[at] = rec.sl;
+            a.c_pop[rec.sl] = (int32_t)near;
+        }
+        return;
+    }
     int wb = 0;
     if (lane == 0 && m) wb = atomicAdd(l.cnt + 1, (int)__popcll(m));
-    wb = __shfl(wb, 0, 64);
+    if (lane == 1 && wides) wb = atomicAdd(l.cnt + 3, (int)__popcll(wides));
+    const int w0 = __shfl(wb, 0, 64), w1 = __shfl(wb, 1, 64);
     if (test) {
-        const int k = wb + (int)__popcll(m & lanemask_lt(lane));
+        const int k = wide ? T - 1 - (w1 + (int)__popcll(wides & lanemask_lt(lane)))
+                           : w0 + (int)__popcll(m & lanemask_lt(lane));
         l.list[k] = rec;
         l.near[k] = near;
+    }
+}
+
+// The wide records at the list's end, a wave each.
+template <int N>
+__device__ __forceinline__ void test_wide(const RoundArgs& a, const BoxLds& s, const PairLds& l, PairCounts& n) {
+    const int n_list = l.cnt[3];
+    if (n_list == 0) return;
+    for (;;) {
+        int i = 0;
+        if ((threadIdx.x & 63) == 0) i = atomicAdd(l.cnt + 4, 1);
+        i = uniform(i);
+        if (i >= n_list) return;
+        const int k = blockDim.x - 1 - i;
+        by_particle<N>(a, s, uniform(l.list[k]), uniform(l.near[k]), n);
     }
 }
 
@@ -754,33 +1028,44 @@ __device__ __forceinline__ void mark_pass(const RoundArgs& a, int first, int tak
 //   3. the particles of those with any, a record per lane (test_records).
 // With fewer, one short pass each, so that every workgroup has some (a few
 // hundred pairs make a whole round of a small query), and several lanes for
-// each record it gets (test_records_wide).  l.cnt is zero on entry and on
-// return; the counts are added to tot.
+// each record it gets (test_records_several).  l.cnt is zero on entry and on
+// return; the counts are added to tot.  With `queue` the marked records are left to
+// queued_by_particle.  With NaN deviations, whose particles only the rank tables
+// leave out, every record is tested by rank.
 template <int N>
 __device__ __forceinline__ void expand_box_block(const RoundArgs& a, int q0, int q_end, int rank,
                                                  int size, int n_B, const BoxLds& s, const float* gl,
-                                                 const float* gh, const PairLds& l, PairTotals* tot) {
+                                                 const float* gh, const PairLds& l, bool queue, PairTotals* tot) {
     constexpr int W = N / 32;
     constexpr int kLeast = 8;   // pairs of a short pass
     PairCounts n;
     const int T = blockDim.x, tid = threadIdx.x;
     const int per = max((q_end - q0 + size - 1) / size, kLeast);
     const bool all_faces = *a.rank_nan != 0;
+    queue &= !all_faces;
+    auto leave = [&]() {   // (one thread, between barriers)
+        if (l.cnt[5] && !all_faces) atomicAdd(&a.ctl->wide, l.cnt[5]);
+        for (int k = 0; k < kPairCounters; ++k) l.cnt[k] = 0;
+    };
     if (per <= T) {
         const int base = q0 + rank * per;
         if (base >= q_end) return;
         q_end = min(q_end, base + per);
         front_pass(a, base, q_end, n_B, l, n);
         __syncthreads();
-        mark_pass<N>(a, 0, l.cnt[0], s, gl, gh, l);
+        mark_pass<N>(a, 0, l.cnt[0], s, gl, gh, l, queue, all_faces);
         __syncthreads();
         const int n_list = l.cnt[1];
-        int wide = 0;
-        while (wide < 4 && (n_list << (wide + 1)) <= T) ++wide;
-        test_records_wide<N>(a, s, l, n_list, wide, all_faces, n);
+        int sh = 0;
+        while (sh < 4 && (n_list << (sh + 1)) <= T) ++sh;
+        test_records_several<N>(a, s, l, n_list, sh, all_faces, n);
+        test_wide<N>(a, s, l, n);
         add_counts(tot, n);
         __syncthreads();
-        if (tid < 3) l.cnt[tid] = 0;
+        if (tid == 0) {
+            if (l.cnt[3]) l.cnt[5] += (kWideShare - 1) * l.cnt[3] - l.cnt[1];
+            leave();
+        }
         __syncthreads();
         return;
     }
@@ -792,7 +1077,8 @@ __device__ __forceinline__ void expand_box_block(const RoundArgs& a, int q0, int
     unsigned long long cand = 0ull;
     uint32_t wm = 0u;
     int st = 0, box = -1, cw = 0, faces = 0;
-    bool active = false, close = false;
+    bool active = false;
+    uint32_t close = 0u;
     int have = 0;   // stack entries (this and base are the same in every thread)
     while (base < q_end || have > 0) {
         while (have < T && base < q_end) {
@@ -804,19 +1090,22 @@ __device__ __forceinline__ void expand_box_block(const RoundArgs& a, int q0, int
         }
         const int take = min(have, T);
         have -= take;
-        mark_pass<N>(a, have, take, s, gl, gh, l);
+        mark_pass<N>(a, have, take, s, gl, gh, l, queue, all_faces);
         __syncthreads();
         test_records<N>(a, s, l, l.cnt[1], base < q_end || have > 0, all_faces, nom, c6, acc, hit,
                         cand, wm, st, box, cw, faces, active, close, n);
+        test_wide<N>(a, s, l, n);
         add_counts(tot, n);
         __syncthreads();
         if (tid == 0) {
             l.cnt[0] = have;
-            l.cnt[1] = 0;
-            l.cnt[2] = 0;
+            if (l.cnt[3]) l.cnt[5] += (kWideShare - 1) * l.cnt[3] - l.cnt[1];
+            for (int k = 1; k < 5; ++k) l.cnt[k] = 0;
         }
         __syncthreads();
     }
+    if (tid == 0) leave();
+    __syncthreads();
 }
 
 }  // namespace pump

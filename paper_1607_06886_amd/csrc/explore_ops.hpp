@@ -68,6 +68,7 @@ __device__ __forceinline__ void explore_init_root(const RoundArgs& a, int N) {
     c->done = c->goal_stop;
     c->err = 0;
     c->n_tasks = 0;
+    c->wide = 0;
     c->simulated = c->preprune = c->inserted = c->dropped_steps = c->flagged = 0;
     c->sim_waypoints = c->sim_box_tests = 0;
 }

@@ -19,11 +19,18 @@
 
 namespace pump {
 
-// Dynamic LDS of a team kernel: the boxes of the largest query (and the
+// Dynamic LDS of a team kernel: the boxes of the largest query (or the
 // half-space model's planes).
 __host__ __device__ constexpr size_t team_lds_bytes(int cp_model, int n_obs) {
     return cp_model == 0 ? box_lds_bytes(n_obs) : half_lds_bytes(n_obs);
 }
+
+// A workgroup's counters, and the phase wall times seen by the leader (constant-rate
+// real-time counter): in LDS, since they outlive every phase.
+struct TeamTotals {
+    PairTotals tot;
+    unsigned long long t_prev, ticks[8];
+};
 
 __device__ __forceinline__ unsigned long long rt_ticks() { return __builtin_amdgcn_s_memrealtime(); }
 
@@ -263,10 +270,10 @@ __device__ __forceinline__ long long block_sum_ll2(long long v, long long* s) {
 // (open_cur -> open_next) and (open_next -> open_cur); they are read through
 // the pointer, so they stay in memory rather than in registers.  The LDS
 // arrays are the caller's: the boxes (s_box, team_lds_bytes), the box model's
-// pair records (pl), the counters' totals (tot) and small reduction scratch.
+// pair records (pl), its totals and small reduction scratch.
 template <int N, int CP>
 __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g, bool init,
-                             int n_nodes, char* s_box, const PairLds& pl, PairTotals* tot, int* s_w,
+                             int n_nodes, char* s_box, const PairLds& pl, TeamTotals* totals, int* s_w,
                              unsigned long long* s_m, long long* s_ll, int* s_fail_p) {
     constexpr int W = N / 32;
     unsigned epoch = 0;
@@ -275,10 +282,12 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
     const bool leader = (b == 0 && tid == 0);
     BoxLds box;
     HalfStage half;
+    bool queue = false;           // box model: marked records of the round are queued
     if constexpr (CP == 0) box = stage_box_lds(ra[0], s_box);
     else half = stage_half_lds(ra[0], s_box);
-    if (CP == 0 && tid < 3) pl.cnt[tid] = 0;
-    if (tid == 0) *tot = PairTotals{};
+    if (CP == 0 && tid < kPairCounters) pl.cnt[tid] = 0;
+    PairTotals* tot = &totals->tot;
+    if (tid == 0) *totals = TeamTotals{};
     if (init) {
         // the root goes to the list the first round reads (ra[1].open_out)
         explore_init_fill(ra[1], n_nodes, (size_t)b * T + tid, (size_t)G * T);
@@ -299,12 +308,10 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
     long long kept = 0, partial = 0;
     int rounds = 0, err = 0;
     int fail_surv = 0;            // survivors of the round that overflowed the plan store
-    // phase wall times seen by the leader (constant-rate real-time counter)
-    unsigned long long t_prev = 0, ticks[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     auto tick = [&](int k) {
-        const unsigned long long now = __builtin_amdgcn_s_memrealtime();
-        ticks[k] += now - t_prev;
-        t_prev = now;
+        const unsigned long long now = rt_ticks();
+        totals->ticks[k] += now - totals->t_prev;
+        totals->t_prev = now;
     };
     __syncthreads();
     while (!done) {
@@ -320,15 +327,25 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         const RoundArgs& a = ra[par];
         partial += n_pairs;
         ++rounds;
-        if (leader) t_prev = __builtin_amdgcn_s_memrealtime();
+        if (leader) totals->t_prev = rt_ticks();
         // (1) expansion, the workgroup's passes strided over the team; the
         //     leader resets the cheapest-open-cost
         //     accumulator of phase 5 (its store is written back at the next
         //     barrier).
         if (leader) c->min_cost_bits = 0x7FF0000000000000ull;
         if constexpr (CP == 0) {
-            expand_box_block<N>(a, 0, n_pairs, b, G, n_B, box, gl, gh, pl, tot);
+            expand_box_block<N>(a, 0, n_pairs, b, G, n_B, box, gl, gh, pl, queue, tot);
             if (leader) tick(0);
+            if (team_barrier(g, epoch, s_fail_p)) break;
+            // (2) the queued records
+            const bool queued = queue;
+            queue = uni(__hip_atomic_load(&c->wide, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >= kWideRecords;
+            if (queued) {
+                const int n_tasks =
+                    uni(__hip_atomic_load(&c->n_tasks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                queued_by_particle<N>(a, n_tasks, b, G, box, tot);
+                if (team_barrier(g, epoch, s_fail_p)) break;
+            }
         } else {
             half_headers(a, 0, n_pairs, b, G, n_B, tot);
             if (team_barrier(g, epoch, s_fail_p)) break;
@@ -337,8 +354,8 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
             const int n_tasks =
                 uni(__hip_atomic_load(&c->n_tasks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             half_batches<N>(a, n_tasks, b, G, half, tot);
+            if (team_barrier(g, epoch, s_fail_p)) break;
         }
-        if (team_barrier(g, epoch, s_fail_p)) break;
         if (leader) tick(1);
         // (3) staircase update (atomic minima only).  The barrier after it
         //     needs no cache maintenance: phase 4 reads the staircase with
@@ -434,7 +451,10 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         // (6) next group index; flag the group and count it per chunk.  The
         //     leader empties the queue for the next round (written back at the
         //     barrier after phase 7).
-        if (leader) c->n_tasks = 0;
+        if (leader) {
+            c->n_tasks = 0;
+            c->wide = 0;
+        }
         if (n_open == 0) {
             done = 1;
             i_cur += 1;
@@ -531,7 +551,7 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
         c->rounds = rounds;
         c->partial = partial;
         c->open_final = (cur == g.open_cur) ? 0 : 1;
-        for (int k = 0; k < 8; ++k) c->phase_ticks[k] += (long long)ticks[k];
+        for (int k = 0; k < 8; ++k) c->phase_ticks[k] += (long long)totals->ticks[k];
     }
 }
 

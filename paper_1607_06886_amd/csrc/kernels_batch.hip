@@ -257,7 +257,7 @@ __global__ __launch_bounds__(256, 2) void k_b_explore(BatchQuery* qs, BatchSched
                                                                     int* counter, BatchOut* outs) {
     extern __shared__ __align__(16) char s_box[];
     __shared__ __align__(16) char s_pair[CP == 0 ? pair_lds_bytes(256) : 16];
-    __shared__ PairTotals s_tot;
+    __shared__ TeamTotals s_tot;
     __shared__ int s_w[16];
     __shared__ unsigned long long s_m[16];
     __shared__ long long s_ll[16];

@@ -17,7 +17,7 @@ __global__ __launch_bounds__(coop_threads<N>()) void k_explore_coop(const RoundA
                                                                    CoopArgs ca) {
     extern __shared__ __align__(16) char s_box[];
     __shared__ __align__(16) char s_pair[CP == 0 ? pair_lds_bytes(coop_threads<N>()) : 16];
-    __shared__ PairTotals s_tot;
+    __shared__ TeamTotals s_tot;
     __shared__ int s_w[16];
     __shared__ unsigned long long s_m[16];
     __shared__ long long s_ll[16];

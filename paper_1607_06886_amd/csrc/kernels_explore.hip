@@ -251,14 +251,28 @@ __global__ __launch_bounds__(256, 3) void k_expand_box(RoundArgs a) {
     __shared__ PairTotals s_tot;
     const BoxLds box = stage_box_lds(a, s_box);
     const PairLds pl = pair_lds(s_pair, 256);
-    if (threadIdx.x < 3) pl.cnt[threadIdx.x] = 0;
+    if (threadIdx.x < kPairCounters) pl.cnt[threadIdx.x] = 0;
     if (threadIdx.x == 0) s_tot = PairTotals{};
     __syncthreads();
     // pairs [a.q0, q_end) of the round: all of them, or one chunk
     const int q_end = a.chunked ? a.q0 + a.ctl->chunk_n : a.ctl->n_pairs;
     float gl[3], gh[3];
     for (int k = 0; k < 3; ++k) { gl[k] = a.gcloud[k]; gh[k] = a.gcloud[3 + k]; }
-    expand_box_block<N>(a, a.q0, q_end, blockIdx.x, gridDim.x, a.ctl->n_B, box, gl, gh, pl, &s_tot);
+    expand_box_block<N>(a, a.q0, q_end, blockIdx.x, gridDim.x, a.ctl->n_B, box, gl, gh, pl, a.queue != 0,
+                        &s_tot);
+    expand_counts(a, s_tot);
+}
+
+template <int N>
+__global__ __launch_bounds__(256, 4) void k_by_particle(RoundArgs a) {
+    extern __shared__ __align__(16) char s_box[];
+    __shared__ PairTotals s_tot;
+    const int n_tasks = a.ctl->n_tasks;
+    if ((int)blockIdx.x * 4 >= n_tasks) return;
+    const BoxLds box = stage_box_lds(a, s_box);
+    if (threadIdx.x == 0) s_tot = PairTotals{};
+    __syncthreads();
+    queued_by_particle<N>(a, n_tasks, blockIdx.x, gridDim.x, box, &s_tot);
     expand_counts(a, s_tot);
 }
 
@@ -289,15 +303,19 @@ __global__ __launch_bounds__(256, N == 256 ? 3 : 4) void k_half_batches(RoundArg
 // batches are even (a workgroup per 32 pairs with their headers: 1.34 ms
 // instead of 0.95 on the case above; 768 workgroups, some 100 pairs each: 1.75).
 constexpr int kHalfGrid = 1024;
+constexpr int kParticleGrid = 1024;   // likewise of the queued records
 
 // part 1: the half-space model's headers; part 2: the rest (all of the box
 // model's expansion).
 template <int N>
 static void launch_expand_n(hipStream_t s, const RoundArgs& a, int32_t n_pairs, int part) {
     if (a.cp_model == 0) {
-        if (part & 2)
+        if (part & 2) {
             k_expand_box<N><<<(unsigned)std::min(part_grid(n_pairs, 16), kBoxGrid), 256,
                               box_lds_bytes(a.n_obs), s>>>(a);
+            if (a.queue)
+                k_by_particle<N><<<kParticleGrid, 256, box_lds_bytes(a.n_obs), s>>>(a);
+        }
         return;
     }
     if (part & 1) k_half_headers<<<part_grid(n_pairs, 256), 256, 0, s>>>(a);
@@ -416,6 +434,7 @@ void launch_compact(hipStream_t s, const RoundArgs& a, int N, int32_t n_pairs, i
 __global__ void k_chunk_begin(Ctl* c, int32_t n) {
     c->chunk_n = n;
     c->n_tasks = 0;
+    c->wide = 0;
 }
 
 __global__ __launch_bounds__(256) void k_mark_open_only(RoundArgs a) {
@@ -554,6 +573,8 @@ __global__ __launch_bounds__(256) void k_scatter_group(RoundArgs a, const int32_
 
 __global__ void k_group_finalize(RoundArgs a) {
     Ctl* c = a.ctl;
+    c->last_wide = c->wide;
+    c->wide = 0;
     if (c->done) {
         c->n_B = 0;
         c->n_pairs = 0;

@@ -727,6 +727,7 @@ int pump_explore_round(pump_ctx* ctx, int32_t* done) {
     const int32_t n_pairs = ctx->ctl_h->n_pairs;
     const int32_t n_open = ctx->ctl_h->n_open;
     RoundArgs a = round_args(ctx);
+    a.queue = ctx->cfg.cp_model == 0 && ctx->ctl_h->last_wide >= kWideRecords ? 1 : 0;
     const long long slots = ctx->cfg.cap_pairs;
     if ((long long)n_pairs <= slots) {
         if (ctx->cfg.cp_model == 1) {

@@ -23,6 +23,9 @@ constexpr int kMaxGoal = 1 << 16;     // goal plans gathered for selection
 // error of a position of magnitude <= 16).
 constexpr float kGuard = 6.103515625e-05f;
 constexpr double kFlagEps = 1e-5;     // face distance counted as a flagged decision
+// A round queues its records if half of those marked in the round before were wide,
+// and some hundreds more (see Ctl::wide).
+constexpr int kWideShare = 2, kWideRecords = 256;
 constexpr double kTauMin = 1e-6;      // connections shorter than this are skipped
 
 enum PlanState : uint8_t { kOpen = 0, kClosed = 1, kRemoved = 2 };
@@ -61,7 +64,11 @@ struct Ctl {
     int32_t n_surv;
     int32_t n_goal;
     int32_t n_front;
-    int32_t n_tasks;           // pairs queued for particle simulation this round
+    int32_t n_tasks;           // records queued this round
+    // box model: kWideShare times the wide records (explore_lane.hpp) less all that
+    // were marked (without the queue: in passes with a wide one), of this round and,
+    // with a launch per phase, of the last one
+    int32_t wide, last_wide;
     int32_t pad_;
     unsigned long long min_cost_bits;
     long long simulated;
@@ -132,6 +139,7 @@ struct RoundArgs {
     int32_t c_cut, c_min;
     double h;                  // lambda * r_n
     int32_t preprune;
+    int32_t queue;             // box model, a launch per phase: marked records are queued
     int32_t cp_model;          // exploration collision model: 0 box, 1 half-space (HSMC)
     // graph
     const int32_t* row_ptr;

@@ -308,19 +308,6 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// A value all lanes hold, in scalar registers (loads through a query's record
-// are not known to be uniform).
-template <typename T>
-__device__ __forceinline__ T uniform(T v) {
-    static_assert(sizeof(T) % 4 == 0, "whole words");
-    uint32_t w[sizeof(T) / 4];
-    __builtin_memcpy(w, &v, sizeof(T));
-#pragma unroll
-    for (size_t i = 0; i < sizeof(T) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
-    __builtin_memcpy(&v, w, sizeof(T));
-    return v;
-}
-
 // Append `ok` items of a wave to a list: one atomic per wave (all 64 lanes
 // call it).  Returns the slot of this lane's item.
 __device__ __forceinline__ int wave_append(bool ok, int32_t* counter) {
