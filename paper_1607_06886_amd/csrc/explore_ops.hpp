@@ -238,13 +238,8 @@ __device__ __forceinline__ bool flag_group_one(const RoundArgs& a, int i, double
     return inB && a.goal[a.p_head[p]] && a.p_pop[p] < a.c_min;
 }
 
-__device__ __forceinline__ void scatter_group_one(const RoundArgs& a, int i, int32_t* deg) {
-    if (!a.o_inB[i]) return;
-    const int p = a.open_out[i];
-    const int pos = a.o_keep[i];
-    const int h = a.p_head[p];
-    a.b_ids[pos] = p;
-    deg[pos] = a.row_ptr[h + 1] - a.row_ptr[h];
+__device__ __forceinline__ void scatter_group_one(const RoundArgs& a, int i) {
+    if (a.o_inB[i]) a.b_ids[a.o_keep[i]] = a.open_out[i];
 }
 
 }  // namespace pump

@@ -56,7 +56,6 @@ struct TeamCtx {
     int rank, size;
     unsigned long long* xa;    // [size] exchanged chunk totals, tagged (team_exchange)
     unsigned long long* xb;    // [size]
-    int32_t* b_deg;            // group degrees (scatter output)
     int32_t* open_cur;         // open list read by the first round
     int32_t* open_next;
     int64_t cap_pairs;
@@ -518,7 +517,7 @@ __device__ void explore_team(const RoundArgs* __restrict__ ra, const TeamCtx& g,
             }
         }
         __syncthreads();
-        for (int t = n_lo + tid; t < n_hi; t += T) scatter_group_one(a, t, g.b_deg);
+        for (int t = n_lo + tid; t < n_hi; t += T) scatter_group_one(a, t);
         if (leader) a.b_off[nB] = n_pairs_next;
         n_B = nB;
         n_pairs = n_pairs_next;

@@ -289,7 +289,6 @@ __global__ __launch_bounds__(256, 2) void k_b_explore(BatchQuery* qs, BatchSched
         t.arrive = Q.team_sync + 64;
         t.xa = Q.team_tot;
         t.xb = Q.team_tot + kMaxTeam;
-        t.b_deg = Q.b_deg;
         t.open_cur = Q.open_a;
         t.open_next = Q.open_b;
         t.cap_pairs = Q.cap_pairs;

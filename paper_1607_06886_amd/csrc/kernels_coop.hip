@@ -31,7 +31,6 @@ __global__ __launch_bounds__(coop_threads<N>()) void k_explore_coop(const RoundA
     t.size = gridDim.x;
     t.xa = ca.xa;
     t.xb = ca.xb;
-    t.b_deg = ca.b_deg;
     t.open_cur = ca.open_cur;
     t.open_next = ca.open_next;
     t.cap_pairs = ca.cap_pairs;

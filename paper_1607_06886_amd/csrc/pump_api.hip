@@ -72,7 +72,7 @@ struct pump_ctx {
     // candidates
     int32_t *c_head = nullptr, *c_parent = nullptr, *c_edge = nullptr, *c_step = nullptr,
             *c_pop = nullptr, *c_pos = nullptr;
-    HalfPair* tasks = nullptr;          // half-space model: queued pairs
+    HalfPair* tasks = nullptr;          // queued pairs (half-space model only)
     double* c_cost = nullptr;
     uint32_t* c_mask = nullptr;
     uint8_t* c_flag = nullptr;
@@ -462,7 +462,7 @@ int pump_create(const pump_config* cfg_in, void* hip_stream, pump_ctx** out) {
     A(dalloc(&ctx->c_step, Q));
     A(dalloc(&ctx->c_pop, Q));
     A(dalloc(&ctx->c_pos, Q));
-    A(dalloc(&ctx->tasks, Q));
+    if (cfg.cp_model == 1) A(dalloc(&ctx->tasks, Q));
     A(dalloc(&ctx->c_cost, Q));
     A(dalloc(&ctx->c_mask, Q * ctx->W));
     A(dalloc(&ctx->c_flag, Q));
@@ -836,7 +836,6 @@ static int explore_single_enqueue(pump_ctx* ctx) {
     ca.sync.patience = ctx->patience;
     ca.xa = reinterpret_cast<unsigned long long*>(ctx->coop_sync + 64 + 4096);
     ca.xb = ca.xa + blocks;
-    ca.b_deg = ctx->b_deg;
     ca.open_cur = ctx->open_cur;
     ca.open_next = ctx->open_next;
     ca.cap_pairs = ctx->cfg.cap_pairs;

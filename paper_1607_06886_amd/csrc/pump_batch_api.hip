@@ -32,7 +32,7 @@ struct Slot {
     uint8_t *valid, *goal, *p_state, *o_inB, *c_flag;
     uint32_t *ebits, *p_mask, *c_mask;
     int32_t *wstart, *deg, *row_ptr, *col, *esrc, *p_head, *p_parent, *p_edge, *p_step, *p_pop, *p_round;
-    int32_t *open_a, *open_b, *o_keep, *b_ids, *b_off, *b_deg;
+    int32_t *open_a, *open_b, *o_keep, *b_ids, *b_off;
     int32_t *c_head, *c_parent, *c_edge, *c_step, *c_pop, *c_pos;
     HalfPair* tasks;
     int32_t *goal_ids, *front_ids, *paths, *path_len, *wp_len, *mc_counts;
@@ -161,9 +161,9 @@ int pump_batch_create(const pump_config* cfg_in, int32_t max_queries, void* hip_
     take(&lay.p_pop, P); take(&lay.p_round, P); take(&lay.p_cost, P); take(&lay.p_mask, P * W);
     take(&lay.p_state, P); take(&lay.stair, nn * (N + 1)); take(&lay.open_a, P);
     take(&lay.open_b, P); take(&lay.o_keep, P); take(&lay.o_inB, P); take(&lay.b_ids, P + 1);
-    take(&lay.b_off, P + 1); take(&lay.b_deg, P + 1); take(&lay.c_head, Q); take(&lay.c_parent, Q);
+    take(&lay.b_off, P + 1); take(&lay.c_head, Q); take(&lay.c_parent, Q);
     take(&lay.c_edge, Q); take(&lay.c_step, Q); take(&lay.c_pop, Q); take(&lay.c_pos, Q);
-    take(&lay.tasks, Q); take(&lay.c_cost, Q); take(&lay.c_mask, Q * W); take(&lay.c_flag, Q);
+    take(&lay.tasks, cfg.cp_model == 1 ? Q : 1); take(&lay.c_cost, Q); take(&lay.c_mask, Q * W); take(&lay.c_flag, Q);
     take(&lay.goal_ids, (size_t)kMaxGoal); take(&lay.front_ids, kBatchFrontHost);
     take(&lay.paths, (size_t)kBatchFrontHost * (S + 1)); take(&lay.path_len, kBatchFrontHost);
     take(&lay.wp_len, kBatchFrontHost); take(&lay.mc_counts, kBatchFrontHost);
@@ -287,7 +287,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         }
         Q.X = s.X; Q.obs = s.obs; Q.valid = s.valid; Q.goal = s.goal; Q.ebits = s.ebits;
         Q.wstart = s.wstart; Q.deg = s.deg; Q.row_ptr = s.row_ptr; Q.col = s.col; Q.esrc = s.esrc; Q.etau = s.etau;
-        Q.ecost = s.ecost; Q.b_deg = s.b_deg; Q.open_a = s.open_a; Q.open_b = s.open_b;
+        Q.ecost = s.ecost; Q.open_a = s.open_a; Q.open_b = s.open_b;
         RoundArgs& a = Q.ra[0];
         a.X = s.X; a.goal = s.goal; a.obs = s.obs; a.n_obs = pr.n_obs; a.D = s.D; a.cloud = s.cloud;
         a.gcloud = s.gcloud; a.rank = s.rank; a.prefix = s.prefix; a.bins = s.bins;

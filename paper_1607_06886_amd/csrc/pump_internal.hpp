@@ -108,6 +108,7 @@ struct HalfPair {
     uint32_t nodes;            // edge endpoints: head | x << 16 (node ids < 65536)
     int32_t K, s_p;            // waypoints on the edge (at most 32), parent's step count
 };
+static_assert(sizeof(HalfPair) == 32, "a queued pair is two 16-byte words");
 
 // Counter partials of the per-phase Explore kernels: workgroup b of a kernel
 // adds its sums to part[b * kPartK + k] (its own slot, no atomics), and one
@@ -176,7 +177,7 @@ struct RoundArgs {
     uint32_t* c_mask;
     uint8_t* c_flag;
     int32_t* c_pos;            // scan input/output over the pairs
-    HalfPair* tasks;            // pairs queued for particle simulation
+    HalfPair* tasks;           // queued pairs (half-space model only)
     Ctl* ctl;
     // a round run in chunks (more pairs than candidate slots): pair q of the
     // round is slot q - q0 (q0 = 0 otherwise); quiet = 1 in the second pass
@@ -393,7 +394,6 @@ struct CoopArgs {
     CoopSync sync;
     unsigned long long* xa;    // [grid] exchanged chunk totals (zero at launch)
     unsigned long long* xb;    // [grid]
-    int32_t* b_deg;            // group degrees (scatter output)
     int32_t* open_cur;         // open list read by the first round
     int32_t* open_next;
     int64_t cap_pairs;
@@ -442,7 +442,6 @@ struct BatchQuery {
     int32_t* esrc;
     double* etau;
     double* ecost;
-    int32_t* b_deg;
     int32_t* open_a;
     int32_t* open_b;
     double* dev_scratch;       // deviation-table chunk states
