@@ -458,7 +458,9 @@ typedef struct pump_batch_tuning {
     int32_t team_scale;      /* workgroups per query: 0 = one; 1..256: k/4 times the
                                 query's share of the estimated work (samples^2 x
                                 sqrt(particles)) of all workgroups, at most 64
-                                workgroups per team */
+                                workgroups per team; with 64, the default, also no
+                                more than 3 times that share or nodes^2 / 250,000,
+                                whichever is more */
 } pump_batch_tuning;
 
 /* Allocate per-query workspaces for up to max_queries queries, each sized by
@@ -472,8 +474,7 @@ int pump_batch_destroy(pump_batch* b);
  * the device, read only, kept alive until the call returns); n_particles[i]
  * is that query's N (32/64/128/256, at most cfg.n_particles; noise arrays are
  * [S_max][6][N] for that N).  tune may be NULL (256 threads, 2 per CU,
- * largest first, graph on, team_scale 64, with
- * smaller teams where a team's queries share the device).  out[i] receives query i's result; the returned
+ * largest first, graph on, team_scale 64).  out[i] receives query i's result; the returned
  * code is PUMP_OK or the first negative per-query status.  ms_total holds the
  * wall time of the whole batch. */
 int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_particles,
@@ -491,7 +492,7 @@ int pump_batch_set_roadmaps(pump_batch* b, const pump_roadmap* const* rms, int32
 int pump_batch_get_path(pump_batch* b, int32_t query, int32_t plan, int32_t* nodes, int32_t cap,
                         int32_t* len);
 /* Autotuner: time every persistent-kernel shape (threads x workgroups per CU x
- * team scale, largest first, graph on) on these queries, check that every shape returns the same
+ * team scale, largest first, graph on; the default shape among them) on these queries, check that every shape returns the same
  * per-query results, write the timings as JSON to json_path (if not NULL)
  * and return the fastest shape and its time. */
 int pump_batch_tune(pump_batch* b, const pump_problem* probs, const int32_t* n_particles,

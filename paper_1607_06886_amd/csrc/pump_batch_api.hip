@@ -14,6 +14,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "batch_schedule.hpp"
 #include "box_bins.hpp"
 #include "host_consts.hpp"
 #include "pump_internal.hpp"
@@ -221,9 +222,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
     if (!b || !probs || !n_particles || q < 1) return PUMP_E_ARG;
     if (q > b->max_q) return bfail(b, PUMP_E_ARG, "more queries than max_queries");
     const pump_config& cfg = b->cfg;
-    pump_batch_tuning t;
-    if (tune) t = *tune;
-    else { t.explore_threads = 256; t.blocks_per_cu = 2; t.order = 1; t.use_graph = 1; t.team_scale = 64; }
+    const pump_batch_tuning t = tuning_or_default(tune);
     if (t.explore_threads != 256 ||
         t.blocks_per_cu < 1 || t.blocks_per_cu > 8 || t.team_scale < 0 || t.team_scale > 256)
         return bfail(b, PUMP_E_ARG, "bad tuning");
@@ -327,17 +326,10 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         work[i] = (double)Q.n_nodes * Q.n_nodes * sqrt((double)N);
     }
     // Schedules of the persistent Explore kernels, one per particle count:
-    // entries in input order or largest first; entry i gets a team of
-    // workgroups in proportion to its share of its group's estimated work
-    // (team_scale / 4 times the proportional share; 0 = one workgroup per
-    // query).  Without a tuning a team is also no larger than three times that
-    // share, or than its query has use for beside others (16 workgroups at 2000
-    // samples, and with their square), whichever is more: what a round's
-    // barriers cost grows with the team.  With 16 times the share throughout, 96
-    // queries of 2000 samples took 11.1 ms, now 7.7 (1.5 times the share: 7.2;
-    // but 64 queries of 1000 to 8000 samples then take 29.3 instead of 28.3, as
-    // now, since a heavy one ends last); few queries keep the whole device.  Teams need every workgroup of a launch resident at once, so
-    // each launch is capped by its kernel's occupancy.
+    // entries in input order or largest first; entry i gets a team of workgroups
+    // by its share of its group's estimated work (batch_schedule.hpp).  Teams need
+    // every workgroup of a launch resident at once, so each launch is capped by its
+    // kernel's occupancy.
     std::vector<int> order, off;
     order.reserve(q);
     off.reserve(q + kBatchGroups);
@@ -363,16 +355,7 @@ int pump_batch_plan(pump_batch* b, const pump_problem* probs, const int32_t* n_p
         const int e0 = (int)order.size(), f0 = (int)off.size();
         off.push_back(0);
         for (int i : mem) {
-            int size = 1;
-            if (t.team_scale > 0 && wsum > 0.0) {
-                const double share = 0.25 * t.team_scale * grid * work[i] / wsum;
-                size = (int)std::min<double>(std::max(1.0, floor(share + 0.5)), (double)team_cap);
-                if (!tune) {
-                    const double prop = 3.0 * grid * work[i] / wsum;
-                    const double useful = (double)b->qs[i].n_nodes * b->qs[i].n_nodes / 2.5e5;
-                    size = std::min(size, (int)std::max(1.0, std::max(prop, useful)));
-                }
-            }
+            const int size = team_size(t.team_scale, grid, team_cap, work[i], wsum, b->qs[i].n_nodes);
             order.push_back(i);
             off.push_back(off.back() + size);
         }
@@ -481,10 +464,10 @@ int pump_batch_tune(pump_batch* b, const pump_problem* probs, const int32_t* n_p
     if (!b || !probs || !n_particles || !best) return PUMP_E_ARG;
     const int threads[1] = {256};
     const int per_cu[3] = {1, 2, 4};
-    const int scales[3] = {16, 64, 256};
+    const int scales[3] = {16, kDefaultTeamScale, 256};
     std::vector<pump_result> ref(q), cur(q);
     double bms = 1e30;
-    pump_batch_tuning bt{256, 2, 1, 1, 64};
+    pump_batch_tuning bt = tuning_or_default(nullptr);
     std::string js = "{\"candidates\": [";
     bool first = true;
     bool have_ref = false;
