@@ -93,7 +93,9 @@ __device__ __forceinline__ int half_header(const RoundArgs& a, int q, int lo, in
     return 1;
 }
 
-// The nominal position and velocity at waypoint k of the pair in slot i.
+// The nominal position and velocity at waypoint k of the pair in slot i.  At a
+// node at rest the velocity is zero but for its rounding, whose direction
+// decides the plane that eq. (7) leaves: its form is written out.
 __device__ __forceinline__ void half_waypoint(const HalfLds& l, int i, double tau, int K, int k, double* y,
                                               double* v) {
     const double t = ((double)k * tau) / (double)K;
@@ -102,7 +104,7 @@ __device__ __forceinline__ void half_waypoint(const HalfLds& l, int i, double ta
         const Cubic c{(double)l.c01[i][2 * ax], (double)l.c01[i][2 * ax + 1], l.c23[i][2 * ax],
                       l.c23[i][2 * ax + 1]};
         y[ax] = c.at(t);
-        v[ax] = c.slope(t);
+        v[ax] = fma(t, fma(t * 3.0, c.c3, 2.0 * c.c2), c.c1);
     }
 }
 
