@@ -323,11 +323,12 @@ int pump_sample_halton(int32_t n, int32_t n_goal, const float* lo, const float* 
  *   5 compact (scans + scatter)   6 next group (min, flags, scans)
  *   7 front selection   8 MC certification   9 Explore as one launch
  *   10..16 phases of the single-launch Explore as seen by its first
- *   workgroup (expand, simulate, staircase, marks, scans + compaction,
+ *   workgroup (expand, queued pairs, staircase, marks, scans + compaction,
  *   next group, group scatter + pair offsets; each includes its barrier;
  *   "launches" counts rounds)   17 Smooth (all of its launches)
  *   18 expand, batches of queued pairs (per-phase mode; with the box model
- *   the whole expansion, and nothing is timed under 3)
+ *   the whole expansion, queued records included, and nothing is timed
+ *   under 3)
  * pump_set_timing(ctx, on) switches it and clears the totals;
  * pump_get_timing copies min(n, PUMP_TIMING_KINDS) totals (ms) and launch
  * counts (either pointer may be NULL). */
@@ -340,11 +341,12 @@ int pump_get_timing(pump_ctx* ctx, double* ms, int64_t* launches, int32_t n);
  * at grid-wide barriers; mode 0 launches each phase of each round separately
  * and reads the loop state back after every round (as pump_explore_round
  * always does); mode 2 (the default where the single launch fits) chooses
- * per query from the graph's edge count: the single launch below 4 * 2^20
- * edges, per-phase launches from there on, where the particle simulation's
- * own kernel is faster, and per-phase launches at any size with the
- * half-space model (cp_model 1).  All modes build the same plan store.  get
- * reports the configured mode and the workgroups of the single launch. */
+ * per query from the graph's edge count: the single launch below 900,000
+ * edges, per-phase launches from there on, where the expansion's own kernel
+ * is faster, and per-phase launches at any size with the half-space model
+ * (cp_model 1).  All modes build the same plan store.  get reports the
+ * configured mode and the most workgroups the single launch may take (a query
+ * takes one per 512 of its graph's edges, at least 16 and at most that). */
 int pump_set_explore_mode(pump_ctx* ctx, int32_t mode);
 int pump_get_explore_mode(pump_ctx* ctx, int32_t* mode, int32_t* blocks);
 
@@ -355,8 +357,9 @@ int pump_get_explore_mode(pump_ctx* ctx, int32_t* mode, int32_t* blocks);
  * pump_explore_run then redo Explore from the root with one launch per phase
  * (mode 0 for that call only), which gives the same plan store, and count
  * the event.  They do the same when a round of the single launch has more
- * pairs than cap_pairs (the per-phase rounds run it in chunks).  pump_get_explore_fallbacks reports how many times that
- * happened on this context. */
+ * pairs than cap_pairs (the per-phase rounds run it in chunks).
+ * pump_get_explore_fallbacks reports how many times that happened on this
+ * context. */
 int pump_set_barrier_patience(pump_ctx* ctx, double ms);
 int pump_get_explore_fallbacks(pump_ctx* ctx, int64_t* n);
 
@@ -444,8 +447,7 @@ const char* pump_mlp_last_error(const pump_mlp* m);
  * team that runs all of its rounds, meeting at barriers (one workgroup for a
  * small query, several for a large one).  Each query's results equal those of pump_plan on
  * the same inputs (same per-element code, same orders).  Selection certifies
- * at most 32 Pareto-front plans per query (a larger front makes that query
- * report PUMP_E_CAPACITY).
+ * as many Pareto-front plans per query as pump_plan does.
  * ------------------------------------------------------------------------- */
 typedef struct pump_batch pump_batch;
 
