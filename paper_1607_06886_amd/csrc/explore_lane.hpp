@@ -10,14 +10,15 @@
 // particle cloud can meet a box, then takes the marked ones in order: each
 // box's hits come from the rank tables (rank_tables.hpp), a few lane
 // operations per face instead of a test per particle.  Wide records, whose
-// clouds meet many boxes, are tested by particle all the same (by_particle).
+// clouds meet many boxes, are tested by particle all the same (by_particle),
+// by their workgroup or, where many are wide, from a queue all workgroups share.
 //
 // Measured on the 20,000-sample indoor query (N = 256, 60 boxes; 1.0e7 pairs,
 // 9.5e6 tested waypoints, 1.1e7 box tests): expansion took 5.5 ms as a pair
 // kernel and a particle kernel with a wave per pair and a test per particle
-// (3.9 ms, bound by VALU issue), and takes 2.05 ms here.  What bounds it is
+// (3.9 ms, bound by VALU issue), and takes 2.1 to 2.3 ms here.  What bounds it is
 // latency: its waves wait some 60 % of their cycles on the chains of gathers,
-// at three waves per SIMD (151 registers for N = 256).
+// at three waves per SIMD (158 registers for N = 256).
 #pragma once
 
 #include "box_bins.hpp"

@@ -7,10 +7,13 @@
 // same index ranges), so the plan store is identical to the one the
 // per-round path builds, whatever the team size.
 //
-// Work split: expansion strides over pairs by workgroup pass, the staircase
-// update by thread.  Marking, compaction and the next group use contiguous chunks of the pair and open lists, one chunk per
-// member, so each scan needs one exchange of chunk totals: a member publishes
-// its totals and then adds those of the members before it.
+// Work split: expansion strides over pairs by workgroup pass, what it queues
+// (the half-space model's pairs; with the box model the marked records of a
+// round that follows one of many wide records) over the queue, the staircase
+// update by thread.  Marking, compaction and the next group use contiguous
+// chunks of the pair and open lists, one chunk per member, so each scan needs
+// one exchange of chunk totals: a member publishes its totals and then adds
+// those of the members before it.
 #pragma once
 
 #include "explore_half.hpp"

@@ -1,9 +1,10 @@
 // Batched engine: many planning queries of uneven size in one sequence of
 // launches with no host round trips (so it can be captured in one HIP graph).
 // Setup and selection run as batched kernels (the query index is a grid
-// dimension); Explore runs in one persistent kernel whose workgroups pull
-// whole queries from a queue and run every round of a query with block-level
-// synchronisation only.  Every per-element body is shared with the
+// dimension); Explore runs in one persistent kernel per particle count, whose
+// workgroups pull slots from a queue: the workgroups that hold a query's slots
+// are its team and run all of its rounds, meeting at the team's barriers (one
+// workgroup: its own only).  Every per-element body is shared with the
 // single-query path (explore_ops.hpp, setup_ops.hpp, select_ops.hpp) and runs
 // in the same orders, so each query's results equal its single-query results.
 #include "explore_team.hpp"
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(256) void k_b_edge_cost(BatchQuery* qs) {
 // drains.  A query's team sync words and totals were zeroed by k_b_reset.
 // One kernel per particle count N (a schedule holds only queries of that N),
 // so each gets the registers its own N needs: two workgroups of 256 per CU
-// fit for N <= 128, one for N = 256.
+// fit for every N (the box model's N = 256 takes all 256 registers of that bound).
 template <int N, int CP>
 __global__ __launch_bounds__(256, 2) void k_b_explore(BatchQuery* qs, BatchSched sch,
                                                                     int* counter, BatchOut* outs) {

@@ -193,9 +193,9 @@ __global__ __launch_bounds__(kRowThreads, 2) void k_mlp_forward(MlpDev d, const 
 }
 
 // A workgroup takes a CU (its weights in registers).  As long as every 16 rows
-// have one of the 256 CUs, a workgroup takes 16 rows (2048 to 4095 rows: 13.5 to
-// 14.5 us); beyond that 32, in one pass over the CUs where 16 would need two
-// (4096 rows 18.6 us, 4999: 19, 8192: 20.5).
+// have one of the 256 CUs, up to 4096 rows, a workgroup takes 16 (2048 to 4096
+// rows: 13.5 to 14.7 us; 4096 rows by 32: 18.6); beyond that 32, in one pass over
+// the CUs where 16 would need two (4999 rows 19 us, 8192: 20 to 25).
 constexpr int kNarrowRows = 16 * 256;
 
 void launch_mlp_forward(hipStream_t s, const MlpDev& d, const float* X, int B, float* out, int ld,

@@ -71,8 +71,9 @@ void launch_waypoints(hipStream_t s, const SelectArgs& a, int32_t n_paths) {
 
 // Rows of the MC grid: a workgroup takes front plans blockIdx.y, + gridDim.y,
 // ...; the deviations of a workgroup serve all of its plans, and too few workgroups
-// leave CUs idle.  Measured with 16, 8 and 4 rows: 66, 63 and 50 us on the
-// 20,000-sample indoor query, 25 to 24 on smaller fronts.
+// leave CUs idle.  Measured with 16, 8 and 4 rows: 61, 61 and 50 us on a
+// 20,000-sample indoor query (35 with 4 rows where its front is three plans), 21.5
+// on a 4000-sample query with any of them.
 constexpr int kMcRows = 4;
 
 __global__ __launch_bounds__(kMcThreads) void k_mc(SelectArgs a, int n_paths) {

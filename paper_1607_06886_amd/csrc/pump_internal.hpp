@@ -18,9 +18,10 @@ constexpr int kMaxFront = 256;        // Pareto front entries handled by selecti
 // 4 s unless the host sets another bound.
 constexpr unsigned long long kDefaultPatience = 400000000ull;
 constexpr int kMaxGoal = 1 << 16;     // goal plans gathered for selection
-// FP32 guard band of the particle test: a particle whose FP32 position is
-// within kGuard of a face is re-tested in FP64 (2^-14, far above the FP32
-// error of a position of magnitude <= 16).
+// FP32 guard band of a box's faces (2^-14, far above the FP32 error of a position
+// of magnitude <= 16): the boxes that the tests of the particle cloud use are
+// grown by it, those that count a particle as inside at once shrunk by it, and
+// the particles between are tested in FP64.
 constexpr float kGuard = 6.103515625e-05f;
 constexpr double kFlagEps = 1e-5;     // face distance counted as a flagged decision
 // A round queues its records if half of those marked in the round before were wide,
