@@ -21,10 +21,10 @@ inline pump_batch_tuning tuning_or_default(const pump_batch_tuning* t) {
 // default scale a team is also no larger than three times that share, or than its
 // query has use for beside others (16 workgroups at 2000 nodes, and with their
 // square), whichever is more: what a round's barriers cost grows with the team.
-// With 16 times the share throughout, 96 queries of 2000 samples took 11.1 ms, with
-// this 7.8 (1.5 times the share: 7.3; but 64 queries of 1000 to 8000 samples then
-// take 29.3 instead of 28.3, since a heavy one ends last); few queries keep the
-// whole device.
+// With 16 times the share throughout, planning 96 queries of 2000 samples took 10.8
+// ms, with this 7.6 (1.5 times the share: 7.3; but 64 queries of 1000 to 8000
+// samples then take 28.8 instead of 27.6, since a heavy one ends last); few queries
+// keep the whole device.
 inline int team_size(int team_scale, int grid, int team_cap, double work, double work_sum, double nodes) {
     if (team_scale <= 0 || !(work_sum > 0.0)) return 1;
     const double share = grid * work / work_sum;
