@@ -110,3 +110,30 @@ def test_flagged_counts_equal_the_oracle():
         assert r["partial_plans"] == ref["stats"]["partial_plans"]
         assert r["sim_box_tests"] >= 2.5 * r["sim_waypoints"]
         assert r["flagged"] == want
+
+
+@pytest.mark.parametrize("N,special", [(32, np.nan), (256, np.nan), (64, np.inf), (256, -np.inf)])
+def test_positions_that_are_no_numbers(N, special):
+    """A particle without a position on some axis is in no box, whichever way its
+    record is tested (by rank: test_gpu_rank_tables)."""
+    print_case("wide clouds, not finite", N=N, special=special)
+    sc = _scene(400, N, 40, 0.15, 60 + N)
+    for j, (step, row) in enumerate([(1, 0), (2, 2), (4, 4), (1, 1)]):   # particles 5, 12, 19, 26
+        sc.noise[step, row, 5 + 7 * j] = special
+    ref = None
+    for mode in (0, 1):
+        pl = planner_for(sc)
+        pl.set_explore_mode(mode)
+        r = pl.plan(pl.scene_problem(sc, device=True))
+        st, D = pl.plans(), pl.deviation()
+        if ref is None:
+            assert not np.isfinite(D[6:]).all(axis=(0, 1))[[5, 12, 19, 26]].any()
+            with np.errstate(invalid="ignore"):
+                n, hits = _check_plans(st, pl.graph(sc.n + 1), sc, D, 400)
+            print("  plans", n, "new hits", hits, "box tests", r["sim_box_tests"], "waypoints", r["sim_waypoints"],
+                  flush=True)
+            assert n > 50 and hits > 0 and r["sim_box_tests"] >= 3 * r["sim_waypoints"]
+            ref = st
+        for k in st:
+            np.testing.assert_array_equal(st[k], ref[k], err_msg=f"{mode} {k}")
+        pl.close()
