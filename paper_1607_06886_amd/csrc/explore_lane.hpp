@@ -285,6 +285,7 @@ __device__ __forceinline__ int flagged_count(const RoundArgs& a, const PairRec& 
 
 // Lane k's value in every lane (k wave-uniform).
 __device__ __forceinline__ int lane_int(int v, int k) { return __builtin_amdgcn_readlane(v, k); }
+__device__ __forceinline__ float lane_float(float v, int k) { return __int_as_float(lane_int(__float_as_int(v), k)); }
 __device__ __forceinline__ double lane_double(double v, int k) {
     const long long b = __double_as_longlong(v);
     const int lo = lane_int((int)(unsigned)(b & 0xFFFFFFFFll), k), hi = lane_int((int)(b >> 32), k);
@@ -296,7 +297,11 @@ __device__ __forceinline__ double lane_double(double v, int k) {
 // l, l + 64, ..., so the hits of particle row r are one ballot): at each marked
 // waypoint every particle against the boxes that the cloud meets, in FP32 with an
 // FP64 re-test inside the guard band, until the pair reaches the cutoff.  The next
-// waypoint's deviations are asked for before a waypoint is tested.
+// waypoint's deviations are asked for before a waypoint is tested, and the clouds of
+// all of them at the start where the registers are there (N < 256: a load and its
+// wait less for each); with 32 particles the halves of the wave take the boxes in
+// turn (1000 samples, 50 boxes, sigma 0.2, alpha 0.9, N = 32: 4.7 ms without the
+// two, 3.8 with them).
 //
 // For wide records.  A rank test takes a lane three dependent gathers for each face
 // that cuts the cloud; where a cloud is wider than a box that is most of its six
@@ -323,6 +328,8 @@ __device__ __forceinline__ void by_particle(const RoundArgs& a, const BoxLds& s,
     const int lane = threadIdx.x & 63;
     const bool valid = N >= 64 || lane < N;
     const int j0 = N >= 64 ? lane : (lane & (N - 1));
+    constexpr bool kHalves = N < 64;      // each half of the wave takes every other box
+    constexpr bool kCloudsHeld = N < 256; // (its registers are all taken)
     const int s_p = rec.ks >> 8;
     uint32_t wm = near;
     float d[PPL][3], dn[PPL][3];
@@ -333,13 +340,17 @@ __device__ __forceinline__ void by_particle(const RoundArgs& a, const BoxLds& s,
             for (int r = 0; r < PPL; ++r) dn[r][ax] = a.D[((size_t)(s_p + k) * 3 + ax) * N + r * 64 + j0];
     };
     ask(__ffs((int)wm));
-    // lane k - 1 holds waypoint k's nominal point
+    // lane k - 1 holds waypoint k's nominal point and cloud box
     double my_nom[3];
+    float my_lo[3], my_hi[3];
     {
+        float c6[6];
+        if (kCloudsHeld) load_cloud(a.cloud + (size_t)(s_p + min(lane + 1, rec.ks & 255)) * 6, c6);
         Cubic cs[3];
         const double dtk = record_cubics(a, rec, cs);
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) my_nom[ax] = cs[ax].at((double)(lane + 1) * dtk);
+        if (kCloudsHeld) cloud_box(my_nom, c6, my_lo, my_hi);
     }
     uint32_t par = 0u;   // the parent's bits of this lane's particles
 #pragma unroll
@@ -359,11 +370,20 @@ __device__ __forceinline__ void by_particle(const RoundArgs& a, const BoxLds& s,
         if (wm) ask(__ffs((int)wm));
         ++n.wp;
         double nom[3];
-        float c6[6], lo3[3], hi3[3];
+        float lo3[3], hi3[3];
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) nom[ax] = lane_double(my_nom[ax], k - 1);
-        load_cloud(a.cloud + (size_t)(s_p + k) * 6, c6);
-        cloud_box(nom, c6, lo3, hi3);
+        if (kCloudsHeld) {
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                lo3[ax] = lane_float(my_lo[ax], k - 1);
+                hi3[ax] = lane_float(my_hi[ax], k - 1);
+            }
+        } else {
+            float c6[6];
+            load_cloud(a.cloud + (size_t)(s_p + k) * 6, c6);
+            cloud_box(nom, c6, lo3, hi3);
+        }
         float y[PPL][3];
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
@@ -376,8 +396,12 @@ __device__ __forceinline__ void by_particle(const RoundArgs& a, const BoxLds& s,
             unsigned long long om = __ballot(o < s.n_obs && boxes_overlap(lo3, hi3, s.out + o * 6));
             n.bt += (int)__popcll(om);
             while (om) {
-                const int ob = c0 + __ffsll((long long)om) - 1;
+                int ob = c0 + __ffsll((long long)om) - 1;
                 om &= om - 1ull;
+                if (kHalves && om) {
+                    if (lane >= N) ob = c0 + __ffsll((long long)om) - 1;
+                    om &= om - 1ull;
+                }
                 // u = max over axes of |y - c| - (h - g): u <= 0, inside by more
                 // than the guard band (a hit, deep); 0 < u <= 2 g, within it,
                 // decided in FP64 (rare)
@@ -393,7 +417,7 @@ __device__ __forceinline__ void by_particle(const RoundArgs& a, const BoxLds& s,
                 }
                 hm |= inb;
                 dm |= inb;
-                if (!valid) bnd = 0u;
+                if (!valid && !kHalves) bnd = 0u;
                 if (__ballot(bnd != 0u) == 0ull) continue;
                 const float* b = s.raw + ob * 6;
 #pragma unroll
@@ -417,9 +441,14 @@ __device__ __forceinline__ void by_particle(const RoundArgs& a, const BoxLds& s,
             }
         }
         int cnt = 0;
+        if (kHalves) hm |= (uint32_t)__shfl_xor((int)hm, N, 64);
 #pragma unroll
         for (int r = 0; r < PPL; ++r) cnt += (int)__popcll(__ballot(valid && (((hm | par) >> r) & 1u)));
         if (!wm || cnt >= a.c_cut) break;
+    }
+    if (kHalves) {
+        dm |= (uint32_t)__shfl_xor((int)dm, N, 64);
+        nm |= (uint32_t)__shfl_xor((int)nm, N, 64);
     }
     uint32_t words[W];
     int popc = 0, flg = 0;

@@ -137,3 +137,22 @@ def test_positions_that_are_no_numbers(N, special):
         for k in st:
             np.testing.assert_array_equal(st[k], ref[k], err_msg=f"{mode} {k}")
         pl.close()
+
+
+def test_flagged_counts_of_half_waves():
+    """(32 particles: each half of a wave tests every other box.)"""
+    print_case("wide clouds, flagged, 32 particles")
+    sc = _scene(220, 32, 25, 0.12, 3)
+    sc.obstacles[:, 2] = np.float32(0.0)     # boxes from the floor up: more decisions near a face
+    ref = opump.run(sc, CFG)
+    for mode in (0, 1):
+        pl = planner_for(sc, preprune=0)
+        pl.set_explore_mode(mode)
+        r = pl.plan(pl.scene_problem(sc, device=True))
+        pl.close()
+        print("  flagged", r["flagged"], ref["stats"]["flagged_below_cut"], "box tests", r["sim_box_tests"], "waypoints",
+              r["sim_waypoints"], flush=True)
+        assert r["partial_plans"] == ref["stats"]["partial_plans"]
+        assert r["sim_box_tests"] >= 2 * r["sim_waypoints"]
+        assert r["flagged"] == ref["stats"]["flagged_below_cut"]
+    assert ref["stats"]["flagged_below_cut"] > 0
